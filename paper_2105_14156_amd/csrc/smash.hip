@@ -58,14 +58,14 @@ enum KernelId {
     K_VALIDATE, K_ANALYZE, K_BIN_COUNT, K_BIN_SCAN, K_SCATTER, K_SYM_ROWS, K_BSPLIT, K_SYM_HEAVY,
     K_SYM_GLOBAL, K_FILL, K_SCAN_REDUCE, K_SCAN_TOP, K_SCAN_APPLY, K_NUM_BINS, K_CHUNK_PREFIX,
     K_SEG_PLAN, K_SEG_SCAN, K_NUM_ROWS, K_NUM_SEG, K_NUM_DENSE, K_NUM_GLOBAL, K_FEATURES, K_MLP_PREDICT,
-    K_MLP_FWD, K_MLP_BWD, K_ADAM, K_FUSED_ROWS, K_FUSED_AUX, K_FUSED_COPY, K_WS_QUERY, K_COUNT
+    K_MLP_STEP, K_ADAM, K_FUSED_ROWS, K_FUSED_AUX, K_FUSED_COPY, K_WS_QUERY, K_COUNT
 };
 
 const char *const kKernelNames[K_COUNT] = {
     "validate", "analyze", "bin_count", "bin_scan", "scatter", "sym_rows", "bsplit", "sym_heavy",
     "sym_global", "fill", "scan_reduce", "scan_top", "scan_apply", "num_bins", "chunk_prefix",
     "seg_plan", "seg_scan", "num_rows", "num_seg", "num_dense", "num_global", "features", "mlp_predict",
-    "mlp_fwd", "mlp_bwd", "adam", "fused_rows", "fused_aux", "fused_copy", "ws_query"};
+    "mlp_step", "adam", "fused_rows", "fused_aux", "fused_copy", "ws_query"};
 
 // Grow-only device buffer of the context (predictor weights, training
 // buffers): not used by the multiply's calls.
@@ -1284,46 +1284,34 @@ smash_status smash_mlp_predict(smash_ctx c, int64_t m, const float *feats, const
 namespace {
 
 struct MlpBufs {
-    float *h1, *h2, *dz2, *dz1, *dy, *grad, *mom, *vel;
-    double *sse;
+    float *mom, *vel;
+    double *part, *sse;
 };
+
+// Blocks of a training step over n samples: its number of partial gradients.
+int mlp_blocks(long long n) { return (int)std::min<long long>(blocks_for(n, kTrainTile), kTrainMaxBlocks); }
 
 smash_status mlp_bufs(smash_ctx c, hipStream_t s, int batch, long long sse_slots, MlpBufs &b)
 {
-    const size_t need = carve_size({(size_t)batch * kHid * 4, (size_t)batch * kHid * 4, (size_t)batch * kHid * 4,
-                                    (size_t)batch * kHid * 4, (size_t)batch * 4, (size_t)kParams * 4,
-                                    (size_t)kParams * 4, (size_t)kParams * 4, (size_t)sse_slots * 8});
+    const size_t parts = (size_t)mlp_blocks(batch) * kParams;
+    const size_t need = carve_size({(size_t)kParams * 4, (size_t)kParams * 4, parts * 8, (size_t)sse_slots * 8});
     TRY(ensure(c, c->mlp_mem, need, s));
     Carve cv{(char *)c->mlp_mem.ptr};
-    b.h1 = cv.take<float>((size_t)batch * kHid);
-    b.h2 = cv.take<float>((size_t)batch * kHid);
-    b.dz2 = cv.take<float>((size_t)batch * kHid);
-    b.dz1 = cv.take<float>((size_t)batch * kHid);
-    b.dy = cv.take<float>(batch);
-    b.grad = cv.take<float>(kParams);
     b.mom = cv.take<float>(kParams);
     b.vel = cv.take<float>(kParams);
+    b.part = cv.take<double>(parts);
     b.sse = cv.take<double>(sse_slots);
     return SMASH_OK;
 }
 
-// Forward and backward of one batch; leaves the gradient in b.grad and the
-// block sums of squared errors in sse[0 .. ceil(n/256)).
+// Forward and backward of one batch; leaves the partial gradients in b.part
+// and the blocks' sums of squared errors in sse[0 .. mlp_blocks(n)).
 smash_status mlp_step(smash_ctx c, hipStream_t s, const float *feats, const float *targets, const int *idx, int n,
                       const float *ms, const float *params, MlpBufs &b, double *sse)
 {
-    TRY(launch(c, K_MLP_FWD, s, [&] {
-        k_mlp_fwd<<<blocks_for(n, 256), 256, 0, s>>>(n, idx, feats, targets, ms, params, b.h1, b.h2, b.dy, sse);
-    }));
-    TRY(launch(c, K_MLP_BWD, s, [&] {
-        k_mlp_grad_out<<<kHid + 1, 256, 0, s>>>(n, b.h2, b.dy, params, b.dz2, b.grad);
-    }));
-    TRY(launch(c, K_MLP_BWD, s, [&] { k_mlp_grad_mid<<<kHid, 256, 0, s>>>(n, b.h1, b.dz2, b.grad); }));
-    TRY(launch(c, K_MLP_BWD, s, [&] {
-        k_mlp_back_h1<<<blocks_for((long long)n * kHid, 256), 256, 0, s>>>(n, b.h1, b.dz2, params, b.dz1);
-    }));
-    TRY(launch(c, K_MLP_BWD, s, [&] { k_mlp_grad_in<<<kHid, 256, 0, s>>>(n, idx, feats, ms, b.dz1, b.grad); }));
-    return SMASH_OK;
+    return launch(c, K_MLP_STEP, s, [&] {
+        k_mlp_step<<<mlp_blocks(n), kTrainThreads, 0, s>>>(n, idx, feats, targets, ms, params, b.part, sse);
+    });
 }
 
 }  // namespace
@@ -1340,10 +1328,10 @@ smash_status smash_mlp_loss_grad(smash_ctx c, const float *feats, const float *t
         return fail(c, SMASH_ERR_INVALID_ARG, "null pointer");
     DeviceGuard g(c->device);
     MlpBufs b;
-    const int nb = (int)blocks_for(n, 256);
+    const int nb = mlp_blocks(n);
     TRY(mlp_bufs(c, s, (int)n, nb, b));
     TRY(mlp_step(c, s, feats, targets, idx, (int)n, ms, params, b, b.sse));
-    HIP_TRY(c, hipMemcpyAsync(grad, b.grad, kParams * sizeof(float), hipMemcpyDeviceToDevice, s));
+    TRY(launch(c, K_ADAM, s, [&] { k_mlp_grad<<<blocks_for(kParams, kWave), kWave, 0, s>>>(nb, b.part, grad); }));
     std::vector<double> part(nb);
     HIP_TRY(c, hipMemcpyAsync(part.data(), b.sse, nb * sizeof(double), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
@@ -1367,7 +1355,7 @@ smash_status smash_mlp_train(smash_ctx c, const float *feats, const float *targe
     DeviceGuard g(c->device);
     const int batch = (int)std::min<int64_t>(a->batch, n);
     const int steps = (int)((n + batch - 1) / batch);
-    const int nbmax = (int)blocks_for(batch, 256);
+    const int nbmax = mlp_blocks(batch);
     const long long slots = (long long)a->epochs * steps * nbmax;
     MlpBufs b;
     TRY(mlp_bufs(c, s, batch, slots, b));
@@ -1383,8 +1371,8 @@ smash_status smash_mlp_train(smash_ctx c, const float *feats, const float *targe
             TRY(mlp_step(c, s, feats, targets, idx, nb, ms, params, b, b.sse + ((long long)e * steps + st) * nbmax));
             ++t;
             TRY(launch(c, K_ADAM, s, [&] {
-                k_adam<<<blocks_for(kParams, 256), 256, 0, s>>>(kParams, params, b.grad, b.mom, b.vel, t, a->lr,
-                                                               a->beta1, a->beta2, a->eps);
+                k_mlp_adam<<<blocks_for(kParams, kWave), kWave, 0, s>>>(mlp_blocks(nb), b.part, params, b.mom, b.vel, t,
+                                                                       a->lr, a->beta1, a->beta2, a->eps);
             }));
         }
     }

@@ -72,10 +72,8 @@ __device__ __forceinline__ void load_params(float *s_w, const float *__restrict_
     for (int t = threadIdx.x; t < kParams; t += blockDim.x) s_w[t] = theta[t];
 }
 
-// Network output for one standardized feature vector; h1/h2 receive the
-// hidden activations when non-null.
-__device__ __forceinline__ float mlp_eval(const float *s_w, const float x[kFeat], float *h1_out, float *h2_out,
-                                          int stride)
+// Network output for one standardized feature vector.
+__device__ __forceinline__ float mlp_eval(const float *s_w, const float x[kFeat])
 {
     float h1[kHid];
 #pragma unroll
@@ -84,16 +82,13 @@ __device__ __forceinline__ float mlp_eval(const float *s_w, const float x[kFeat]
 #pragma unroll
         for (int f = 0; f < kFeat; ++f) z = fmaf(s_w[kOW1 + i * kFeat + f], x[f], z);
         h1[i] = z > 0.f ? z : 0.f;
-        if (h1_out) h1_out[i * stride] = h1[i];
     }
     float y = s_w[kOB3];
     for (int j = 0; j < kHid; ++j) {
         float z = s_w[kOB2 + j];
 #pragma unroll
         for (int i = 0; i < kHid; ++i) z = fmaf(s_w[kOW2 + j * kHid + i], h1[i], z);
-        const float h = z > 0.f ? z : 0.f;
-        if (h2_out) h2_out[j * stride] = h;
-        y = fmaf(s_w[kOW3 + j], h, y);
+        y = fmaf(s_w[kOW3 + j], z > 0.f ? z : 0.f, y);
     }
     return y;
 }
@@ -156,7 +151,7 @@ __global__ __launch_bounds__(256) void k_mlp_predict(int m, int ncols, const flo
         float x[kFeat];
 #pragma unroll
         for (int f = 0; f < kFeat; ++f) x[f] = (feats[(long long)i * kFeat + f] - s_ms[f]) / s_ms[kFeat + f];
-        const float y = mlp_eval(s_w, x, nullptr, nullptr, 0);
+        const float y = mlp_eval(s_w, x);
         if (yhat_out) yhat_out[i] = y;
         if (cap_out) cap_out[i] = predicted_capacity(y, delta, ub[i], maxb[i], ncols);
         return;
@@ -200,137 +195,209 @@ __global__ __launch_bounds__(256) void k_mlp_predict(int m, int ncols, const flo
 
 // ------------------------------------------------------------ training
 
-// Forward pass of one batch (one thread per sample): hidden activations
-// h1, h2 (batch x 64, sample-major), dL/dyhat = 2 (yhat - y) / n, and the
-// block's sum of squared errors.
-__global__ __launch_bounds__(256) void k_mlp_fwd(int n, const int *__restrict__ idx, const float *__restrict__ feats,
-                                                 const float *__restrict__ y, const float *__restrict__ ms,
-                                                 const float *__restrict__ theta, float *__restrict__ h1,
-                                                 float *__restrict__ h2, float *__restrict__ dy,
-                                                 double *__restrict__ sse_part)
+// One training step is two launches: k_mlp_step takes the batch forward and
+// backward in tiles of 64 samples and leaves one partial gradient per block;
+// k_mlp_adam (or k_mlp_grad) adds the partials in block order and updates.
+// Everything a tile computes stays in registers and LDS.  At batch 4096 the
+// step is bound by latency (18M multiply-adds on 64 of 256 CUs): five separate
+// kernels through global activations took 371 us a step, 292 of them in the
+// 64 x 64 x batch contraction dW2 on 64 blocks of strided loads; as two
+// launches with that contraction on the FP64 matrix instruction a step takes
+// 32 us (23 forward and backward, 6 sums and update).
+constexpr int kTrainTile = 64;        // samples per tile: one per lane
+constexpr int kTrainThreads = 256;    // four waves: 16 hidden units each
+constexpr int kTrainMaxBlocks = 256;  // partial gradients at most (one block per CU)
+constexpr int kTrainLd = kTrainTile + 4;
+
+typedef double mlp_f64x4 __attribute__((ext_vector_type(4)));
+
+// The gradient sums use V_MFMA_F64_16X16X4 (D += A B): lane l gives A[l % 16][k]
+// and B[k][l % 16] with k = l / 16, and holds rows 4 r + l / 16 (r = 0..3),
+// column l % 16 of D.  Products of two floats are exact in FP64.  Rows of the
+// LDS arrays are padded to 68 floats, so that those reads touch every bank
+// once and float4 reads stay aligned.
+// Forward and backward of the batch idx[0, n): block b takes tiles b, b +
+// gridDim.x, ... and writes its sums of the gradient to part[b] (FP64) and of
+// the squared errors to sse_part[b].  The two 64 x 64 x 64 products of a tile
+// (z2 = W2 h1 and W2^T dz2) are register tiles of 4 units x 4 samples per
+// thread, weights and activations read from LDS as float4; loops stay rolled,
+// since straight-line code run once per launch is bound by instruction
+// fetches (weights through scalar loads in unrolled code: 44 us a launch at
+// batch 4096, 23 us so).  Every unit adds its inputs in the order of
+// mlp_eval.  Gradient sums are FP64 in a fixed order (no atomics), so
+// training is deterministic.
+__global__ __launch_bounds__(kTrainThreads) void k_mlp_step(int n, const int *__restrict__ idx,
+                                                            const float *__restrict__ feats,
+                                                            const float *__restrict__ y, const float *__restrict__ ms,
+                                                            const float *__restrict__ theta, double *__restrict__ part,
+                                                            double *__restrict__ sse_part)
 {
-    __shared__ float s_w[kParams];
-    __shared__ float s_ms[2 * kFeat];
-    __shared__ double s_tmp[256 / kWave + 1];
+    static_assert(kTrainTile == kWave && kTrainThreads == 4 * kWave && kHid == 64, "tile shape");
+    constexpr int U = kHid / 4;         // hidden units per wave
+    __shared__ __align__(16) float s_w[kParams];
+    __shared__ __align__(16) float s_h1[kHid * kTrainLd], s_h2[kHid * kTrainLd];
+    __shared__ __align__(16) float s_dz2[kHid * kTrainLd], s_dz1[kHid * kTrainLd];
+    __shared__ float s_x[16 * kTrainLd];    // rows 0..5 the inputs, row 6 ones, row 7 dL/dy, the others zero
+    const int lane = lane_id(), u0 = (int)threadIdx.x / kWave * U;
+    const int tu = (int)threadIdx.x / 16 * 4, ts = (int)threadIdx.x % 16 * 4;   // this thread's 4 x 4 tile
     load_params(s_w, theta);
-    if (threadIdx.x < 2 * kFeat) s_ms[threadIdx.x] = ms[threadIdx.x];
-    __syncthreads();
-    const int s = blockIdx.x * blockDim.x + threadIdx.x;
-    double se = 0.0;
-    if (s < n) {
-        const long long r = idx[s];
+    for (int t = threadIdx.x; t < 16 * kTrainLd; t += kTrainThreads) s_x[t] = t / kTrainLd == kFeat ? 1.f : 0.f;
+    mlp_f64x4 gw2[4] = {}, gin = {}, gout = {}, gb2 = {};
+    double se = 0.0, gb3 = 0.0;
+    for (int tile = blockIdx.x; tile < (n + kTrainTile - 1) / kTrainTile; tile += gridDim.x) {
+        const int s = tile * kTrainTile + lane;
+        const bool live = s < n;
+        const long long r = live ? idx[s] : 0;
         float x[kFeat];
 #pragma unroll
-        for (int f = 0; f < kFeat; ++f) x[f] = (feats[r * kFeat + f] - s_ms[f]) / s_ms[kFeat + f];
-        const float yh = mlp_eval(s_w, x, h1 + (long long)s * kHid, h2 + (long long)s * kHid, 1);
-        const float res = yh - y[r];
-        dy[s] = 2.f * res / (float)n;
-        se = (double)res * (double)res;
-    }
-    double tot;
-    block_excl_scan<double, 256>(se, s_tmp, tot);
-    if (threadIdx.x == 0) sse_part[blockIdx.x] = tot;
-}
-
-// Output layer gradients: block j < 64 computes dw3[j] = sum_s dy_s h2[s][j]
-// and writes dz2[s][j] = dy_s w3[j] [h2[s][j] > 0]; block 64 computes db3.
-__global__ __launch_bounds__(256) void k_mlp_grad_out(int n, const float *__restrict__ h2, const float *__restrict__ dy,
-                                                      const float *__restrict__ theta, float *__restrict__ dz2,
-                                                      float *__restrict__ grad)
-{
-    __shared__ double s_tmp[256 / kWave + 1];
-    const int j = blockIdx.x;
-    double acc = 0.0;
-    if (j < kHid) {
-        const float w = theta[kOW3 + j];
-        for (int s = threadIdx.x; s < n; s += 256) {
-            const float h = h2[(long long)s * kHid + j];
-            acc += (double)dy[s] * (double)h;
-            dz2[(long long)s * kHid + j] = h > 0.f ? dy[s] * w : 0.f;
-        }
-    } else {
-        for (int s = threadIdx.x; s < n; s += 256) acc += (double)dy[s];
-    }
-    double tot;
-    block_excl_scan<double, 256>(acc, s_tmp, tot);
-    if (threadIdx.x == 0) grad[j < kHid ? kOW3 + j : kOB3] = (float)tot;
-}
-
-// Hidden layer 2: block j computes dW2[j][i] = sum_s dz2[s][j] h1[s][i] for
-// all i (4 partial sums per i over interleaved samples) and db2[j].
-__global__ __launch_bounds__(256) void k_mlp_grad_mid(int n, const float *__restrict__ h1,
-                                                      const float *__restrict__ dz2, float *__restrict__ grad)
-{
-    __shared__ double s_part[4][kHid];
-    __shared__ double s_tmp[256 / kWave + 1];
-    const int j = blockIdx.x;
-    const int i = threadIdx.x % kHid, q = threadIdx.x / kHid;
-    double acc = 0.0, accb = 0.0;
-    for (int s = q; s < n; s += 4) {
-        const float d = dz2[(long long)s * kHid + j];
-        acc += (double)d * (double)h1[(long long)s * kHid + i];
-        if (i == 0) accb += (double)d;
-    }
-    s_part[q][i] = acc;
-    double totb;
-    block_excl_scan<double, 256>(accb, s_tmp, totb);
-    if (threadIdx.x < kHid)
-        grad[kOW2 + j * kHid + threadIdx.x] =
-            (float)(s_part[0][threadIdx.x] + s_part[1][threadIdx.x] + s_part[2][threadIdx.x] + s_part[3][threadIdx.x]);
-    if (threadIdx.x == 0) grad[kOB2 + j] = (float)totb;
-}
-
-// Back through W2: dz1[s][i] = (sum_j W2[j][i] dz2[s][j]) [h1[s][i] > 0],
-// one thread per (sample, i).
-__global__ __launch_bounds__(256) void k_mlp_back_h1(int n, const float *__restrict__ h1,
-                                                     const float *__restrict__ dz2, const float *__restrict__ theta,
-                                                     float *__restrict__ dz1)
-{
-    __shared__ float s_w2[kHid * kHid];
-    for (int t = threadIdx.x; t < kHid * kHid; t += 256) s_w2[t] = theta[kOW2 + t];
-    __syncthreads();
-    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
-    if (t >= (long long)n * kHid) return;
-    const long long s = t / kHid;
-    const int i = (int)(t % kHid);
-    float acc = 0.f;
-    const float *d = dz2 + s * kHid;
-#pragma unroll 8
-    for (int j = 0; j < kHid; ++j) acc = fmaf(s_w2[j * kHid + i], d[j], acc);
-    dz1[t] = h1[t] > 0.f ? acc : 0.f;
-}
-
-// Input layer: block i computes dW1[i][f] = sum_s dz1[s][i] x[s][f] and
-// db1[i].
-__global__ __launch_bounds__(256) void k_mlp_grad_in(int n, const int *__restrict__ idx, const float *__restrict__ feats,
-                                                     const float *__restrict__ ms, const float *__restrict__ dz1,
-                                                     float *__restrict__ grad)
-{
-    __shared__ double s_tmp[256 / kWave + 1];
-    const int i = blockIdx.x;
-    double acc[kFeat + 1] = {0, 0, 0, 0, 0, 0, 0};
-    for (int s = threadIdx.x; s < n; s += 256) {
-        const float d = dz1[(long long)s * kHid + i];
-        const long long r = idx[s];
+        for (int f = 0; f < kFeat; ++f) x[f] = live ? (feats[r * kFeat + f] - ms[f]) / ms[kFeat + f] : 0.f;
+        const float target = live ? y[r] : 0.f;
+        __syncthreads();                    // weights in; the last tile's sums are done with the arrays
+#pragma unroll 4
+        for (int i = u0; i < u0 + U; ++i) {
+            float z = s_w[kOB1 + i];
 #pragma unroll
-        for (int f = 0; f < kFeat; ++f) acc[f] += (double)d * (double)((feats[r * kFeat + f] - ms[f]) / ms[kFeat + f]);
-        acc[kFeat] += (double)d;
+            for (int f = 0; f < kFeat; ++f) z = fmaf(s_w[kOW1 + i * kFeat + f], x[f], z);
+            s_h1[i * kTrainLd + lane] = live && z > 0.f ? z : 0.f;
+        }
+        __syncthreads();
+        float acc[4][4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[u][q] = s_w[kOB2 + tu + u];
+#pragma unroll 1
+        for (int i = 0; i < kHid; i += 4) {
+            float4 w[4], h[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) w[u] = *(const float4 *)&s_w[kOW2 + (tu + u) * kHid + i];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) h[k] = *(const float4 *)&s_h1[(i + k) * kTrainLd + ts];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const float wk[4] = {w[u].x, w[u].y, w[u].z, w[u].w};
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    acc[u][0] = fmaf(wk[k], h[k].x, acc[u][0]);
+                    acc[u][1] = fmaf(wk[k], h[k].y, acc[u][1]);
+                    acc[u][2] = fmaf(wk[k], h[k].z, acc[u][2]);
+                    acc[u][3] = fmaf(wk[k], h[k].w, acc[u][3]);
+                }
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            float h[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                h[q] = tile * kTrainTile + ts + q < n && acc[u][q] > 0.f ? acc[u][q] : 0.f;
+            *(float4 *)&s_h2[(tu + u) * kTrainLd + ts] = make_float4(h[0], h[1], h[2], h[3]);
+        }
+        __syncthreads();
+        float yh = s_w[kOB3];
+#pragma unroll 16
+        for (int j = 0; j < kHid; ++j) yh = fmaf(s_w[kOW3 + j], s_h2[j * kTrainLd + lane], yh);
+        const float res = yh - target;
+        const float dy = live ? 2.f * res / (float)n : 0.f;
+        if (u0 == 0) {
+            se += live ? (double)res * (double)res : 0.0;
+            gb3 += (double)dy;
+#pragma unroll
+            for (int f = 0; f < kFeat; ++f) s_x[f * kTrainLd + lane] = x[f];
+            s_x[(kFeat + 1) * kTrainLd + lane] = dy;
+        }
+#pragma unroll 4
+        for (int j = u0; j < u0 + U; ++j)
+            s_dz2[j * kTrainLd + lane] = s_h2[j * kTrainLd + lane] > 0.f ? dy * s_w[kOW3 + j] : 0.f;
+        __syncthreads();
+        // back through W2: dz1_i = (sum_j W2[j][i] dz2_j) [h1_i > 0]
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[u][q] = 0.f;
+#pragma unroll 4
+        for (int j = 0; j < kHid; ++j) {
+            const float4 w = *(const float4 *)&s_w[kOW2 + j * kHid + tu];
+            const float4 d = *(const float4 *)&s_dz2[j * kTrainLd + ts];
+            const float wu[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                acc[u][0] = fmaf(wu[u], d.x, acc[u][0]);
+                acc[u][1] = fmaf(wu[u], d.y, acc[u][1]);
+                acc[u][2] = fmaf(wu[u], d.z, acc[u][2]);
+                acc[u][3] = fmaf(wu[u], d.w, acc[u][3]);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float4 h = *(const float4 *)&s_h1[(tu + u) * kTrainLd + ts];
+            *(float4 *)&s_dz1[(tu + u) * kTrainLd + ts] =
+                make_float4(h.x > 0.f ? acc[u][0] : 0.f, h.y > 0.f ? acc[u][1] : 0.f, h.z > 0.f ? acc[u][2] : 0.f,
+                            h.w > 0.f ? acc[u][3] : 0.f);
+        }
+        __syncthreads();
+        // gradient sums over the tile's samples: dW2 (16 x 64 per wave), db2
+        // (against the row of ones), dW1 and db1 (inputs and ones), dw3
+#pragma unroll 2
+        for (int t = 0; t < kTrainTile / 4; ++t) {
+            const int at = (lane & 15) * kTrainLd + (lane >> 4) + 4 * t;
+            const double d2 = (double)s_dz2[u0 * kTrainLd + at], xx = (double)s_x[at];
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                gw2[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(d2, (double)s_h1[c * 16 * kTrainLd + at], gw2[c], 0, 0, 0);
+            gb2 = __builtin_amdgcn_mfma_f64_16x16x4f64(d2, xx, gb2, 0, 0, 0);
+            gin = __builtin_amdgcn_mfma_f64_16x16x4f64((double)s_dz1[u0 * kTrainLd + at], xx, gin, 0, 0, 0);
+            gout = __builtin_amdgcn_mfma_f64_16x16x4f64((double)s_h2[u0 * kTrainLd + at], xx, gout, 0, 0, 0);
+        }
     }
-    for (int f = 0; f <= kFeat; ++f) {
-        double tot;
-        block_excl_scan<double, 256>(acc[f], s_tmp, tot);
-        if (threadIdx.x == 0) grad[f < kFeat ? kOW1 + i * kFeat + f : kOB1 + i] = (float)tot;
+    double *o = part + (long long)blockIdx.x * kParams;
+    const int c = lane & 15;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int u = u0 + 4 * q + (lane >> 4);
+#pragma unroll
+        for (int t = 0; t < 4; ++t) o[kOW2 + u * kHid + t * 16 + c] = gw2[t][q];
+        if (c < kFeat) o[kOW1 + u * kFeat + c] = gin[q];
+        if (c == kFeat) {
+            o[kOB1 + u] = gin[q];
+            o[kOB2 + u] = gb2[q];
+        }
+        if (c == kFeat + 1) o[kOW3 + u] = gout[q];
+    }
+    if (u0 == 0) {
+        se = wave_sum(se);
+        gb3 = wave_sum(gb3);
+        if (lane == 0) {
+            o[kOB3] = gb3;
+            sse_part[blockIdx.x] = se;
+        }
     }
 }
 
-// Adam update of every parameter (t counts steps from 1).
-__global__ __launch_bounds__(256) void k_adam(int np, float *__restrict__ theta, const float *__restrict__ grad,
-                                              float *__restrict__ mom, float *__restrict__ vel, int t, float lr,
-                                              float b1, float b2, float eps)
+// Gradient of parameter p: the blocks' partial sums in order.
+__device__ __forceinline__ float mlp_grad_sum(int nb, int p, const double *__restrict__ part)
 {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= np) return;
-    const float g = grad[p];
+    double g = 0.0;
+#pragma unroll 16
+    for (int b = 0; b < nb; ++b) g += part[(long long)b * kParams + p];
+    return (float)g;
+}
+
+__global__ __launch_bounds__(kWave) void k_mlp_grad(int nb, const double *__restrict__ part, float *__restrict__ grad)
+{
+    const int p = blockIdx.x * kWave + threadIdx.x;
+    if (p < kParams) grad[p] = mlp_grad_sum(nb, p, part);
+}
+
+// Adam update of every parameter from the step's partial gradients (t counts
+// steps from 1).
+__global__ __launch_bounds__(kWave) void k_mlp_adam(int nb, const double *__restrict__ part, float *__restrict__ theta,
+                                                    float *__restrict__ mom, float *__restrict__ vel, int t, float lr,
+                                                    float b1, float b2, float eps)
+{
+    const int p = blockIdx.x * kWave + threadIdx.x;
+    if (p >= kParams) return;
+    const float g = mlp_grad_sum(nb, p, part);
     const float m = b1 * mom[p] + (1.f - b1) * g;
     const float v = b2 * vel[p] + (1.f - b2) * g * g;
     mom[p] = m;

@@ -65,6 +65,29 @@ def test_predict_and_gradient_parity(env):
         pos += k
 
 
+@pytest.mark.parametrize("n", [1, 64, 65, 16384, 16449])
+def test_gradient_tile_edges(env, n):
+    """Batches around one tile of 64 samples and around one tile per block of
+    the largest grid (256): one lane, a full tile, a remainder, a second tile
+    in one block.  Gradients are FP64 sums rounded once (2^-24 relative), their
+    FP32 terms carry the forward pass's roundings (about 70 dependent
+    operations of 2^-24 each, amplified by cancellation): 1e-4 of each block's
+    norm."""
+    torch, smash, ctx = env
+    F, y, ms, th, t = _setup(torch, n=3000, seed=13)
+    X = (F - ms[:6]) / ms[6:]
+    idx = (syn.uniform01(19, 0, n) * len(y)).astype(np.int32)
+    loss, grad = ctx.mlp_loss_grad(t(F), t(y), t(idx, torch.int32), t(ms), t(th))
+    rloss, rgrad = mlp.loss_grad(th, X[idx], y[idx])
+    assert abs(loss - rloss) <= 1e-5 * rloss
+    g = grad.cpu().numpy().astype(np.float64)
+    pos = 0
+    for name, shape in syn.MLP_LAYOUT:
+        k = int(np.prod(shape))
+        assert _rel(g[pos:pos + k], rgrad[pos:pos + k]) < 1e-4, name
+        pos += k
+
+
 def test_training_parity(env):
     torch, smash, ctx = env
     F, y, ms, th, t = _setup(torch, n=2000, seed=5)
