@@ -537,11 +537,17 @@ smash_status numeric_impl(smash_ctx c, hipStream_t s, const Plan &p, const V *Av
     const int H = p.hdr.sym.count[kBinHeavy];
     if (H == 0) return SMASH_OK;
     if (p.heavy_mode == 0) {
-        // segments of up to 128 entries (table of 256 slots): one wave; up to
-        // 700 (1024 slots) and up to 1024 entries (2048 slots): four waves
+        // segments of up to 128 entries are hashed by one wave (table of 256
+        // slots), larger ones ranked
         TRY(launch_seg_bin<V, 8, 64>(c, s, p, 0, Aval, Bval, crp, ccol, cval));
-        TRY(launch_seg_bin<V, 10, 256>(c, s, p, 1, Aval, Bval, crp, ccol, cval));
-        TRY(launch_seg_bin<V, 11, 256>(c, s, p, 2, Aval, Bval, crp, ccol, cval));
+        if (const int nr = p.hdr.seg.count[1]) {
+            const int grid = std::min(nr, resident_blocks(c, (const void *)k_num_rank<V>, kRankThreads, 0));
+            TRY(launch(c, K_NUM_SEG, s, [&] {
+                k_num_rank<V><<<grid, kRankThreads, 0, s>>>(p.A.col_idx, Aval, p.B.col_idx, Bval, p.bsplit,
+                                                           (long long)(p.nchunks + 1), p.segs + p.hdr.seg.offset[1],
+                                                           nr, ccol, cval, c->d_numerr);
+            }));
+        }
         const int nd = p.hdr.seg.count[kSegDense];
         if (nd) {
             const size_t lds = (size_t)kChunkCols * sizeof(double);

@@ -41,6 +41,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace smash {
 
 constexpr int kWave = 64;
@@ -54,11 +56,12 @@ constexpr int kNumBins = kLdsBins + 2;
 constexpr int kChunkCols = 8192;        // column granularity of heavy-row counts
 constexpr int kChunkWords = kChunkCols / 32;
 constexpr int kSymWinChunks = 16;       // symbolic heavy window: 16 chunks, 16 KiB bitmap
-constexpr int kSegCap = 1024;           // entries of one hashed segment (table of 2048 slots)
-constexpr int kSegMerge = 600;          // chunks are merged into one segment up to this many entries
-constexpr int kSegMaxSpan = 8;          // chunks spanned by one hashed segment
-constexpr int kSegBins = 4;             // hashed segments with <=128, <=700, <=1024 entries; dense chunks
-constexpr int kSegDense = 3;
+constexpr int kDenseMin = 1024;         // chunks with more entries are accumulated by column
+constexpr int kSegCap = 2048;           // entries of one segment
+constexpr int kSegMaxSpan = 16;         // chunks spanned by one segment
+constexpr int kSegHash = 128;           // segments of at most this many entries are hashed
+constexpr int kSegBins = 3;             // hashed segments, ranked segments, dense chunks
+constexpr int kSegDense = 2;
 constexpr int kBinBlockRows = 1024;     // rows per block of the binning kernels
 
 enum : int {
@@ -662,6 +665,182 @@ __device__ __forceinline__ void run_products(int e0, int e1, int gt, RunScratch<
             emit_products<WITH_VAL, N, ARRAY_SINK>(sink, pos, j, av, bv);
         }
         group_sync<WG>();
+    }
+}
+
+// ------------------------------------------- product enumeration by 16-pieces
+//
+// piece_products enumerates the same products in pieces of at most 16 of one
+// B range, a row of 16 lanes per piece, four pieces per wave step.  A piece is
+// located once, by one lane (a binary search over the prefix of the entries'
+// piece counts), and its start, end and A value reach the 16 lanes that load
+// it by a DPP row broadcast: no LDS access and no search per product, and a
+// short range wastes at most 15 lanes.
+constexpr int kPiece = 16;
+constexpr int kDppRowNewBcast = 0x150;   // lane t of each row of 16 to the whole row (gfx90a and later)
+
+template <typename V, int GE>
+struct PieceScratch {
+    int incl[GE];   // inclusive prefix of the entries' piece counts, 64 entries at a time
+    int bs[GE];     // B range of each entry
+    int be[GE];
+    V a[GE];        // A value
+    int wsum[GE / kWave];   // pieces of each 64 entries
+};
+
+template <int T>
+__device__ __forceinline__ int row_bcast(int v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, kDppRowNewBcast + T, 0xf, 0xf, false);
+}
+
+template <int T>
+__device__ __forceinline__ float row_bcast(float v)
+{
+    return __int_as_float(row_bcast<T>(__float_as_int(v)));
+}
+
+template <int T>
+__device__ __forceinline__ double row_bcast(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = row_bcast<T>((int)(b & 0xffffffff)), hi = row_bcast<T>((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
+
+// Lists one A entry per thread gt < GE (its B range [bs, bs + bl), empty beyond
+// the n entries of the step) in S: the prefix of the piece counts runs within
+// each 64 entries, so no barrier is needed inside.  Every thread of the group
+// calls it; readers of S come after a barrier.
+template <typename V, bool WITH_VAL, int GE>
+__device__ __forceinline__ void piece_list(int n, int gt, int bs, int bl, V a, PieceScratch<V, GE> &S)
+{
+    static_assert(GE % kWave == 0, "entry step");
+    if (gt >= GE) return;                                          // whole waves
+    int ip = 0;
+    if (gt - lane_id() < n) {
+        ip = wave_incl_scan((bl + kPiece - 1) / kPiece);
+        S.incl[gt] = ip;
+        S.bs[gt] = bs;
+        S.be[gt] = bs + bl;
+        if constexpr (WITH_VAL) S.a[gt] = a;
+    }
+    if (lane_id() == kWave - 1) S.wsum[gt / kWave] = ip;
+}
+
+// Number of pieces listed in S.
+template <typename V, int GE>
+__device__ __forceinline__ int piece_count(const PieceScratch<V, GE> &S)
+{
+    int P = 0;
+#pragma unroll
+    for (int w = 0; w < GE / kWave; ++w) P += S.wsum[w];
+    return P;
+}
+
+// The step's steps T, T + 1, ... of U wave steps each: products of the pieces
+// located in (st, en, al) are loaded and handed to the sink, U at a time.
+template <typename V, bool WITH_VAL, int U, int T, typename Sink>
+__device__ __forceinline__ void piece_steps(int left, int st, int en, V al, const int *__restrict__ Bcol,
+                                            const V *__restrict__ Bval, Sink &sink)
+{
+    if constexpr (T < kPiece) {
+        if (T * 4 >= left) return;                       // wave-uniform
+        int pos[U];
+        double av[U];
+        auto take = [&](auto u) {
+            constexpr int N = decltype(u)::value;
+            const int q = row_bcast<T + N>(st) + (lane_id() & (kPiece - 1));
+            pos[N] = q < row_bcast<T + N>(en) ? q : -1;
+            if constexpr (WITH_VAL) av[N] = (double)row_bcast<T + N>(al);
+            else av[N] = 0.0;
+        };
+        if constexpr (U >= 1) take(std::integral_constant<int, 0>());
+        if constexpr (U >= 2) take(std::integral_constant<int, 1>());
+        if constexpr (U >= 4) {
+            take(std::integral_constant<int, 2>());
+            take(std::integral_constant<int, 3>());
+        }
+        int j[U];
+        double bv[U];
+        load_products<V, WITH_VAL, U>(Bcol, Bval, pos, j, bv);
+        emit_products<WITH_VAL, U, true>(sink, pos, j, av, bv);
+        piece_steps<V, WITH_VAL, U, T + U>(left, st, en, al, Bcol, Bval, sink);
+    }
+}
+
+// Locates 64 of the listed pieces (of n entries), [p0, p1) at most: lane l
+// finds piece p0 + (l % 16) * 4 + l / 16, so that row g of the wave holds
+// pieces g, g + 4, ... and step t takes every row's lane t.  Absent pieces are
+// empty (st = en = 0).
+template <typename V, bool WITH_VAL, int GE>
+__device__ __forceinline__ void piece_locate(int p0, int p1, int n, const PieceScratch<V, GE> &S, int &st, int &en,
+                                             V &al)
+{
+    const int lane = lane_id();
+    int pc = p0 + (lane & 15) * 4 + (lane >> 4);
+    st = en = 0;
+    al = V(0);
+    if (pc < p1) {
+        int g = 0;                                                 // the 64 entries that hold piece pc
+        if (n > kWave) {
+#pragma unroll
+            for (int w = 0; w < GE / kWave - 1; ++w) {
+                const int t = S.wsum[w];
+                if (g == w * kWave && pc >= t) {
+                    pc -= t;
+                    g += kWave;
+                }
+            }
+        }
+        const int *incl = S.incl + g;
+        const int m = n - g < kWave ? n - g : kWave;
+        int src = 0;                                               // their entries whose prefix is <= pc
+        for (int s = n > kWave ? kWave / 2 : n > 1 ? 1 << (31 - __clz(n - 1)) : 0; s > 0; s >>= 1) {
+            const int t = src + s;
+            if (t < m && incl[t - 1] <= pc) src = t;
+        }
+        const int ex = src ? incl[src - 1] : 0;
+        src += g;
+        st = S.bs[src] + (pc - ex) * kPiece;
+        en = S.be[src];
+        if constexpr (WITH_VAL) al = S.a[src];
+    }
+}
+
+// Pieces of each wave when the waves of a group share P pieces in equal
+// contiguous parts (whole steps of four).
+template <int WG>
+__device__ __forceinline__ int piece_share(int P)
+{
+    return ((P + WG - 1) / WG + 3) & ~3;
+}
+
+// Hands every product of the P pieces listed in S (of n entries) to the sink
+// (sink(j[U], p[U], ok[U]) or, without values, sink(j[U], ok[U])).
+template <typename V, bool WITH_VAL, int GE, int G, int U, typename Sink>
+__device__ __forceinline__ void piece_run(int P, int n, int gt, const PieceScratch<V, GE> &S,
+                                          const int *__restrict__ Bcol, const V *__restrict__ Bval, Sink &sink)
+{
+    const int wg = __builtin_amdgcn_readfirstlane(gt / kWave), per = piece_share<G / kWave>(P);
+    const int p1 = (wg + 1) * per < P ? (wg + 1) * per : P;
+    for (int p0 = wg * per; p0 < p1; p0 += kWave) {
+        int st, en;
+        V al;
+        piece_locate<V, WITH_VAL, GE>(p0, p1, n, S, st, en, al);
+        piece_steps<V, WITH_VAL, U, 0>(p1 - p0, st, en, al, Bcol, Bval, sink);
+    }
+}
+
+// f(integral_constant<int, T>) for T = 0 .. N - 1 while 4 T < left
+// (wave-uniform): the steps of a wave with `left` located pieces.
+template <int N, typename F, int T = 0>
+__device__ __forceinline__ void piece_each(int left, F &f)
+{
+    if constexpr (T < N) {
+        if (T * 4 >= left) return;
+        f(std::integral_constant<int, T>());
+        piece_each<N, F, T + 1>(left, f);
     }
 }
 
@@ -1772,15 +1951,13 @@ __global__ __launch_bounds__(256) void k_chunk_prefix(const BinHdr *sh, int nchu
 }
 
 // Cuts every heavy row into segments (one thread per heavy row): a chunk
-// with more than kSegCap columns is a dense segment of its own; otherwise
-// consecutive chunks are merged while the count stays <= kSegMerge and the
-// span <= kSegMaxSpan chunks (a single chunk of up to kSegCap entries is a
-// segment of its own: smaller merged segments keep more of them in the
-// 1024-slot tables, which fit more blocks per CU).  Pass 0 counts segments per block and bin;
+// with more than kDenseMin columns is a dense segment of its own; otherwise
+// consecutive chunks are merged while the count stays <= kSegCap and the
+// span <= kSegMaxSpan chunks.  Pass 0 counts segments per block and bin;
 // pass 1 writes them at offset[bin] + block base + rank in block.
 __device__ __forceinline__ int seg_bin(int count, bool dense)
 {
-    return dense ? kSegDense : (count <= 128 ? 0 : (count <= 700 ? 1 : 2));
+    return dense ? kSegDense : (count <= kSegHash ? 0 : 1);
 }
 
 template <typename F>
@@ -1790,12 +1967,12 @@ __device__ __forceinline__ void plan_row_segments(const int *__restrict__ wc, in
     while (c < nchunks) {
         const int n0 = wc[c];
         if (n0 == 0) { ++c; continue; }
-        if (n0 > kSegCap) { emit(c, c + 1, n0, true); ++c; continue; }
+        if (n0 > kDenseMin) { emit(c, c + 1, n0, true); ++c; continue; }
         const int start = c;
         int sum = 0, last = c;
         while (c < nchunks && c - start < kSegMaxSpan) {
             const int n = wc[c];
-            if (n > kSegCap || (sum + n > kSegMerge && sum > 0)) break;
+            if (n > kDenseMin || sum + n > kSegCap) break;
             sum += n;
             if (n) last = c;
             ++c;
@@ -1835,7 +2012,7 @@ __global__ __launch_bounds__(256) void k_seg_plan(int pass, const BinHdr *bh, co
     const int *wc = wcnt + (long long)h * nchunks;
     // count this block's segments per (bin, chunk)
     if (h < nheavy) {
-        long long lnnz[kSegBins] = {0, 0, 0, 0};
+        long long lnnz[kSegBins] = {};
         plan_row_segments(wc, nchunks, [&](int a, int, int n, bool dense) {
             const int b = seg_bin(n, dense);
             if (pass == 0) {
@@ -1978,6 +2155,224 @@ __global__ __launch_bounds__(THREADS) void k_num_seg(
     for (int t = gt; t < n; t += THREADS) {
         store_c(&Ccol[out0 + t], keys[t]);
         store_c(&Cval[out0 + t], (V)vals[t]);
+    }
+}
+
+// Ranked segments of heavy rows: at most kSegCap entries in at most
+// kSegMaxSpan chunks.  A first pass over a segment's products marks their
+// columns in an LDS bitmap; with the bitmap's prefix counts every column's
+// rank is two LDS reads, so a second pass adds each product straight into its
+// entry's sum and notes its column: no table, no probing, and the entries are
+// in column order when the pass ends.  Products are loaded once, into
+// registers (HOLD steps per wave; more than that, or more A entries than one
+// list holds, takes them from memory twice).
+//
+// A segment has some 1900 products, four per thread, so a block that starts
+// from nothing spends its time in a chain of six memory latencies.  The grid
+// is persistent (the LDS, 48 KB FP32 and 49 KB FP64, lets three blocks of
+// eight waves share a CU) and the chain is spread over three segments: while
+// one is marked and added, the next one's A entries and split points are on
+// their way, and its products are loaded before this one is written out.
+// RMAT scale 19 A * A FP32 (1.5M segments): 10.9 ms, 11.6 without the
+// persistent grid, 13.9 loading the products twice, 12.9 with four waves;
+// hashed segments of up to 1024 entries in 8 chunks (3.4M of them) took 21.3.
+constexpr int kRankThreads = 512;
+constexpr int kRankEntries = 256;       // A entries listed per step
+constexpr int kRankWords = kSegMaxSpan * kChunkWords;
+
+template <typename V>
+__global__ __launch_bounds__(kRankThreads, 6) void k_num_rank(
+    const int *__restrict__ Acol, const V *__restrict__ Aval, const int *__restrict__ Bcol,
+    const V *__restrict__ Bval, const int *__restrict__ Bsplit, long long per, const Seg *__restrict__ segs, int nseg,
+    int *__restrict__ Ccol, V *__restrict__ Cval, int *err)
+{
+    constexpr int G = kRankThreads, NW = G / kWave, WPT = kRankWords / G, GE = kRankEntries;
+    constexpr int HOLD = 4096 / G;      // steps of products held in registers
+    static_assert(WPT == 8, "one 16-byte store of prefix counts per thread");
+    __shared__ __align__(16) unsigned bm[kRankWords];
+    __shared__ __align__(16) unsigned short pref[kRankWords];   // entries below each word
+    __shared__ double vals[kSegCap];
+    __shared__ unsigned short cols[kSegCap];                    // low 16 bits of each entry's column
+    __shared__ PieceScratch<V, GE> S;
+    __shared__ int s_scan[NW];
+    const int gt = threadIdx.x, lane = lane_id(), wg = __builtin_amdgcn_readfirstlane(gt / kWave);
+    const int w0 = gt * WPT;
+    const int last = nseg - 1, step = gridDim.x;
+    auto at = [&](int i) { return segs[i < last ? i : last]; };
+    // the products of the segment at hand, its located pieces and its list
+    int hc[HOLD], st = 0, en = 0, left = 0;
+    V hv[HOLD], al = V(0);
+    bool hok[HOLD], held = false;
+    auto entries = [](const Seg &g) { return g.e1 - g.e0 < GE ? g.e1 - g.e0 : GE; };
+    auto locate_and_load = [&](const Seg &g) {
+        const int P = piece_count(S);
+        held = g.e1 - g.e0 <= GE && P <= NW * HOLD * 4;
+        if (!held) return;
+        const int share = piece_share<NW>(P), p0 = wg * share;
+        left = (p0 + share < P ? p0 + share : P) - p0;
+        piece_locate<V, true, GE>(p0, p0 + left, g.e1 - g.e0, S, st, en, al);
+        auto load = [&](auto t) {
+            constexpr int T = decltype(t)::value;
+            const int q = row_bcast<T>(st) + (lane & (kPiece - 1));
+            hok[T] = q < row_bcast<T>(en);
+            const int pos = hok[T] ? q : 0;
+            hc[T] = Bcol[pos];
+            hv[T] = Bval[pos];
+        };
+        piece_each<HOLD>(left, load);
+    };
+    auto clear = [&]() {
+        *(uint4 *)&bm[w0] = make_uint4(0, 0, 0, 0);
+        *(uint4 *)&bm[w0 + 4] = make_uint4(0, 0, 0, 0);
+    };
+    Seg sg = at(blockIdx.x), nx = at(blockIdx.x + step);
+    {
+        int bs = 0, bl = 0;
+        V a = V(0);
+        if (gt < entries(sg)) {
+            const long long k = Acol[sg.e0 + gt] * per;
+            a = Aval[sg.e0 + gt];
+            bs = Bsplit[k + sg.c0];
+            bl = Bsplit[k + sg.c1] - bs;
+        }
+        piece_list<V, true, GE>(entries(sg), gt, bs, bl, a, S);
+        clear();
+        __syncthreads();
+        locate_and_load(sg);
+    }
+    for (int i = blockIdx.x; i < nseg; i += step) {
+        const Seg nn = at(i + 2 * step);
+        const int lo = sg.c0 * kChunkCols, W = (sg.c1 - sg.c0) * kChunkWords;
+        // the next segment's A entries
+        const int ne = entries(nx);
+        int nbs = 0, nbl = 0;
+        long long nk = 0;
+        V na = V(0);
+        if (gt < ne) {
+            nk = Acol[nx.e0 + gt] * per;
+            na = Aval[nx.e0 + gt];
+        }
+        for (int t = gt; t < sg.count; t += G) vals[t] = 0.0;
+        // the general form of a pass: the row's entries, a list at a time
+        auto pass = [&](auto with_val, auto &sink) {
+            constexpr bool WV = decltype(with_val)::value;
+            for (int base = sg.e0; base < sg.e1; base += GE) {
+                const int n = sg.e1 - base < GE ? sg.e1 - base : GE;
+                int bs = 0, bl = 0;
+                V a = V(0);
+                if (gt < n) {
+                    const long long k = Acol[base + gt] * per;
+                    a = Aval[base + gt];
+                    bs = Bsplit[k + sg.c0];
+                    bl = Bsplit[k + sg.c1] - bs;
+                }
+                __syncthreads();                         // S is free
+                piece_list<V, true, GE>(n, gt, bs, bl, a, S);
+                __syncthreads();
+                piece_run<V, WV, GE, G, 4>(piece_count(S), n, gt, S, Bcol, Bval, sink);
+            }
+        };
+        if (held) {
+            auto mark = [&](auto t) {
+                constexpr int T = decltype(t)::value;
+                hc[T] -= lo;
+                if (hok[T]) atomicOr(&bm[hc[T] >> 5], 1u << (hc[T] & 31));
+            };
+            piece_each<HOLD>(left, mark);
+        } else {
+            auto mark = [&](const auto &j, const auto &ok) {
+                constexpr int N = sizeof(j) / sizeof(j[0]);
+                unsigned w[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) w[u] = ok[u] ? bm[(j[u] - lo) >> 5] : ~0u;
+#pragma unroll
+                for (int u = 0; u < N; ++u) {
+                    const unsigned bit = 1u << ((j[u] - lo) & 31);
+                    if (!(w[u] & bit)) atomicOr(&bm[(j[u] - lo) >> 5], bit);
+                }
+            };
+            pass(std::false_type(), mark);
+        }
+        // the next segment's split points
+        if (gt < ne) {
+            nbs = Bsplit[nk + nx.c0];
+            nbl = Bsplit[nk + nx.c1];
+        }
+        __syncthreads();
+        // prefix counts: eight words per thread
+        int pc = 0;
+        unsigned pw[WPT / 2];
+        if (w0 < W) {
+#pragma unroll
+            for (int q = 0; q < WPT; q += 4) {
+                const uint4 v = *(const uint4 *)&bm[w0 + q];
+                pw[q / 2] = (unsigned)pc | (unsigned)(pc + __popc(v.x)) << 16;
+                pc += __popc(v.x) + __popc(v.y);
+                pw[q / 2 + 1] = (unsigned)pc | (unsigned)(pc + __popc(v.z)) << 16;
+                pc += __popc(v.z) + __popc(v.w);
+            }
+        }
+        const int inc = wave_incl_scan(pc);
+        if (lane == kWave - 1) s_scan[wg] = inc;
+        __syncthreads();
+        int run = 0, total = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const int t = s_scan[w];
+            if (w < wg) run += t;
+            total += t;
+        }
+        if (w0 < W) {
+            const unsigned add = (unsigned)(run + inc - pc) * 0x10001u;
+            *(uint4 *)&pref[w0] = make_uint4(pw[0] + add, pw[1] + add, pw[2] + add, pw[3] + add);
+        }
+        __syncthreads();
+        if (gt == 0 && total != sg.count) atomicOr(err, kErrCount);
+        const int cnt = total < sg.count ? total : sg.count;
+        auto rank = [&](int c) { return pref[c >> 5] + __popc(bm[c >> 5] & ((1u << (c & 31)) - 1u)); };
+        if (held) {
+            auto put = [&](auto t) {
+                constexpr int T = decltype(t)::value;
+                const double p = (double)row_bcast<T>(al) * (double)hv[T];
+                if (hok[T]) {
+                    const int r = rank(hc[T]);
+                    if (r < cnt) {
+                        atomicAdd(&vals[r], p);
+                        cols[r] = (unsigned short)hc[T];
+                    }
+                }
+            };
+            piece_each<HOLD>(left, put);
+        } else {
+            auto put = [&](const auto &j, const auto &p, const auto &ok) {
+                constexpr int N = sizeof(j) / sizeof(j[0]);
+                int r[N];
+#pragma unroll
+                for (int u = 0; u < N; ++u) r[u] = ok[u] ? rank(j[u] - lo) : kSegCap;
+#pragma unroll
+                for (int u = 0; u < N; ++u)
+                    if (r[u] < cnt) {
+                        atomicAdd(&vals[r[u]], p[u]);
+                        cols[r[u]] = (unsigned short)(j[u] - lo);
+                    }
+            };
+            pass(std::true_type(), put);
+            __syncthreads();                             // S is free
+        }
+        // entries from `half` on lie 65536 or more columns above lo
+        const int half = W > 2048 ? pref[2048] : cnt;
+        const long long out = sg.out;
+        piece_list<V, true, GE>(ne, gt, nbs, nbl - nbs, na, S);
+        __syncthreads();
+        clear();
+        sg = nx;
+        nx = nn;
+        if (i + step < nseg) locate_and_load(sg);
+        for (int t = gt; t < cnt; t += G) {
+            store_c(&Ccol[out + t], lo + cols[t] + (t >= half ? 65536 : 0));
+            store_c(&Cval[out + t], (V)vals[t]);
+        }
+        __syncthreads();
     }
 }
 

@@ -422,3 +422,44 @@ def test_global_touched_lists_across_windows(sm, ctx, oracle_mod, dtype):
     full_check(sm, ctx, A, B, dtype, oracle_mod, False, "global, 3 windows")
     st = ctx.stats()
     assert st["rows_heavy"] > 100 and st["global_slots"] > 0
+
+
+def _segment_edges(dtype, repeat=200):
+    """Heavy rows at the edges of the ranked segments (at most 2048 entries in
+    at most 16 chunks of 8192 columns; 128 entries and fewer are hashed; A's
+    entries listed 256 at a time; products of up to 256 pieces of 16 held in
+    registers), repeated so that every block takes several segments."""
+    n = 300_000
+    span = 16 * 8192
+    rows_b, rows_a = [], []
+
+    def row(*cols):
+        rows_a.append(list(range(len(rows_b), len(rows_b) + len(cols))))
+        rows_b.extend(np.unique(np.asarray(c, np.int64)) for c in cols)
+
+    for count in (128, 129, 1025, 2047, 2048, 2049):    # bins, capacity; all in 16 chunks
+        c = np.linspace(0, span - 1, count).astype(np.int64)
+        row(*([c] * (1 + 1100 // count)), c[::2])
+    row(*[np.arange(37 + i, n, 601) for i in range(3)])              # wider than one segment
+    row([65535, 65536, span - 1, span], *[np.arange(i, span, 97) for i in range(2)])
+    row(*[np.arange(5) * 20_011 + 17 * i for i in range(300)])       # more A entries than one list
+    row(*[np.arange(33) * 3001 + (i % 7) for i in range(200)])       # more pieces than are held
+    rp = np.zeros(len(rows_b) + 1, np.int32)
+    rp[1:] = np.cumsum([len(r) for r in rows_b])
+    nnz = int(rp[-1])
+    B = syn.CSR(len(rows_b), n, rp, np.concatenate(rows_b).astype(np.int32),
+                (2.0 * syn.uniform01(71, 0, nnz) - 1.0).astype(dtype))
+    rows_a = rows_a * repeat
+    ap = np.zeros(len(rows_a) + 1, np.int32)
+    ap[1:] = np.cumsum([len(r) for r in rows_a])
+    A = syn.CSR(len(rows_a), len(rows_b), ap, np.concatenate([np.array(r, np.int32) for r in rows_a]),
+                (2.0 * syn.uniform01(72, 0, int(ap[-1])) - 1.0).astype(dtype))
+    return A, B
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_ranked_segment_edges(sm, ctx, oracle_mod, dtype):
+    A, B = _segment_edges(dtype)
+    full_check(sm, ctx, A, B, dtype, oracle_mod, False, "segment edges")
+    st = ctx.stats()
+    assert st["rows_heavy"] == A.rows and st["heavy_segments"] > A.rows and st["heavy_dense_chunks"] == 0, st
