@@ -738,35 +738,68 @@ __device__ __forceinline__ int piece_count(const PieceScratch<V, GE> &S)
     return P;
 }
 
-// The step's steps T, T + 1, ... of U wave steps each: products of the pieces
-// located in (st, en, al) are loaded and handed to the sink, U at a time.
-template <typename V, bool WITH_VAL, int U, int T, typename Sink>
-__device__ __forceinline__ void piece_steps(int left, int st, int en, V al, const int *__restrict__ Bcol,
-                                            const V *__restrict__ Bval, Sink &sink)
-{
-    if constexpr (T < kPiece) {
-        if (T * 4 >= left) return;                       // wave-uniform
-        int pos[U];
-        double av[U];
-        auto take = [&](auto u) {
-            constexpr int N = decltype(u)::value;
+// U wave steps of the located pieces (st, en, al) from step T on, loaded.
+template <typename V, bool WITH_VAL, int U>
+struct PieceGroup {
+    int pos[U], j[U];
+    double av[U];
+    V raw[U];
+
+    template <int T>
+    __device__ __forceinline__ void load(int st, int en, V al, const int *__restrict__ Bcol,
+                                         const V *__restrict__ Bval)
+    {
+        take<T, 0>(st, en, al);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int q = pos[u] >= 0 ? pos[u] : 0;
+            j[u] = Bcol[q];
+            if constexpr (WITH_VAL) raw[u] = Bval[q];
+        }
+    }
+
+    template <int T, int N>
+    __device__ __forceinline__ void take(int st, int en, V al)
+    {
+        if constexpr (N < U) {
             const int q = row_bcast<T + N>(st) + (lane_id() & (kPiece - 1));
             pos[N] = q < row_bcast<T + N>(en) ? q : -1;
             if constexpr (WITH_VAL) av[N] = (double)row_bcast<T + N>(al);
             else av[N] = 0.0;
-        };
-        if constexpr (U >= 1) take(std::integral_constant<int, 0>());
-        if constexpr (U >= 2) take(std::integral_constant<int, 1>());
-        if constexpr (U >= 4) {
-            take(std::integral_constant<int, 2>());
-            take(std::integral_constant<int, 3>());
+            take<T, N + 1>(st, en, al);
         }
-        int j[U];
-        double bv[U];
-        load_products<V, WITH_VAL, U>(Bcol, Bval, pos, j, bv);
-        emit_products<WITH_VAL, U, true>(sink, pos, j, av, bv);
-        piece_steps<V, WITH_VAL, U, T + U>(left, st, en, al, Bcol, Bval, sink);
     }
+
+    template <typename Sink>
+    __device__ __forceinline__ void emit(Sink &sink)
+    {
+        double bv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if constexpr (WITH_VAL) bv[u] = (double)raw[u];
+            else bv[u] = 0.0;
+        }
+        emit_products<WITH_VAL, U, true>(sink, pos, j, av, bv);
+    }
+};
+
+// Steps T, T + 1, ... of the located pieces to the sink, U at a time; the
+// loads of the next U are in flight while this U are handed over (`cur` holds
+// step T's).
+template <typename V, bool WITH_VAL, int U, int T, typename Sink>
+__device__ __forceinline__ void piece_steps(int left, int st, int en, V al, const int *__restrict__ Bcol,
+                                            const V *__restrict__ Bval, PieceGroup<V, WITH_VAL, U> &cur, Sink &sink)
+{
+    if constexpr (T + U < kPiece) {
+        if ((T + U) * 4 < left) {                        // wave-uniform
+            PieceGroup<V, WITH_VAL, U> nxt;
+            nxt.template load<T + U>(st, en, al, Bcol, Bval);
+            cur.emit(sink);
+            piece_steps<V, WITH_VAL, U, T + U>(left, st, en, al, Bcol, Bval, nxt, sink);
+            return;
+        }
+    }
+    cur.emit(sink);
 }
 
 // Locates 64 of the listed pieces (of n entries), [p0, p1) at most: lane l
@@ -828,7 +861,9 @@ __device__ __forceinline__ void piece_run(int P, int n, int gt, const PieceScrat
         int st, en;
         V al;
         piece_locate<V, WITH_VAL, GE>(p0, p1, n, S, st, en, al);
-        piece_steps<V, WITH_VAL, U, 0>(p1 - p0, st, en, al, Bcol, Bval, sink);
+        PieceGroup<V, WITH_VAL, U> first;
+        first.template load<0>(st, en, al, Bcol, Bval);
+        piece_steps<V, WITH_VAL, U, 0>(p1 - p0, st, en, al, Bcol, Bval, first, sink);
     }
 }
 
@@ -2269,7 +2304,7 @@ __global__ __launch_bounds__(kRankThreads, 6) void k_num_rank(
                 __syncthreads();                         // S is free
                 piece_list<V, true, GE>(n, gt, bs, bl, a, S);
                 __syncthreads();
-                piece_run<V, WV, GE, G, 4>(piece_count(S), n, gt, S, Bcol, Bval, sink);
+                piece_run<V, WV, GE, G, 1>(piece_count(S), n, gt, S, Bcol, Bval, sink);
             }
         };
         if (held) {
@@ -2452,12 +2487,19 @@ __device__ __forceinline__ void wave_store_ranked(const double (&vr)[ROUNDS], co
 // Occupancy needs no bitmap: the array starts at -0.0 and every product is
 // added as p + 0.0, which is never -0.0, so a column was reached exactly when
 // its sum is no longer the bit pattern of -0.0 (a sum of terms that are not
-// -0.0 is never -0.0 under round-to-nearest, even when they cancel).  The
-// kernel is persistent: a grid that fills the GPU once takes the dense chunks
-// from a global queue (one atomic per `claim` chunks), so that long and
-// short chunks balance across CUs, and each wave puts -0.0 back in its slots once its
-// entries are out, so the array is ready for the next chunk without a
-// separate clearing pass.
+// -0.0 is never -0.0 under round-to-nearest, even when they cancel).
+//
+// The kernel is persistent: a grid that fills the GPU once (two blocks of
+// eight waves per CU, by LDS) takes the dense chunks from a global queue (one
+// atomic per `claim` chunks), so that long and short chunks balance across
+// CUs, and each wave puts -0.0 back in its slots once its entries are out, so
+// the array is ready for the next chunk without a separate clearing pass.
+// Bound by instruction issue (about half the cycles) and LDS adds (a third):
+// RMAT scale 19 A * A FP32 (844K chunks, 4.9e9 products) takes 14.8 ms; with
+// a search per product instead of per piece of 16 it was 17.9, with four
+// instead of up to eight products per thread in flight 16.9.  Chunks dealt
+// ahead, their A entries and split points fetched while the one before is
+// ranked, were no faster (15.1).
 constexpr int kDenseThreads = 512;
 // dense chunks a block claims with one atomic on the queue when every block
 // has many to do (one atomic per chunk from every resident block serialises
@@ -2467,67 +2509,76 @@ constexpr int kDenseClaimMinPerBlock = 256;
 
 template <typename V>
 __global__ __launch_bounds__(kDenseThreads) void k_num_dense(
-    const int *__restrict__ Arp, const int *__restrict__ Acol, const V *__restrict__ Aval,
-    const int *__restrict__ Bcol, const V *__restrict__ Bval, const int *__restrict__ Bsplit, long long per,
-    const int *__restrict__ heavy_rows, const Seg *__restrict__ segs, int nchunks,
-    const int *__restrict__ woff, const long long *__restrict__ Crp, int *__restrict__ Ccol,
-    V *__restrict__ Cval, int *err, int nseg, int *queue, int claim)
+    const int *__restrict__ Acol, const V *__restrict__ Aval, const int *__restrict__ Bcol,
+    const V *__restrict__ Bval, const int *__restrict__ Bsplit, long long per, const Seg *__restrict__ segs, int nseg,
+    int claim, int *__restrict__ Ccol, V *__restrict__ Cval, int *err, int *queue)
 {
-    constexpr int NW = kDenseThreads / kWave;
+    constexpr int G = kDenseThreads, NW = G / kWave;
     constexpr int CPW = kChunkCols / NW;              // columns ranked by each wave
     constexpr int ROUNDS = CPW / kWave;
     extern __shared__ __align__(16) unsigned char s_raw[];
     double *acc = (double *)s_raw;                      // [kChunkCols]
-    __shared__ EnumScratch<V, kDenseThreads> S;
+    __shared__ PieceScratch<V, G> S;
     __shared__ int s_wt[NW];
     __shared__ int s_next;
     const int gt = threadIdx.x, lane = lane_id(), wg = gt / kWave;
-    for (int t = gt; t < kChunkCols; t += kDenseThreads) acc[t] = -0.0;
-    for (;;) {
-    if (gt == 0) s_next = atomicAdd(queue, claim);
-    __syncthreads();                                    // also: the previous chunk is fully written
-    const int first = s_next;
-    if (first >= nseg) break;
-    const int last = first + claim < nseg ? first + claim : nseg;
-    for (int t = first; t < last; ++t) {
-    const Seg sg = segs[t];
-    const int lo = sg.c0 * kChunkCols;
-    const int *__restrict__ split0 = Bsplit + sg.c0;
-    const int *__restrict__ split1 = split0 + 1;
-    auto get = [&](int e, int &bs, int &bl, V &a) {
-        const int k = Acol[e];
-        bs = split0[k * per];
-        bl = split1[k * per] - bs;
-        a = Aval[e];
-    };
-    auto sink = [&](int j, double p) { atomicAdd(&acc[j - lo], p + 0.0); };
-    group_products<V, true, kDenseThreads, 2, decltype(get), decltype(sink), false, true>(sg.e0, sg.e1, gt, S, Bcol,
-                                                                                          Bval, get, sink);
-    __syncthreads();
-    double vr[ROUNDS];
-    unsigned long long msk[ROUNDS];
-    int wcount = 0;
+    for (int t = gt; t < kChunkCols; t += G) acc[t] = -0.0;
+    for (int t = 0, last = 0;; ++t) {
+        if (t >= last) {
+            if (gt == 0) s_next = atomicAdd(queue, claim);
+            __syncthreads();
+            t = s_next;
+            if (t >= nseg) break;
+            last = t + claim < nseg ? t + claim : nseg;
+        }
+        const Seg sg = segs[t];
+        const int lo = sg.c0 * kChunkCols;
+        const int *__restrict__ split0 = Bsplit + sg.c0;
+        auto sink = [&](const auto &j, const auto &p, const auto &ok) {
+            constexpr int N = sizeof(j) / sizeof(j[0]);
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) {
-        vr[r] = acc[wg * CPW + r * kWave + lane];
-        msk[r] = wave_ballot(reached(vr[r]));
-        wcount += __popcll(msk[r]);
-    }
-    if (lane == 0) s_wt[wg] = wcount;
-    __syncthreads();
-    int run = 0, tot = 0;
-    for (int w = 0; w < NW; ++w) {
-        const int c = s_wt[w];
-        if (w < wg) run += c;
-        tot += c;
-    }
-    if (gt == 0 && tot != sg.count) atomicOr(err, kErrCount);
-    const int n = wcount < sg.count - run ? wcount : (sg.count - run > 0 ? sg.count - run : 0);
-    wave_store_ranked<V, ROUNDS>(vr, msk, acc + wg * CPW, lo + wg * CPW, sg.out + run, n, Ccol, Cval);
+            for (int u = 0; u < N; ++u)
+                if (ok[u]) atomicAdd(&acc[j[u] - lo], p[u] + 0.0);
+        };
+        for (int base = sg.e0; base < sg.e1; base += G) {
+            const int n = sg.e1 - base < G ? sg.e1 - base : G;
+            int bs = 0, bl = 0;
+            V a = V(0);
+            if (gt < n) {
+                const long long k = Acol[base + gt] * per;
+                a = Aval[base + gt];
+                bs = split0[k];
+                bl = split0[k + 1] - bs;
+            }
+            piece_list<V, true, G>(n, gt, bs, bl, a, S);
+            __syncthreads();                            // also: the previous chunk is fully written
+            piece_run<V, true, G, G, 4>(piece_count(S), n, gt, S, Bcol, Bval, sink);
+            __syncthreads();
+        }
+        double vr[ROUNDS];
+        unsigned long long msk[ROUNDS];
+        int wcount = 0;
 #pragma unroll
-    for (int r = 0; r < ROUNDS; ++r) acc[wg * CPW + r * kWave + lane] = -0.0;   // cleared for the next chunk
-    __syncthreads();                                    // s_wt and s_next are reused
-    }
+        for (int r = 0; r < ROUNDS; ++r) {
+            vr[r] = acc[wg * CPW + r * kWave + lane];
+            msk[r] = wave_ballot(reached(vr[r]));
+            wcount += __popcll(msk[r]);
+        }
+        if (lane == 0) s_wt[wg] = wcount;
+        __syncthreads();
+        int run = 0, tot = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const int c = s_wt[w];
+            if (w < wg) run += c;
+            tot += c;
+        }
+        if (gt == 0 && tot != sg.count) atomicOr(err, kErrCount);
+        const int n = wcount < sg.count - run ? wcount : (sg.count - run > 0 ? sg.count - run : 0);
+        wave_store_ranked<V, ROUNDS>(vr, msk, acc + wg * CPW, lo + wg * CPW, sg.out + run, n, Ccol, Cval);
+#pragma unroll
+        for (int r = 0; r < ROUNDS; ++r) acc[wg * CPW + r * kWave + lane] = -0.0;   // cleared for the next chunk
+        __syncthreads();                                // s_wt and s_next are reused
     }
 }
 
