@@ -487,187 +487,6 @@ __device__ __forceinline__ void group_products(int e0, int e1, int gt, EnumScrat
     }
 }
 
-// --------------------------------------------- product enumeration by runs
-//
-// run_products enumerates the same products as group_products with fewer
-// instructions per product: locating a product's A entry (a search in LDS)
-// is shared by 64 products of a wave (a full piece of a long range) or by
-// the kRun consecutive products of one lane (a run of a short range), never
-// done once per product.  Every B range is split into full pieces of 64
-// products and a tail of fewer than 64; entries with full pieces form the
-// long list, entries with a tail the short list (an entry can be in both),
-// each compacted in LDS with the inclusive prefix of its piece (or run)
-// counts.  Long phase: each wave locates 64 of its pieces at once, one per
-// lane (a binary search over the long list, O(log n) reads per lane), keeps
-// their starts in registers and then takes U pieces per step: the start of
-// piece u is read across lanes (v_readlane) and lane l loads product
-// start + l, coalesced.  Short phase: thread gt takes runs q = gt, gt + G,
-// ... (RU per step), finds each run's entry by binary search over the short
-// list and loads its kRun consecutive products.  Pieces are dealt to the
-// waves U at a time in turn, so short rows still spread over the group.
-constexpr int kRun = 4;
-
-template <typename V, int GE, int G = GE>
-struct RunScratch {
-    int lincl[GE];  // long list: inclusive prefix of the full-piece counts
-    int lbs[GE];    //   B range start
-    V la[GE];       //   A value
-    int sincl[GE];  // short list: inclusive prefix of the tail-run counts
-    int sbs[GE];    //   start of the tail
-    int sbe[GE];    //   end of the B range
-    V sa[GE];       //   A value
-    int wsum[3 * (G / kWave)];
-};
-
-// Number of entries of the strictly increasing incl[0, n) that are <= x,
-// i.e. the first index whose prefix exceeds x (n is group-uniform).
-__device__ __forceinline__ int prefix_rank(const int *incl, int n, int x)
-{
-    int lo = 0;
-    for (int s = n > 0 ? 1 << (31 - __clz(n)) : 0; s > 0; s >>= 1)
-        if (lo + s <= n && incl[lo + s - 1] <= x) lo += s;
-    return lo;
-}
-
-__device__ __forceinline__ double readlane_d(double v, int lane)
-{
-    const long long b = __double_as_longlong(v);
-    const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffff), lane);
-    const int hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-
-// GE (a multiple of 64, at most G) is the number of A entries taken per step;
-// a group with more threads than entries per step keeps the LDS lists small
-// while all G threads share the products.
-template <typename V, bool WITH_VAL, int GE, int G, int U, int RU, int RUN, typename Get, typename Sink,
-          bool ARRAY_SINK = false>
-__device__ __forceinline__ void run_products(int e0, int e1, int gt, RunScratch<V, GE, G> &S,
-                                             const int *__restrict__ Bcol, const V *__restrict__ Bval, Get get,
-                                             Sink sink)
-{
-    constexpr int WG = G / kWave;
-    static_assert(kWave % U == 0, "U must divide the wave");
-    static_assert(GE % kWave == 0 && GE <= G, "entry step");
-    const int lane = lane_id(), wg = gt / kWave;
-    for (int base = e0; base < e1; base += GE) {
-        const int e = base + gt;
-        int bs = 0, bl = 0;
-        V a = V(0);
-        if (gt < GE && e < e1) get(e, bs, bl, a);
-        const int np = bl >> 6;                          // full pieces
-        const int tail = bl & (kWave - 1);
-        const int nr = (tail + RUN - 1) / RUN;           // runs of the tail
-        const int isl = np > 0, iss = tail > 0;
-        int ip = wave_incl_scan(np);
-        int ic = wave_incl_scan(isl | (iss << 16));
-        int ir = wave_incl_scan(nr);
-        int P, RT, NC;
-        if constexpr (WG > 1) {
-            if (lane == kWave - 1) {
-                S.wsum[wg] = ip;
-                S.wsum[WG + wg] = ic;
-                S.wsum[2 * WG + wg] = ir;
-            }
-            group_sync<WG>();
-            int ap = 0, ac = 0, ar = 0;
-            P = 0, NC = 0, RT = 0;
-            for (int w = 0; w < WG; ++w) {
-                const int tp = S.wsum[w], tc = S.wsum[WG + w], tr = S.wsum[2 * WG + w];
-                if (w < wg) { ap += tp; ac += tc; ar += tr; }
-                P += tp;
-                NC += tc;
-                RT += tr;
-            }
-            ip += ap;
-            ic += ac;
-            ir += ar;
-        } else {
-            P = __builtin_amdgcn_readlane(ip, kWave - 1);
-            NC = __builtin_amdgcn_readlane(ic, kWave - 1);
-            RT = __builtin_amdgcn_readlane(ir, kWave - 1);
-        }
-        const int NL = NC & 0xffff, NS = NC >> 16;
-        if (isl) {
-            const int li = (ic & 0xffff) - 1;
-            S.lincl[li] = ip;
-            S.lbs[li] = bs;
-            if constexpr (WITH_VAL) S.la[li] = a;
-        }
-        if (iss) {
-            const int si = (ic >> 16) - 1;
-            S.sincl[si] = ir;
-            S.sbs[si] = bs + (np << 6);
-            S.sbe[si] = bs + bl;
-            if constexpr (WITH_VAL) S.sa[si] = a;
-        }
-        group_sync<WG>();
-        // long phase: wave wg owns pieces (k * WG + wg) * U + u, k = 0, 1, ...
-        for (int k0 = 0; (k0 * WG + wg) * U < P; k0 += kWave / U) {
-            const int pc = ((k0 + lane / U) * WG + wg) * U + lane % U;
-            int st = -1;
-            double al = 0.0;
-            if (pc < P) {
-                const int li = prefix_rank(S.lincl, NL, pc);
-                const int ex = li ? S.lincl[li - 1] : 0;
-                st = S.lbs[li] + ((pc - ex) << 6);
-                if constexpr (WITH_VAL) al = (double)S.la[li];
-            }
-            for (int g = 0; g < kWave / U && ((k0 + g) * WG + wg) * U < P; ++g) {
-                int pos[U], j[U];
-                double av[U], bv[U];
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int s = __builtin_amdgcn_readlane(st, g * U + u);
-                    pos[u] = s >= 0 ? s + lane : -1;
-                    if constexpr (WITH_VAL) av[u] = readlane_d(al, g * U + u);
-                    else av[u] = 0.0;
-                }
-                load_products<V, WITH_VAL, U>(Bcol, Bval, pos, j, bv);
-                emit_products<WITH_VAL, U, ARRAY_SINK>(sink, pos, j, av, bv);
-            }
-        }
-        // short phase: runs of kRun consecutive products of the tails
-        for (int q0 = 0; q0 < RT; q0 += G * RU) {
-            int src[RU];
-#pragma unroll
-            for (int r = 0; r < RU; ++r) src[r] = 0;
-            // the RU searches advance together (their LDS reads overlap)
-            for (int s = NS > 0 ? 1 << (31 - __clz(NS)) : 0; s > 0; s >>= 1) {
-                int t[RU];
-#pragma unroll
-                for (int r = 0; r < RU; ++r) t[r] = src[r] + s <= NS ? S.sincl[src[r] + s - 1] : 0x7fffffff;
-#pragma unroll
-                for (int r = 0; r < RU; ++r)
-                    if (t[r] <= q0 + r * G + gt) src[r] += s;
-            }
-            constexpr int N = RU * RUN;
-            int pos[N], j[N];
-            double av[N], bv[N];
-#pragma unroll
-            for (int r = 0; r < RU; ++r) {
-                const int q = q0 + r * G + gt;
-                int st = 0, en = 0;
-                double ar = 0.0;
-                if (q < RT) {
-                    const int ex = src[r] ? S.sincl[src[r] - 1] : 0;
-                    st = S.sbs[src[r]] + (q - ex) * RUN;
-                    en = S.sbe[src[r]];
-                    if constexpr (WITH_VAL) ar = (double)S.sa[src[r]];
-                }
-#pragma unroll
-                for (int i = 0; i < RUN; ++i) {
-                    pos[r * RUN + i] = st + i < en ? st + i : -1;
-                    av[r * RUN + i] = ar;
-                }
-            }
-            load_products<V, WITH_VAL, N>(Bcol, Bval, pos, j, bv);
-            emit_products<WITH_VAL, N, ARRAY_SINK>(sink, pos, j, av, bv);
-        }
-        group_sync<WG>();
-    }
-}
-
 // ------------------------------------------- product enumeration by 16-pieces
 //
 // piece_products enumerates the same products in pieces of at most 16 of one
@@ -864,6 +683,62 @@ __device__ __forceinline__ void piece_run(int P, int n, int gt, const PieceScrat
         PieceGroup<V, WITH_VAL, U> first;
         first.template load<0>(st, en, al, Bcol, Bval);
         piece_steps<V, WITH_VAL, U, 0>(p1 - p0, st, en, al, Bcol, Bval, first, sink);
+    }
+}
+
+// Hands every product of the A entries [e0, e1) of one row to the sink, GE
+// entries at a time: entry e takes row Acol[e] of B between its split points
+// split[k * per] and split[k * per + d].  The split points of the next GE
+// entries and the columns of those after them are on their way while one list
+// is run, so that a hub row's steps do not each wait for two dependent
+// gathers.  Every thread of the group of G calls it; S is free again when it
+// returns.  AHEAD = false leaves that out, where registers are short.
+template <typename V, bool WITH_VAL, int GE, int G, int U, bool AHEAD = true, typename Sink>
+__device__ __forceinline__ void piece_products(int e0, int e1, int gt, PieceScratch<V, GE> &S,
+                                               const int *__restrict__ Acol, const V *__restrict__ Aval,
+                                               const int *__restrict__ split, long long per, int d,
+                                               const int *__restrict__ Bcol, const V *__restrict__ Bval, Sink &sink)
+{
+    constexpr int WG = G / kWave;
+    long long k = -1;
+    V a = V(0), a1 = V(0);
+    int bs = 0, be = 0;
+    auto column = [&](int e, V &val) {
+        k = -1;
+        if (gt < GE && e < e1) {
+            k = Acol[e] * per;
+            if constexpr (WITH_VAL) val = Aval[e];
+        }
+    };
+    auto range = [&]() {
+        bs = be = 0;
+        if (k >= 0) {
+            bs = split[k];
+            be = split[k + d];
+        }
+    };
+    column(e0 + gt, a);
+    range();
+    if constexpr (AHEAD) column(e0 + GE + gt, a1);
+    for (int base = e0; base < e1; base += GE) {
+        const int n = e1 - base < GE ? e1 - base : GE;
+        piece_list<V, WITH_VAL, GE>(n, gt, bs, be - bs, a, S);
+        group_sync<WG>();
+        if constexpr (AHEAD) {
+            if (base + GE < e1) {
+                range();
+                a = a1;
+                column(base + 2 * GE + gt, a1);
+            }
+        }
+        piece_run<V, WITH_VAL, GE, G, U>(piece_count(S), n, gt, S, Bcol, Bval, sink);
+        if constexpr (!AHEAD) {
+            if (base + GE < e1) {
+                column(base + GE + gt, a);
+                range();
+            }
+        }
+        group_sync<WG>();
     }
 }
 
@@ -1906,8 +1781,14 @@ __global__ __launch_bounds__(256) void k_bsplit(int brows, int nchunks, const in
 // stores the number of columns of every chunk (wcnt) and adds them to the
 // row's count.  The grid covers hcap heavy rows (the workspace's capacity, a
 // host-side bound); the number present, sh->count[kBinHeavy], comes from the
-// device, and blocks beyond it return at once.
+// device, and blocks beyond it return at once.  Bound by instruction issue
+// (three quarters of the cycles at RMAT scale 19) and, where B is narrow, by
+// the hub rows, which one block works through alone.  With products located per
+// piece of 16 and the next lists' gathers in flight: scale 19 8.0 -> 6.7 ms, the
+// rectangular product (scale 21 times 4096 columns) 0.79 -> 0.44 ms; two
+// products in flight instead of four: 6.8 and 0.52.
 constexpr int kSymHeavyThreads = 256;
+constexpr int kSymU = 4;                // products in flight per thread and step
 
 __global__ __launch_bounds__(kSymHeavyThreads) void k_sym_heavy(
     const int *__restrict__ Arp, const int *__restrict__ Acol, const int *__restrict__ Bcol,
@@ -1918,7 +1799,7 @@ __global__ __launch_bounds__(kSymHeavyThreads) void k_sym_heavy(
     constexpr int WG = G / kWave;
     constexpr int WORDS = kSymWinChunks * kChunkWords;
     __shared__ unsigned bm[WORDS];
-    __shared__ RunScratch<float, G> S;
+    __shared__ PieceScratch<float, G> S;
     // window-major: blocks launched together share one column window of B
     const int w = blockIdx.x / hcap, h = blockIdx.x % hcap;
     if (h >= sh->count[kBinHeavy] || stopped(err)) return;
@@ -1927,15 +1808,7 @@ __global__ __launch_bounds__(kSymHeavyThreads) void k_sym_heavy(
     const int c0 = w * kSymWinChunks;
     const int c1 = c0 + kSymWinChunks < nchunks ? c0 + kSymWinChunks : nchunks;
     const int lo = c0 * kChunkCols;
-    const int *__restrict__ split0 = Bsplit + c0;
-    const int *__restrict__ split1 = Bsplit + c1;
-    for (int t = gt; t < WORDS; t += G) bm[t] = 0u;
-    __syncthreads();
-    auto get = [&](int e, int &bs, int &bl, float &) {
-        const int k = Acol[e];
-        bs = split0[k * per];
-        bl = split1[k * per] - bs;
-    };
+    for (int t = gt; t < WORDS; t += G) bm[t] = 0u;         // the products' first barrier follows
     // all words of the thread's products are read before any is tested, so
     // the reads overlap; most repeated columns then skip the atomic (an OR
     // after a stale read is merely redundant)
@@ -1950,9 +1823,8 @@ __global__ __launch_bounds__(kSymHeavyThreads) void k_sym_heavy(
             if (!(w[u] & bit)) atomicOr(&bm[(j[u] - lo) >> 5], bit);
         }
     };
-    run_products<float, false, G, G, 8, 2, kRun, decltype(get), decltype(sink), true>(
-        Arp[row], Arp[row + 1], gt, S, Bcol, (const float *)nullptr, get, sink);
-    __syncthreads();
+    piece_products<float, false, G, G, kSymU>(Arp[row], Arp[row + 1], gt, S, Acol, (const float *)nullptr, Bsplit + c0,
+                                              per, c1 - c0, Bcol, (const float *)nullptr, sink);
     // per-chunk counts: one wave per chunk
     int local = 0;
     for (int c = wg; c < c1 - c0; c += WG) {
@@ -2290,22 +2162,8 @@ __global__ __launch_bounds__(kRankThreads, 6) void k_num_rank(
         for (int t = gt; t < sg.count; t += G) vals[t] = 0.0;
         // the general form of a pass: the row's entries, a list at a time
         auto pass = [&](auto with_val, auto &sink) {
-            constexpr bool WV = decltype(with_val)::value;
-            for (int base = sg.e0; base < sg.e1; base += GE) {
-                const int n = sg.e1 - base < GE ? sg.e1 - base : GE;
-                int bs = 0, bl = 0;
-                V a = V(0);
-                if (gt < n) {
-                    const long long k = Acol[base + gt] * per;
-                    a = Aval[base + gt];
-                    bs = Bsplit[k + sg.c0];
-                    bl = Bsplit[k + sg.c1] - bs;
-                }
-                __syncthreads();                         // S is free
-                piece_list<V, true, GE>(n, gt, bs, bl, a, S);
-                __syncthreads();
-                piece_run<V, WV, GE, G, 1>(piece_count(S), n, gt, S, Bcol, Bval, sink);
-            }
+            piece_products<V, decltype(with_val)::value, GE, G, 1, false>(sg.e0, sg.e1, gt, S, Acol, Aval, Bsplit + sg.c0,
+                                                                          per, sg.c1 - sg.c0, Bcol, Bval, sink);
         };
         if (held) {
             auto mark = [&](auto t) {
@@ -2392,7 +2250,6 @@ __global__ __launch_bounds__(kRankThreads, 6) void k_num_rank(
                     }
             };
             pass(std::true_type(), put);
-            __syncthreads();                             // S is free
         }
         // entries from `half` on lie 65536 or more columns above lo
         const int half = W > 2048 ? pref[2048] : cnt;
@@ -2540,21 +2397,8 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_dense(
             for (int u = 0; u < N; ++u)
                 if (ok[u]) atomicAdd(&acc[j[u] - lo], p[u] + 0.0);
         };
-        for (int base = sg.e0; base < sg.e1; base += G) {
-            const int n = sg.e1 - base < G ? sg.e1 - base : G;
-            int bs = 0, bl = 0;
-            V a = V(0);
-            if (gt < n) {
-                const long long k = Acol[base + gt] * per;
-                a = Aval[base + gt];
-                bs = split0[k];
-                bl = split0[k + 1] - bs;
-            }
-            piece_list<V, true, G>(n, gt, bs, bl, a, S);
-            __syncthreads();                            // also: the previous chunk is fully written
-            piece_run<V, true, G, G, 4>(piece_count(S), n, gt, S, Bcol, Bval, sink);
-            __syncthreads();
-        }
+        // its first barrier also says that the previous chunk is fully written
+        piece_products<V, true, G, G, 4>(sg.e0, sg.e1, gt, S, Acol, Aval, split0, per, 1, Bcol, Bval, sink);
         double vr[ROUNDS];
         unsigned long long msk[ROUNDS];
         int wcount = 0;
