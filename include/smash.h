@@ -99,7 +99,8 @@ typedef enum {
     /* Heavy-row path: 0 = column segments merged in LDS, hashed or, for
      * chunks with more than 1024 of their 8192 columns, accumulated by column (default);
      * 1 = one hash table per row in global memory (the paper's third
-     * version, "Fragmenting Memory", moves the table to DRAM). */
+     * version, "Fragmenting Memory", moves the table to DRAM), behind a
+     * small LDS table for the columns that come first. */
     SMASH_OPT_HEAVY_MODE = 2,
     /* 1 = record HIP events around every kernel launch and accumulate the
      * elapsed time per kernel (smash_kernel_time).  Default 0. */

@@ -98,8 +98,8 @@ size_t carve_size(std::initializer_list<size_t> parts)
 
 // Bytes of the workspace per heavy row (LDS mode: chunk counts, chunk
 // offsets and up to one segment per chunk) and per global hash slot (global
-// mode: key, FP64 value, touched-slot list entry).
-constexpr size_t kGlobalSlotBytes = sizeof(int) + sizeof(double) + sizeof(int);
+// mode).
+constexpr size_t kGlobalSlotBytes = sizeof(GSlot);
 constexpr size_t kCarveSlack = 4 * 256;
 
 struct Plan {
@@ -126,8 +126,7 @@ struct Plan {
     int *bsplit = nullptr, *wcnt = nullptr, *woff = nullptr, *seg_bcount = nullptr;
     Seg *segs = nullptr;
     int *queue = nullptr;                 // work-queue counter of the persistent dense kernel
-    int *gkeys = nullptr, *gtouch = nullptr;
-    double *gvals = nullptr;
+    GSlot *pool = nullptr;                // (the symbolic pass uses it as an array of keys)
     // global mode: waves of heavy rows (first row and table offset of each
     // wave, then the end) and the pool each pass needs
     std::vector<std::pair<int, long long>> sym_waves, num_waves;
@@ -383,9 +382,7 @@ void carve_workspace(smash_ctx c, Plan &p, char *base, size_t ws_bytes)
     p.pool_cap = 0;
     if (global) {
         p.pool_cap = (long long)(rest / kGlobalSlotBytes);
-        p.gkeys = cv.take<int>(p.pool_cap);
-        p.gvals = cv.take<double>(p.pool_cap);
-        p.gtouch = cv.take<int>(p.pool_cap);
+        p.pool = cv.take<GSlot>(p.pool_cap);
     } else {
         // a heavy row needs more than lds_row_max output columns: with B no
         // wider than that there are none, and no heavy-row kernel is launched
@@ -568,7 +565,7 @@ smash_status numeric_impl(smash_ctx c, hipStream_t s, const Plan &p, const V *Av
     // global-memory hash tables in the workspace's pool, in the waves planned
     // by the symbolic phase (each row clears its own table, so the pool is
     // reused as it is)
-    const size_t lds = (size_t)kGlobalRankBits / 8;
+    const size_t lds = global_rank_lds(p.n);
     (void)hipFuncSetAttribute((const void *)k_num_global<V>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     const int *rows = p.num_perm + p.hdr.num.offset[kBinHeavy];
     for (size_t w = 0; w + 1 < p.num_waves.size(); ++w) {
@@ -576,9 +573,8 @@ smash_status numeric_impl(smash_ctx c, hipStream_t s, const Plan &p, const V *Av
         const long long base = p.num_waves[w].second;
         TRY(launch(c, K_NUM_GLOBAL, s, [&] {
             k_num_global<V><<<nh, kGlobalThreads, lds, s>>>(p.A.row_ptr, p.A.col_idx, Aval, p.B.row_ptr, p.B.col_idx,
-                                                            Bval, rows + h0, (int)p.n, p.goff_num + h0, base, p.gkeys,
-                                                            p.gvals, p.gtouch, (const long long *)crp, ccol, cval,
-                                                            c->d_numerr);
+                                                            Bval, rows + h0, (int)p.n, p.goff_num + h0, base, p.pool,
+                                                            (const long long *)crp, ccol, cval, c->d_numerr);
         }));
     }
     return SMASH_OK;
@@ -1026,11 +1022,11 @@ smash_status symbolic_impl(smash_ctx c, const smash_csr *A, const smash_csr *B, 
             for (size_t w = 0; w + 1 < p.sym_waves.size(); ++w) {
                 const int h0 = p.sym_waves[w].first, nh = p.sym_waves[w + 1].first - h0;
                 const long long base = p.sym_waves[w].second, slots = p.sym_waves[w + 1].second - base;
-                TRY(launch(c, K_FILL, s, [&] { k_fill_i32<<<2048, 256, 0, s>>>(slots, p.gkeys, kEmpty); }));
+                TRY(launch(c, K_FILL, s, [&] { k_fill_i32<<<2048, 256, 0, s>>>(slots, (int *)p.pool, kEmpty); }));
                 TRY(launch(c, K_SYM_GLOBAL, s, [&] {
                     k_sym_global<<<nh, kGlobalThreads, 0, s>>>(A->row_ptr, A->col_idx, B->row_ptr, B->col_idx,
                                                                heavy_rows + h0, p.cap, p.goff_sym + h0, base,
-                                                               p.gkeys, p.nnzc, perr(c));
+                                                               (int *)p.pool, p.nnzc, perr(c));
                 }));
             }
         }
@@ -1521,9 +1517,8 @@ struct smash_batch_plan_s {
     RowDesc *rd = nullptr;               // row records of the LDS bins
     int nblk = 0;
     BatchHdr *d_hdr = nullptr, *h_hdr = nullptr;
-    int *gkeys = nullptr, *gtouch = nullptr;
-    double *gvals = nullptr;
-    long long gcap = 0;                  // slots of gkeys / gvals / gtouch
+    GSlot *pool = nullptr;
+    long long gcap = 0;                  // its slots
     long long cap_total = 0;             // sum of the row bounds (pool capacity)
     int wide_words = 1;                  // LDS bitmap words of the widest problem up to kWideMaxCols
     bool any_global = false;             // a problem wider than kWideMaxCols (global tables)
@@ -1639,8 +1634,8 @@ void batch_numeric(const BPlan &p, hipStream_t s)
         p.d_desc, p.prob, p.d_hdr, p.num_perm, p.ccap, p.crp, p.ccol, (V *)p.cval, &p.d_hdr->error,
         &p.d_hdr->wide_queue);
     if (p.any_global)
-        k_bnum_global<V><<<bgrid(p, p.M), kGlobalThreads, kGlobalRankBits / 8, s>>>(
-        p.d_desc, p.prob, p.d_hdr, p.num_perm, p.goff, p.gcap, p.gkeys, p.gvals, p.gtouch, p.ccap, p.crp, p.ccol,
+        k_bnum_global<V><<<bgrid(p, p.M), kGlobalThreads, global_rank_lds(kGlobalRankBits), s>>>(
+        p.d_desc, p.prob, p.d_hdr, p.num_perm, p.goff, p.gcap, p.pool, p.ccap, p.crp, p.ccol,
         (V *)p.cval, &p.d_hdr->error);
 }
 
@@ -1662,7 +1657,7 @@ void batch_enqueue(const BPlan &p, hipStream_t s)
         p.d_desc, p.prob, &p.d_hdr->sym, p.sym_perm, p.nnzc);
     if (p.any_global)
         k_bsym_global<<<bgrid(p, p.M), kGlobalThreads, 0, s>>>(p.d_desc, p.prob, &p.d_hdr->sym, p.sym_perm, p.cap,
-                                                           p.goff, p.gcap, p.gkeys, p.nnzc, &p.d_hdr->error);
+                                                           p.goff, p.gcap, p.pool, p.nnzc, &p.d_hdr->error);
     bscan<int>(p, s, p.M, p.nnzc, p.crp, &p.d_hdr->nnz_c);
     k_bcheck<<<1, 64, 0, s>>>(p.d_hdr, p.ccap);
     k_bnum_bins<<<bgrid(p, blocks_for(p.M, 256)), 256, 0, s>>>(p.M, p.cfg.table_shift, p.nnzc, p.sym_bin,
@@ -1693,11 +1688,9 @@ smash_status batch_size_tables(BPlan &p, hipStream_t s)
     if (need > p.gcap) {
         // larger tables from the caller's allocation callback (the caller
         // keeps owning the smaller ones it handed out before)
-        p.gkeys = (int *)p.alloc((size_t)need * sizeof(int), p.user);
-        p.gvals = (double *)p.alloc((size_t)need * sizeof(double), p.user);
-        p.gtouch = (int *)p.alloc((size_t)need * sizeof(int), p.user);
+        p.pool = (GSlot *)p.alloc((size_t)need * sizeof(GSlot), p.user);
         p.gcap = 0;
-        if (!p.gkeys || !p.gvals || !p.gtouch)
+        if (!p.pool)
             return fail(p.c, SMASH_ERR_OUT_OF_MEMORY, "global tables of %lld slots", need);
         p.gcap = need;
     }
@@ -1793,9 +1786,9 @@ smash_status smash_batch_plan_create(smash_ctx c, smash_dtype dtype, int32_t cou
     if (hipFuncSetAttribute((const void *)k_bsym_wide, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(p->wide_words * sizeof(unsigned))) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bnum_global<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            kGlobalRankBits / 8) != hipSuccess ||
+                            (int)global_rank_lds(kGlobalRankBits)) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bnum_global<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            kGlobalRankBits / 8) != hipSuccess ||
+                            (int)global_rank_lds(kGlobalRankBits)) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bnum_wide<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(kWideWin * sizeof(double))) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bnum_wide<double>, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -259,9 +259,10 @@ __global__ __launch_bounds__(kGlobalThreads) void k_bsym_global(const BatchDesc 
                                                                 const int *__restrict__ perm,
                                                                 const int *__restrict__ cap,
                                                                 const long long *__restrict__ goff, long long gcap,
-                                                                int *gkeys, int *__restrict__ nnzc, int *err)
+                                                                GSlot *pool, int *__restrict__ nnzc, int *err)
 {
-    __shared__ EnumScratch<float, kGlobalThreads> S;
+    __shared__ PieceScratch<float, kGlobalThreads> S;
+    __shared__ int s_front[1 << kFrontLog];
     __shared__ int s_cnt;
     const int cnt = h->count[kBinHeavy];
     const int *rows = perm + h->offset[kBinHeavy];
@@ -275,11 +276,10 @@ __global__ __launch_bounds__(kGlobalThreads) void k_bsym_global(const BatchDesc 
             if (threadIdx.x == 0) atomicOr(err, kErrCapacity);
             continue;
         }
-        int *keys = gkeys + off;
+        int *keys = (int *)(pool + off);             // its first 4 T bytes
         for (int t = threadIdx.x; t < T; t += kGlobalThreads) keys[t] = kEmpty;
-        __threadfence();
         __syncthreads();
-        sym_global_row(d.Arp, d.Acol, d.Brp, d.Bcol, (int)(grow - d.row0), cap[grow], keys, S, &s_cnt, &nnzc[grow],
+        sym_global_row(d.Arp, d.Acol, d.Brp, d.Bcol, (int)(grow - d.row0), cap[grow], keys, S, s_front, &s_cnt, &nnzc[grow],
                        err);
         __syncthreads();
     }
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(kGlobalThreads) void k_bnum_global(const BatchDesc 
                                                                 const int *__restrict__ prob, const BatchHdr *bh,
                                                                 const int *__restrict__ perm,
                                                                 const long long *__restrict__ goff, long long gcap,
-                                                                int *gkeys, double *gvals, int *gtouch, long long ccap,
+                                                                GSlot *pool, long long ccap,
                                                                 const long long *__restrict__ Crp,
                                                                 int *__restrict__ Ccol, V *__restrict__ Cval, int *err)
 {
@@ -311,7 +311,7 @@ __global__ __launch_bounds__(kGlobalThreads) void k_bnum_global(const BatchDesc 
             continue;
         }
         num_global_row<V>(d.Arp, d.Acol, (const V *)d.Aval, d.Brp, d.Bcol, (const V *)d.Bval, (int)(grow - d.row0),
-                          grow, d.cols, gkeys + off, gvals + off, gtouch + off, L, s_bm, Crp, Ccol, Cval, err);
+                          grow, d.cols, pool + off, L, s_bm, Crp, Ccol, Cval, err);
         __syncthreads();
     }
 }

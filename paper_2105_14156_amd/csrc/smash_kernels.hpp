@@ -2427,16 +2427,86 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_dense(
 }
 
 // ---------------------------------------------- heavy rows: global hash path
+//
+// A row's table lies in global memory but belongs to one block, so everything
+// about it has workgroup scope: atomics then run in the XCD's L2, where agent
+// scope sends them to memory, and a barrier orders them, where a fence of
+// agent scope writes the L2 back.
 
 __device__ __forceinline__ int gload(const int *p)
 {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 template <typename V>
 __device__ __forceinline__ V gload_v(const V *p)
 {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Compare-and-swap kEmpty -> key; returns the previous key.
+__device__ __forceinline__ int gclaim(int *p, int key)
+{
+    int old = kEmpty;
+    __hip_atomic_compare_exchange_strong(p, &old, key, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_WORKGROUP);
+    return old;
+}
+
+// A slot of a numeric table: key and value side by side, so that a probe and
+// the add that follows it touch one cache line.  `list` is an entry of the
+// row's list of claimed slots (entry i of the list is the i-th slot's), not of
+// this slot.
+struct alignas(16) GSlot {
+    double val;
+    int key;
+    int list;
+};
+
+// Slots of the U columns j in a table of 2^logT keys, key_at(h) the address of
+// slot h's (claimed where new; -1 for an absent product or a full table, which
+// sets kErrProbe): the first reads of all U are in flight together, and a
+// column that is there already costs no compare-and-swap.  claimed(slot) is
+// called for every new key.
+template <int U, typename K, typename F>
+__device__ __forceinline__ void gfind(int logT, const int (&j)[U], const bool (&ok)[U], int (&slot)[U], int *err,
+                                      K key_at, F claimed)
+{
+    const unsigned mask = (1u << logT) - 1;
+    int cur[U];
+    unsigned open = 0;                                   // products still looking for their slot
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        slot[u] = ok[u] ? (int)slot_of(j[u], logT) : -1;
+        cur[u] = ok[u] ? gload(key_at(slot[u])) : 0;
+        open |= ok[u] ? 1u << u : 0u;
+    }
+    for (unsigned probe = 0; open; ++probe) {
+        // claims of free slots, all in flight, then the next reads
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if ((open >> u & 1) && cur[u] == kEmpty) {
+                cur[u] = gclaim(key_at(slot[u]), j[u]);
+                if (cur[u] == kEmpty) {
+                    claimed(slot[u]);
+                    open &= ~(1u << u);
+                }
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (open >> u & 1) {
+                if (cur[u] == j[u]) {
+                    open &= ~(1u << u);
+                } else if (probe >= mask) {
+                    atomicOr(err, kErrProbe);
+                    slot[u] = -1;
+                    open &= ~(1u << u);
+                } else {
+                    slot[u] = (int)((unsigned)(slot[u] + 1) & mask);
+                    cur[u] = gload(key_at(slot[u]));
+                }
+            }
+    }
 }
 
 // Fills `n` ints with `v` (table initialisation).
@@ -2446,41 +2516,61 @@ __global__ __launch_bounds__(256) void k_fill_i32(long long n, int *__restrict__
         p[t] = v;
 }
 
-constexpr int kGlobalThreads = 1024;
+constexpr int kGlobalThreads = 512;
+
+// In front of a row's global table lies an LDS table of 2^kFrontLog slots: a
+// column takes one of its kFrontProbes home slots there if one is free when it
+// first comes, else it lives in the global table, for the whole row either
+// way.  The tables of the rows in flight are several times the L2 (16 B a slot,
+// 8K slots a row, 256 CUs), so every access to them is a line from memory; the
+// columns that come first, and a skewed row's frequent ones among them, stay
+// on chip.
+constexpr int kFrontLog = 12;
+constexpr int kFrontProbes = 2;
+
+// LDS slot of column j in the front table, -1 if both its places are taken;
+// fresh: it was claimed now.
+__device__ __forceinline__ int front_find(int *keys, int j, bool &fresh)
+{
+    unsigned h = slot_of(j, kFrontLog);
+    fresh = false;
+#pragma unroll
+    for (int p = 0; p < kFrontProbes; ++p) {
+        const int old = atomicCAS(&keys[h], kEmpty, j);
+        fresh = old == kEmpty;
+        if (fresh || old == j) return (int)h;
+        h = (h + 1) & ((1u << kFrontLog) - 1);
+    }
+    return -1;
+}
 
 // Symbolic count of one heavy row in global mode by a whole block: the row's
 // columns are inserted in its global key table of next_pow2(2 cap) slots
-// (device-scope CAS; the table must hold kEmpty) and counted into *out.
+// (the table must hold kEmpty) and counted into *out.
 __device__ __forceinline__ void sym_global_row(const int *__restrict__ Arp, const int *__restrict__ Acol,
                                                const int *__restrict__ Brp, const int *__restrict__ Bcol, int arow,
-                                               int cap, int *keys, EnumScratch<float, kGlobalThreads> &S, int *s_cnt,
-                                               int *out, int *err)
+                                               int cap, int *keys, PieceScratch<float, kGlobalThreads> &S, int *front,
+                                               int *s_cnt, int *out, int *err)
 {
     const int logT = gtable_log2(cap);
-    const unsigned mask = (1u << logT) - 1;
-    if (threadIdx.x == 0) *s_cnt = 0;
+    for (int t = threadIdx.x; t < 1 << kFrontLog; t += kGlobalThreads) front[t] = kEmpty;
+    if (threadIdx.x == 0) *s_cnt = 0;                      // the products' first barrier follows
     int mine = 0;
-    group_products<float, false, kGlobalThreads, 2>(
-        Arp[arow], Arp[arow + 1], threadIdx.x, S, Bcol, (const float *)nullptr,
-        [&](int e, int &bs, int &bl, float &) {
-            const int k = Acol[e];
-            bs = Brp[k];
-            bl = Brp[k + 1] - bs;
-        },
-        [&](int j) {
-            unsigned hh = slot_of(j, logT);
-            for (unsigned probe = 0; probe <= mask; ++probe) {
-                int cur = gload(&keys[hh]);
-                if (cur == j) return;
-                if (cur == kEmpty) {
-                    int old = atomicCAS(&keys[hh], kEmpty, j);
-                    if (old == kEmpty) { ++mine; return; }
-                    if (old == j) return;
-                }
-                hh = (hh + 1) & mask;
-            }
-            atomicOr(err, kErrProbe);
-        });
+    auto sink = [&](const auto &j, const auto &ok) {
+        constexpr int N = sizeof(j) / sizeof(j[0]);
+        int slot[N];
+        bool far[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            bool fresh = false;
+            far[u] = ok[u] && front_find(front, j[u], fresh) < 0;
+            mine += fresh;
+        }
+        gfind<N>(logT, j, far, slot, err, [&](int h) { return &keys[h]; }, [&](int) { ++mine; });
+    };
+    piece_products<float, false, kGlobalThreads, kGlobalThreads, 4>(Arp[arow], Arp[arow + 1], threadIdx.x, S, Acol,
+                                                                    (const float *)nullptr, Brp, 1, 1, Bcol,
+                                                                    (const float *)nullptr, sink);
     __syncthreads();
     mine = wave_sum(mine);
     if (lane_id() == 0 && mine) atomicAdd(s_cnt, mine);
@@ -2494,30 +2584,48 @@ __global__ __launch_bounds__(kGlobalThreads) void k_sym_global(
     const int *__restrict__ Bcol, const int *__restrict__ rows, const int *__restrict__ cap,
     const long long *__restrict__ goff, long long gbase, int *gkeys, int *__restrict__ nnzc, int *err)
 {
-    __shared__ EnumScratch<float, kGlobalThreads> S;
+    __shared__ PieceScratch<float, kGlobalThreads> S;
+    __shared__ int s_front[1 << kFrontLog];
     __shared__ int s_cnt;
     const int row = rows[blockIdx.x];
-    sym_global_row(Arp, Acol, Brp, Bcol, row, cap[row], gkeys + (goff[blockIdx.x] - gbase), S, &s_cnt, &nnzc[row],
-                   err);
+    sym_global_row(Arp, Acol, Brp, Bcol, row, cap[row], gkeys + (goff[blockIdx.x] - gbase), S, s_front, &s_cnt,
+                   &nnzc[row], err);
 }
 
 // Numeric pass of one heavy row in global mode by a whole block: clears the
 // row's global tag/value table, merges the row's products into it with
-// device-scope CAS and atomic add (FP64 values: the sum is rounded to the
+// compare-and-swap and atomic add (FP64 values: the sum is rounded to the
 // output type once, at write-out), then writes the entries in column order
 // at C's row `crow`.  Every slot the row claims is appended to the row's
-// touched-slot list (`touched`, nc entries: the paper's third version keeps
+// touched-slot list (nc entries: the paper's third version keeps
 // its tags in dense arrays with an offset array for the same purpose), so
 // the write-out reads the row's nc entries instead of scanning all T >= 2 nc
 // slots of its table: per window of kGlobalRankBits columns, the listed
-// entries of the window are marked in an LDS bitmap (s_bm, the block's
-// dynamic LDS), ranked by its popcount prefix and stored.
+// entries of the window are marked in an LDS bitmap and ranked by its
+// prefix counts (a count per owner thread, and 16-bit counts of the words
+// inside the owner's range).  The bitmap and those counts are the block's
+// dynamic LDS (global_rank_lds bytes, no more than B's columns need, so that
+// several rows share a CU where B is narrow).
+//
+// Bound by memory traffic: the tables' lines and their clearing.  RMAT 12289
+// A * A (edge factor 12, 20M products in heavy rows), FP32: 0.77 ms; without the
+// front table 1.53, with keys and values in separate arrays and a
+// compare-and-swap per product 1.80, with agent scope and a 2^19-column
+// bitmap per row 5.64 (symbolic pass 0.17, 0.57, 0.81 and 0.47 ms).
 constexpr int kGlobalRankBits = 1 << 19;
+
+__host__ __device__ __forceinline__ size_t global_rank_lds(long long ncols)
+{
+    const long long bits = ncols < kGlobalRankBits ? ncols : kGlobalRankBits;
+    return (size_t)((bits + 31) / 32 + 1) / 2 * 2 * (sizeof(unsigned) + sizeof(unsigned short));
+}
 
 template <typename V>
 struct GlobalNumLds {
-    EnumScratch<V, kGlobalThreads> S;
-    long long tmp[kGlobalThreads / kWave + 1];
+    double fval[1 << kFrontLog];           // front table
+    int fkey[1 << kFrontLog];
+    PieceScratch<V, kGlobalThreads> S;
+    int tmp[kGlobalThreads / kWave + 1];
     int base[kGlobalThreads];
     int ntouched;
 };
@@ -2526,109 +2634,102 @@ template <typename V>
 __device__ __forceinline__ void num_global_row(const int *__restrict__ Arp, const int *__restrict__ Acol,
                                                const V *__restrict__ Aval, const int *__restrict__ Brp,
                                                const int *__restrict__ Bcol, const V *__restrict__ Bval, int arow,
-                                               long long crow, int ncols, int *keys, double *vals, int *touched,
-                                               GlobalNumLds<V> &L, unsigned *s_bm, const long long *__restrict__ Crp,
-                                               int *__restrict__ Ccol, V *__restrict__ Cval, int *err)
+                                               long long crow, int ncols, GSlot *tab, GlobalNumLds<V> &L,
+                                               unsigned *s_bm, const long long *__restrict__ Crp, int *__restrict__ Ccol, V *__restrict__ Cval, int *err)
 {
-    constexpr int WORDS = kGlobalRankBits / 32;
-    constexpr int WPT = WORDS / kGlobalThreads;
+    constexpr int G = kGlobalThreads;
     const long long rb = Crp[crow];
     const int nc = (int)(Crp[crow + 1] - rb);
     const int logT = gtable_log2(nc);
     const int T = 1 << logT;
-    const unsigned mask = (unsigned)T - 1;
-    for (int t = threadIdx.x; t < T; t += kGlobalThreads) {
-        keys[t] = kEmpty;
-        vals[t] = 0.0;
+    for (int t = threadIdx.x; t < T; t += G) tab[t] = GSlot{0.0, kEmpty, 0};
+    for (int t = threadIdx.x; t < 1 << kFrontLog; t += G) {
+        L.fkey[t] = kEmpty;
+        L.fval[t] = 0.0;
     }
     if (threadIdx.x == 0) L.ntouched = 0;
-    __threadfence();
     __syncthreads();
-    group_products<V, true, kGlobalThreads, 2>(
-        Arp[arow], Arp[arow + 1], threadIdx.x, L.S, Bcol, Bval,
-        [&](int e, int &bs, int &bl, V &a) {
-            const int k = Acol[e];
-            bs = Brp[k];
-            bl = Brp[k + 1] - bs;
-            a = Aval[e];
-        },
-        [&](int j, double p) {
-            unsigned hh = slot_of(j, logT);
-            for (unsigned probe = 0; probe <= mask; ++probe) {
-                int cur = gload(&keys[hh]);
-                if (cur == kEmpty) {
-                    int old = atomicCAS(&keys[hh], kEmpty, j);
-                    if (old == kEmpty) {                  // claimed: list the slot
-                        const int at = atomicAdd(&L.ntouched, 1);
-                        if (at < nc) touched[at] = (int)hh;
-                    }
-                    cur = old == kEmpty ? j : old;
-                }
-                if (cur == j) {
-                    atomicAdd(&vals[hh], p);
-                    return;
-                }
-                hh = (hh + 1) & mask;
-            }
-            atomicOr(err, kErrProbe);
+    auto sink = [&](const auto &j, const auto &p, const auto &ok) {
+        constexpr int N = sizeof(j) / sizeof(j[0]);
+        int slot[N];
+        bool far[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            bool fresh;
+            const int f = ok[u] ? front_find(L.fkey, j[u], fresh) : 0;
+            far[u] = f < 0;
+            if (ok[u] && f >= 0) atomicAdd(&L.fval[f], p[u]);
+        }
+        gfind<N>(logT, j, far, slot, err, [&](int h) { return &tab[h].key; }, [&](int h) {
+            const int at = atomicAdd(&L.ntouched, 1);
+            if (at < nc) tab[at].list = h;
         });
-    __threadfence();
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (slot[u] >= 0)
+                __hip_atomic_fetch_add(&tab[slot[u]].val, p[u], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    };
+    piece_products<V, true, G, G, 4>(Arp[arow], Arp[arow + 1], threadIdx.x, L.S, Acol, Aval, Brp, 1, 1, Bcol, Bval,
+                                     sink);
     __syncthreads();
+    // the row's entries: the front table's slots, then the list
     const int nt = L.ntouched < nc ? L.ntouched : nc;
+    const int nf = 1 << kFrontLog;
+    auto key_of = [&](int t) { return t < nf ? L.fkey[t] : gload(&tab[tab[t - nf].list].key); };
+    const int top = ncols < kGlobalRankBits ? ncols : kGlobalRankBits;
+    const int words = (top + 31) >> 5;
+    unsigned short *s_pref = reinterpret_cast<unsigned short *>(s_bm + ((words + 1) & ~1));
+    const int sh = words <= G ? 0 : ceil_log2((words + G - 1) / G);      // 2^sh words per owner thread, at most 32
     long long done = 0;
     for (int lo = 0; lo < ncols; lo += kGlobalRankBits) {
-        const int hi = lo + kGlobalRankBits < ncols ? lo + kGlobalRankBits : ncols;
-        for (int t = threadIdx.x; t < WORDS; t += kGlobalThreads) s_bm[t] = 0u;
+        const int hi = lo < ncols - kGlobalRankBits ? lo + kGlobalRankBits : ncols;
+        for (int t = threadIdx.x; t < words; t += G) s_bm[t] = 0u;
         __syncthreads();
-        for (int t = threadIdx.x; t < nt; t += kGlobalThreads) {
-            const int j = gload(&keys[touched[t]]);
+        for (int t = threadIdx.x; t < nf + nt; t += G) {
+            const int j = key_of(t);                       // kEmpty lies below every window
             if (j >= lo && j < hi) atomicOr(&s_bm[(j - lo) >> 5], 1u << ((j - lo) & 31));
         }
         __syncthreads();
         int pc = 0;
-        for (int q = 0; q < WPT; ++q) pc += __popc(s_bm[threadIdx.x * WPT + q]);
-        long long tot;
-        const long long ex = block_excl_scan<long long, kGlobalThreads>((long long)pc, L.tmp, tot);
-        L.base[threadIdx.x] = (int)ex;
+        for (int q = (int)threadIdx.x << sh, e = q + (1 << sh) < words ? q + (1 << sh) : words; q < e; ++q) {
+            s_pref[q] = (unsigned short)pc;
+            pc += __popc(s_bm[q]);
+        }
+        int tot;
+        const int ex = block_excl_scan<int, G>(pc, L.tmp, tot);
+        L.base[threadIdx.x] = ex;
         __syncthreads();
-        for (int t = threadIdx.x; t < nt; t += kGlobalThreads) {
-            const int slot = touched[t];
-            const int j = gload(&keys[slot]);
+        for (int t = threadIdx.x; t < nf + nt; t += G) {
+            const int j = key_of(t);
             if (j < lo || j >= hi) continue;
-            const int jl = j - lo, wd = jl >> 5, owner = wd / WPT;
-            int rank = L.base[owner];
-            for (int q = owner * WPT; q < wd; ++q) rank += __popc(s_bm[q]);
-            rank += __popc(s_bm[wd] & ((1u << (jl & 31)) - 1u));
-            const long long pos = done + rank;
+            const int jl = j - lo, wd = jl >> 5;
+            const long long pos = done + L.base[wd >> sh] + s_pref[wd] + __popc(s_bm[wd] & ((1u << (jl & 31)) - 1u));
             if (pos < nc) {
                 store_c(&Ccol[rb + pos], j);
-                store_c(&Cval[rb + pos], (V)gload_v(&vals[slot]));
+                store_c(&Cval[rb + pos], (V)(t < nf ? L.fval[t] : gload_v(&tab[tab[t - nf].list].val)));
             }
         }
         done += tot;
         __syncthreads();
-        if (done >= nt) break;                    // every listed entry is out
+        if (done >= nc || hi == ncols) break;     // every entry is out
     }
-    if (threadIdx.x == 0 && (done != nc || L.ntouched != nc)) atomicOr(err, kErrCount);
+    if (threadIdx.x == 0 && done != nc) atomicOr(err, kErrCount);
 }
 
-// Numeric phase of heavy rows in global mode: one block per row (the row's
-// table and touched-slot list start at the same offset of the pool's key,
-// value and list arrays).
+// Numeric phase of heavy rows in global mode: one block per row.
 template <typename V>
 __global__ __launch_bounds__(kGlobalThreads) void k_num_global(
     const int *__restrict__ Arp, const int *__restrict__ Acol, const V *__restrict__ Aval,
     const int *__restrict__ Brp, const int *__restrict__ Bcol, const V *__restrict__ Bval,
-    const int *__restrict__ rows, int ncols, const long long *__restrict__ goff, long long gbase, int *gkeys,
-    double *gvals, int *gtouch, const long long *__restrict__ Crp, int *__restrict__ Ccol, V *__restrict__ Cval,
+    const int *__restrict__ rows, int ncols, const long long *__restrict__ goff, long long gbase, GSlot *pool,
+    const long long *__restrict__ Crp, int *__restrict__ Ccol, V *__restrict__ Cval,
     int *err)
 {
-    extern __shared__ unsigned s_bm[];                     // [kGlobalRankBits / 32]
+    extern __shared__ unsigned s_bm[];                     // global_rank_lds(ncols) bytes
     __shared__ GlobalNumLds<V> L;
     const int row = rows[blockIdx.x];
-    const long long at = goff[blockIdx.x] - gbase;
-    num_global_row<V>(Arp, Acol, Aval, Brp, Bcol, Bval, row, row, ncols, gkeys + at, gvals + at, gtouch + at, L, s_bm,
-                      Crp, Ccol, Cval, err);
+    num_global_row<V>(Arp, Acol, Aval, Brp, Bcol, Bval, row, row, ncols,
+                      pool + (goff[blockIdx.x] - gbase), L, s_bm, Crp, Ccol, Cval, err);
 }
 
 }  // namespace smash

@@ -463,3 +463,26 @@ def test_ranked_segment_edges(sm, ctx, oracle_mod, dtype):
     full_check(sm, ctx, A, B, dtype, oracle_mod, False, "segment edges")
     st = ctx.stats()
     assert st["rows_heavy"] == A.rows and st["heavy_segments"] > A.rows and st["heavy_dense_chunks"] == 0, st
+
+
+@pytest.mark.parametrize("count", [1025, 4096, 6000])
+@pytest.mark.parametrize("collide", [False, True])
+def test_global_front_table(sm, ctx, oracle_mod, count, collide):
+    """Global mode: the LDS table in front of a row's global table (4096 slots,
+    two places per column).  Rows of columns that all share one home slot
+    (nearly every column lives in the global table) and of evenly spread ones
+    (fewer, as many and more than the front holds), each column reached twice."""
+    n = 1 << 25
+    j = np.arange(n if collide else 40 * count, dtype=np.uint32)
+    if collide:
+        j = j[((j * np.uint32(2654435769)) >> np.uint32(20)) == 5]
+    cols = np.sort(syn.splitmix64(5, 0, 3 * count) % np.uint64(len(j)))
+    cols = j[np.unique(cols)[:count].astype(np.int64)].astype(np.int32)
+    assert len(cols) == count
+    B = syn.CSR(2, n, np.array([0, count, 2 * count], np.int32), np.concatenate([cols, cols]),
+                2.0 * syn.uniform01(81, 0, 2 * count) - 1.0)
+    A = syn.CSR(3, 2, np.array([0, 2, 2, 4], np.int32), np.array([0, 1, 0, 1], np.int32),
+                2.0 * syn.uniform01(82, 0, 4) - 1.0)
+    ctx.set_option(sm.OPT_HEAVY_MODE, 1)
+    full_check(sm, ctx, A, B, np.float64, oracle_mod, False, f"front {count} {collide}")
+    assert ctx.stats()["rows_heavy"] == 2
