@@ -975,7 +975,7 @@ smash_status symbolic_impl(smash_ctx c, const smash_csr *A, const smash_csr *B, 
     const bool global = p.heavy_mode == 1;
     const bool learned = fuse && c->opt[SMASH_OPT_FUSED_SIZING] == 0;
     TRY(launch(c, K_ANALYZE, s, [&] {
-        k_analyze<<<blocks_for(m, 256 / kRowLanes), 256, 0, s>>>(
+        k_analyze<<<row_blocks((int)m), kRowThreads, 0, s>>>(
             (int)m, (int)p.n, p.lds_row_max, A->row_ptr, A->col_idx, B->row_ptr, p.ub, p.cap, p.nnzc, p.sym_bin,
             learned ? p.feats : nullptr, learned ? p.maxb : nullptr, perr(c));
     }));
@@ -1257,8 +1257,8 @@ smash_status smash_features(smash_ctx c, const smash_csr *A, const smash_csr *B,
     if (A->rows == 0) return SMASH_OK;
     DeviceGuard g(c->device);
     TRY(launch(c, K_FEATURES, s, [&] {
-        k_features<<<blocks_for(A->rows, 4), 256, 0, s>>>((int)A->rows, (int)B->cols, A->row_ptr, A->col_idx,
-                                                          B->row_ptr, feats, nullptr, nullptr);
+        k_features<<<row_blocks((int)A->rows), kRowThreads, 0, s>>>((int)A->rows, (int)B->cols, A->row_ptr,
+                                                                          A->col_idx, B->row_ptr, feats);
     }));
     return SMASH_OK;
 }

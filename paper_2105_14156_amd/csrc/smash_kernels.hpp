@@ -955,17 +955,23 @@ __device__ __forceinline__ float row_feature(int t, int na, long long ub, double
 }
 
 // Row analysis (step a1): products ub_i = sum_k nnz(B_k) over row i of A, the
-// output bound cap_i = min(ub_i, cols) and the row's symbolic bin.  A wave
-// takes eight rows: rows of at most 64 entries are summed by their own group
-// of eight lanes (most rows of A have a few dozen entries, so a whole wave
-// per row would leave most lanes idle), longer rows one after another by the
-// whole wave, four entries per lane in flight, so that a hub row does not
-// leave one group with a long serial chain.  With feats non-NULL it also
-// writes the learned predictor's six features and max_k nnz(B_k) (maxb_out)
-// of the rows whose bound exceeds the LDS row limit, the only rows the
-// predictor is asked about.
+// output bound cap_i = min(ub_i, cols) and the row's symbolic bin.  With feats
+// non-NULL it also writes the learned predictor's six features and
+// max_k nnz(B_k) (maxb_out) of the rows whose bound exceeds the LDS row limit,
+// the only rows the predictor is asked about.
+//
+// Bound by the latency of two dependent gathers per entry, so the work is
+// spread for it (for_rows): rows of at most kShortRow entries are summed by
+// groups of eight lanes, consecutive rows in consecutive groups; longer rows by
+// a whole wave, eight entries per lane in flight, and the rows a wave looks
+// at lie an odd stride apart, since hub rows come in clusters (consecutive
+// rows in RMAT matrices).  RMAT scale 21, edge factor 8 (rows of up to 40K
+// entries): 0.23 ms; with eight consecutive rows per wave, long ones summed by
+// the wave in turn, 0.58.  A limit of 32 or 64 entries: 0.24 and 0.23.
 constexpr int kRowLanes = 8;
-constexpr int kShortRow = 64;
+constexpr int kShortRow = 128;
+constexpr int kRowThreads = 256;
+constexpr int kBlockRows = kRowThreads / kRowLanes;
 
 // Partial sums of one lane over entries e0 + first, e0 + first + step, ...
 struct RowPart {
@@ -974,18 +980,18 @@ struct RowPart {
     int mx = 0, mn = 0x7fffffff;
 };
 
-template <bool FEATS>
+template <bool FEATS, int U = 4>
 __device__ __forceinline__ void row_part(const int *__restrict__ Acol, const int *__restrict__ Brp, int e, int e1,
                                          int step, RowPart &r)
 {
-    for (; e + 3 * step < e1; e += 4 * step) {
-        int k[4], len[4];
+    for (; e < e1 - (U - 1) * step; e += U * step) {
+        int k[U], len[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) k[u] = Acol[e + u * step];
+        for (int u = 0; u < U; ++u) k[u] = Acol[e + u * step];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) len[u] = Brp[k[u] + 1] - Brp[k[u]];
+        for (int u = 0; u < U; ++u) len[u] = Brp[k[u] + 1] - Brp[k[u]];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
+        for (int u = 0; u < U; ++u) {
             r.ub += len[u];
             if constexpr (FEATS) {
                 r.sq += (double)len[u] * (double)len[u];
@@ -1020,16 +1026,13 @@ __device__ __forceinline__ void row_reduce(RowPart &r, int width)
     }
 }
 
-// Sums of the wave's eight rows [row0, row0 + 8) into the lanes of each
-// row's group (every lane of the wave calls it).
+// Sums of the entries [e0, e1) of the wave's eight rows, one row per group of
+// eight lanes, into the lanes of each group (every lane of the wave calls it).
 template <bool FEATS>
-__device__ __forceinline__ RowPart wave_rows(int m, int row0, const int *__restrict__ Arp,
-                                             const int *__restrict__ Acol, const int *__restrict__ Brp, int &e0,
-                                             int &e1)
+__device__ __forceinline__ RowPart wave_rows(int e0, int e1, const int *__restrict__ Acol,
+                                             const int *__restrict__ Brp)
 {
-    const int lane = lane_id(), sl = lane & (kRowLanes - 1), row = row0 + lane / kRowLanes;
-    e0 = row < m ? Arp[row] : 0;
-    e1 = row < m ? Arp[row + 1] : 0;
+    const int lane = lane_id(), sl = lane & (kRowLanes - 1);
     const bool lng = e1 - e0 > kShortRow;
     RowPart r;
     if (!lng) row_part<FEATS>(Acol, Brp, e0 + sl, e1, kRowLanes, r);
@@ -1047,38 +1050,76 @@ __device__ __forceinline__ RowPart wave_rows(int m, int row0, const int *__restr
     return r;
 }
 
-__global__ __launch_bounds__(256) void k_analyze(int m, int ncols, int lds_row_max,
+// Blocks for the long rows and for all rows of an analysis of m rows; the long
+// ones come first in the grid.  All but one of the long blocks' waves look at
+// rows, 64 each (an odd number of waves is the stride).
+__host__ __device__ __forceinline__ int long_row_blocks(int m) { return (int)(((long long)m + kWave - 1) / kRowThreads) + 1; }
+__host__ __device__ __forceinline__ int row_blocks(int m)
+{
+    return long_row_blocks(m) + (m + kBlockRows - 1) / kBlockRows;
+}
+
+// finish(row, sl, e0, e1, sums) for every row of A, by eight lanes sl = 0 .. 7 at
+// least.  A grid of row_blocks(m) blocks of kRowThreads threads.
+template <bool FEATS, typename F>
+__device__ __forceinline__ void for_rows(int m, const int *__restrict__ Arp, const int *__restrict__ Acol,
+                                         const int *__restrict__ Brp, F finish)
+{
+    const int lane = lane_id(), nl = long_row_blocks(m);
+    if ((int)blockIdx.x < nl) {
+        const int waves = nl * (kRowThreads / kWave) - 1, w = blockIdx.x * (kRowThreads / kWave) + threadIdx.x / kWave;
+        if (w == waves) return;
+        const long long row = (long long)lane * waves + w;
+        const int e0 = row < m ? Arp[row] : 0, e1 = row < m ? Arp[row + 1] : 0;
+        for (unsigned long long todo = __ballot(e1 - e0 > kShortRow); todo; todo &= todo - 1) {
+            const int src = __ffsll((long long)todo) - 1;
+            const int f0 = __builtin_amdgcn_readlane(e0, src), f1 = __builtin_amdgcn_readlane(e1, src);
+            RowPart r;
+            row_part<FEATS, 8>(Acol, Brp, f0 + lane, f1, kWave, r);
+            row_reduce<FEATS>(r, kWave);
+            finish(src * waves + w, lane, f0, f1, r);
+        }
+        return;
+    }
+    const int row = ((int)blockIdx.x - nl) * kBlockRows + (int)threadIdx.x / kRowLanes, sl = lane & (kRowLanes - 1);
+    const int e0 = row < m ? Arp[row] : 0, e1 = row < m ? Arp[row + 1] : 0;
+    const bool here = row < m && e1 - e0 <= kShortRow;
+    RowPart r;
+    if (here) row_part<FEATS>(Acol, Brp, e0 + sl, e1, kRowLanes, r);
+    row_reduce<FEATS>(r, kRowLanes);
+    if (here) finish(row, sl, e0, e1, r);
+}
+
+__global__ __launch_bounds__(kRowThreads) void k_analyze(int m, int ncols, int lds_row_max,
                                                  const int *__restrict__ Arp, const int *__restrict__ Acol,
                                                  const int *__restrict__ Brp, long long *__restrict__ ub_out,
                                                  int *__restrict__ cap_out, int *__restrict__ nnzc,
                                                  unsigned char *__restrict__ bin_out, float *__restrict__ feats,
                                                  int *__restrict__ maxb_out, const int *err)
 {
-    const int row0 = (blockIdx.x * 256 + (int)threadIdx.x) / kWave * kRowLanes;
-    if (row0 >= m || stopped(err)) return;               // whole waves
-    const int sl = lane_id() & (kRowLanes - 1), row = row0 + lane_id() / kRowLanes;
-    int e0, e1;
-    RowPart r = feats ? wave_rows<true>(m, row0, Arp, Acol, Brp, e0, e1)
-                      : wave_rows<false>(m, row0, Arp, Acol, Brp, e0, e1);
-    if (row >= m) return;
-    const long long ub = r.ub;
-    if (feats && (ub < ncols ? ub : ncols) > lds_row_max) {
-        // the predictor's six features (the same arithmetic as k_features):
-        // lanes 0..5 of the row's group write one each
-        if (sl < 6) feats[(long long)row * 6 + sl] = row_feature(sl, e1 - e0, ub, r.sq, r.mx, r.mn, ncols);
-        if (sl == 0) maxb_out[row] = e1 > e0 ? r.mx : 0;
-    }
-    if (sl == 0) {
-        const int cap = (int)(ub < ncols ? ub : ncols);
-        int b;
-        if (ub == 0) b = kBinEmpty;
-        else if (cap > lds_row_max) b = kBinHeavy;
-        else b = lds_bin(cap);
-        ub_out[row] = ub;
-        cap_out[row] = cap;
-        nnzc[row] = 0;
-        bin_out[row] = (unsigned char)b;
-    }
+    if (stopped(err)) return;
+    auto finish = [&](int row, int sl, int e0, int e1, const RowPart &r) {
+        const long long ub = r.ub;
+        if (feats && sl < 6 && (ub < ncols ? ub : ncols) > lds_row_max) {
+            // the predictor's six features (the same arithmetic as k_features):
+            // lanes 0..5 write one each
+            feats[(long long)row * 6 + sl] = row_feature(sl, e1 - e0, ub, r.sq, r.mx, r.mn, ncols);
+            if (sl == 0) maxb_out[row] = e1 > e0 ? r.mx : 0;
+        }
+        if (sl == 0) {
+            const int cap = (int)(ub < ncols ? ub : ncols);
+            int b;
+            if (ub == 0) b = kBinEmpty;
+            else if (cap > lds_row_max) b = kBinHeavy;
+            else b = lds_bin(cap);
+            ub_out[row] = ub;
+            cap_out[row] = cap;
+            nnzc[row] = 0;
+            bin_out[row] = (unsigned char)b;
+        }
+    };
+    if (feats) for_rows<true>(m, Arp, Acol, Brp, finish);
+    else for_rows<false>(m, Arp, Acol, Brp, finish);
 }
 
 // Workspace query (smash_workspace_size): the number of heavy rows and the
@@ -1098,9 +1139,9 @@ __global__ __launch_bounds__(256) void k_ws_query(int m, int ncols, int lds_row_
     unsigned long long gsum = 0, gmax = 0;
     if (!stopped(&h->error)) {
         for (int r0 = blockIdx.x * RPB + w * kRowLanes; r0 < m; r0 += gridDim.x * RPB) {
-            int e0, e1;
-            const RowPart r = wave_rows<false>(m, r0, Arp, Acol, Brp, e0, e1);
             const int row = r0 + lane / kRowLanes;
+            const int e0 = row < m ? Arp[row] : 0, e1 = row < m ? Arp[row + 1] : 0;
+            const RowPart r = wave_rows<false>(e0, e1, Acol, Brp);
             const long long cap = r.ub < ncols ? r.ub : ncols;
             if (row < m && sl == 0 && cap > lds_row_max) {
                 const unsigned long long t = 1ull << gtable_log2(cap);

@@ -36,6 +36,24 @@ def test_features_match_oracle(env, oracle_mod):
         np.testing.assert_allclose(F, ref, rtol=2e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("m", [1, 63, 64, 192, 193, 257, 449])
+def test_features_row_split(env, m):
+    """Row analysis at the edges of its split (rows of up to 128 entries by
+    eight lanes, longer ones by a wave each): every row count around whole
+    waves and blocks, long and empty rows first, last and in clusters."""
+    torch, smash, ctx = env
+    lens = np.array([129, 0, 3000, 128, 1, 127, 513, 7])[np.arange(m) % 8]
+    lens[-1] = 2000
+    cols = 4000
+    ptr = np.zeros(m + 1, np.int32)
+    ptr[1:] = np.cumsum(lens)
+    col = np.concatenate([np.arange(k, dtype=np.int32) + (i % 500) for i, k in enumerate(lens)])
+    X = syn.CSR(m, cols, ptr, col, np.ones(len(col), np.float32))
+    Y = syn.rmat_rect(cols, 4, 9, np.float32)
+    F = ctx.features(smash.to_device(X), smash.to_device(Y)).cpu().numpy()
+    np.testing.assert_allclose(F, mlp.features(X, Y), rtol=2e-6, atol=1e-6)
+
+
 def _setup(torch, n=3000, seed=3):
     F = np.abs(syn.normal01(seed, 0, n * 6).reshape(n, 6)) * 4
     y = F[:, 1] * 0.7 + np.sin(F[:, 0]) + 0.1 * syn.normal01(seed + 1, 0, n)
