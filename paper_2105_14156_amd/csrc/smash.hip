@@ -430,7 +430,7 @@ smash_status launch_sym_bin(smash_ctx c, hipStream_t s, const Plan &p)
     const unsigned grid = persistent_grid(c, kern, S::THREADS, S::RPW, p.m);
     return launch(c, K_SYM_ROWS, s, [&] {
         kern<<<grid, S::THREADS, 0, s>>>(p.A.row_ptr, p.A.col_idx, p.B.row_ptr, p.B.col_idx, p.sym_perm,
-                                         &c->d_hdr->sym, LOGT - kMinLogT, p.nnzc, perr(c));
+                                         &c->d_hdr->sym, LOGT - kMinLogT, (int)p.n, p.nnzc, perr(c));
     });
 }
 

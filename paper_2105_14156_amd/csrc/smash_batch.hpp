@@ -206,7 +206,7 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_bsym_rows(const BatchDesc *
         RowDesc nxt{};
         if (base + stride + g < cnt) nxt = rows[base + stride + g];
         const BatchDesc &d = desc[active ? cur.prob : 0];
-        sym_row<LOGT, WPR>(cur.e0, cur.e1, d.Acol, d.Brp, d.Bcol, active, gt, s_keys[g], s_en[g], &s_cnt[g],
+        sym_row<LOGT, WPR>(cur.e0, cur.e1, d.Acol, d.Brp, d.Bcol, d.cols, active, gt, s_keys[g], s_en[g], &s_cnt[g],
                            &nnzc[active ? cur.grow : 0], err);
         group_sync<WPR>();
         cur = nxt;

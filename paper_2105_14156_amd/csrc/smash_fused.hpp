@@ -120,6 +120,23 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_fused_rows(
     const int row = active ? rows[r] : 0;
     int *keys = s_keys[g];
     double *vals = s_vals[g];
+    if constexpr (WPR == 1 && LOGT <= kSmallLogT) {
+        SmallRow sr;
+        if (!active) continue;
+        if (small_row<V, true>(Arp[row], Arp[row + 1], Acol, Aval, Brp, Bcol, Bval, ncols, s_en[g].pincl, sr)) {
+            const long long o = stage_off[row];
+            const bool ok = sr.count <= fcap[row] && o + fcap[row] <= stage_cap;
+            if (ok && sr.tail) {
+                scol[o + sr.pos] = sr.col;
+                sval[o + sr.pos] = (V)sr.val;
+            }
+            if (gt == 0) {
+                status[row] = ok ? 1 : 0;
+                if (ok) nnzc[row] = sr.count;
+            }
+            continue;
+        }
+    }
     for (int t = gt; t < T; t += G) {
         keys[t] = kEmpty;
         vals[t] = 0.0;

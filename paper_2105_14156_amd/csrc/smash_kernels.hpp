@@ -898,6 +898,141 @@ __device__ __forceinline__ void lds_insert_add_ord_u(int *keys, double *vals, in
     }
 }
 
+// --------------------------------------------------------------- small rows
+//
+// A row of at most 64 products is merged in one wave's registers, a product
+// per lane: a bitonic network over the lanes sorts the columns, equal
+// neighbours are one entry, their values are added by a segmented scan.  No
+// table is cleared, probed, compacted or ranked: half the instructions of the
+// hashed form (which spends some 200 on ordering 64 entries alone), and
+// instructions are what bounds these rows.  A million rows of 8 x 8 products,
+// FP32: numeric 1.09 -> 0.50 ms, symbolic 0.58 -> 0.31.
+constexpr int kSmallCols = 1 << 25;      // a column and a lane in 32 bits
+
+// The value of lane (l ^ MASK): DPP within a row of 16, else the LDS crossbar.
+template <int MASK>
+__device__ __forceinline__ unsigned lane_xor(unsigned v)
+{
+    if constexpr (MASK == 1) return __builtin_amdgcn_update_dpp(0, (int)v, 0xb1, 0xf, 0xf, true);         // quad_perm 1 0 3 2
+    else if constexpr (MASK == 2) return __builtin_amdgcn_update_dpp(0, (int)v, 0x4e, 0xf, 0xf, true);    // quad_perm 2 3 0 1
+    else if constexpr (MASK == 3) return __builtin_amdgcn_update_dpp(0, (int)v, 0x1b, 0xf, 0xf, true);    // quad_perm 3 2 1 0
+    else if constexpr (MASK == 7) return __builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xf, 0xf, true);   // row_half_mirror
+    else if constexpr (MASK == 8) return __builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xf, 0xf, true);   // row_ror:8
+    else if constexpr (MASK == 15) return __builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xf, 0xf, true);  // row_mirror
+    else if constexpr (MASK < 32) return __builtin_amdgcn_ds_swizzle((int)v, (MASK << 10) | 0x1f);
+    else return __shfl_xor((int)v, MASK, kWave);
+}
+
+// Compare-exchange of every lane with lane (l ^ MASK): the one whose bit BIT is
+// clear keeps the smaller value.
+template <int MASK, int BIT>
+__device__ __forceinline__ void sort_step(unsigned &v)
+{
+    const unsigned o = lane_xor<MASK>(v);
+    const unsigned lo = v < o ? v : o, hi = v < o ? o : v;
+    v = lane_id() & BIT ? hi : lo;
+}
+
+// Ascending sort of one value per lane of the wave.
+__device__ __forceinline__ void wave_sort(unsigned &v)
+{
+    sort_step<1, 1>(v);
+    sort_step<3, 2>(v);
+    sort_step<1, 1>(v);
+    sort_step<7, 4>(v);
+    sort_step<2, 2>(v);
+    sort_step<1, 1>(v);
+    sort_step<15, 8>(v);
+    sort_step<4, 4>(v);
+    sort_step<2, 2>(v);
+    sort_step<1, 1>(v);
+    sort_step<31, 16>(v);
+    sort_step<8, 8>(v);
+    sort_step<4, 4>(v);
+    sort_step<2, 2>(v);
+    sort_step<1, 1>(v);
+    sort_step<63, 32>(v);
+    sort_step<16, 16>(v);
+    sort_step<8, 8>(v);
+    sort_step<4, 4>(v);
+    sort_step<2, 2>(v);
+    sort_step<1, 1>(v);
+}
+
+// One lane's share of a merged small row: with `tail` set, entry `pos` of the
+// row is (col, val); count is the row's number of entries.
+struct SmallRow {
+    bool tail;
+    int pos, col, count;
+    double val;
+};
+
+// Merges the products of the A entries [e0, e1) if they are at most 64 (else,
+// and for more than 64 entries, returns false).  own: 64 ints of the wave's
+// LDS.  Every lane of the wave calls it.
+template <typename V, bool WITH_VAL>
+__device__ __forceinline__ bool small_row(int e0, int e1, const int *__restrict__ Acol, const V *__restrict__ Aval,
+                                          const int *__restrict__ Brp, const int *__restrict__ Bcol,
+                                          const V *__restrict__ Bval, int ncols, int *own, SmallRow &out)
+{
+    const int lane = lane_id();
+    if (e1 - e0 > kWave || ncols > kSmallCols) return false;      // wave-uniform
+    int bs = 0, bl = 0;
+    V a = V(0);
+    if (e0 + lane < e1) {
+        const int k = Acol[e0 + lane];
+        bs = Brp[k];
+        bl = Brp[k + 1] - bs;
+        if constexpr (WITH_VAL) a = Aval[e0 + lane];
+    }
+    const int incl = wave_incl_scan(bl);
+    const int n = __builtin_amdgcn_readlane(incl, kWave - 1);
+    // a prefix that wraps is not small either: every length is at most n then
+    if (n > kWave || __ballot(bl > kWave)) return false;
+    // the entry of lane q's product: each entry marks its first product, and
+    // the marks' running maximum names the entry
+    const int first = incl - bl;
+    own[lane] = 0;
+    wave_sync();
+    if (bl > 0) own[first] = lane;
+    wave_sync();
+    const int src = wave_scan_dpp(own[lane], 0, [](int x, int y) { return x > y ? x : y; });
+    const bool live = lane < n;
+    const int q = __shfl(bs - first, src, kWave) + lane;
+    const int at = live ? q : 0;
+    const int j = Bcol[at];
+    double p = 0.0;
+    if constexpr (WITH_VAL) {
+        const V b = Bval[at];
+        p = (double)__shfl(a, src, kWave) * (double)b + 0.0;      // a sum that starts at 0.0
+    }
+    unsigned c = live ? ((unsigned)j << 6) | (unsigned)lane : 0xffffffffu;
+    wave_sort(c);
+    const int col = (int)(c >> 6);                                 // absent products come last
+    const int before = __builtin_amdgcn_update_dpp(-1, col, kDppWaveShr1, 0xf, 0xf, false);
+    const unsigned long long heads = __ballot(live && col != before);
+    out.count = __popcll(heads);
+    if constexpr (WITH_VAL) {
+        p = __shfl(p, (int)(c & 63u), kWave);
+        const unsigned long long upto = heads & (~0ull >> (63 - lane));
+        if (out.count < n) {
+            // runs of equal columns: an inclusive scan within each run
+            const int start = 63 - __clzll((long long)upto);
+            for (int d = 1; d < kWave; d <<= 1) {
+                const bool take = live && lane - d >= start;
+                if (!__ballot(take)) break;
+                const double o = __shfl_up(p, d, kWave);
+                if (take) p += o;
+            }
+        }
+        out.tail = live && (lane == n - 1 || (heads >> (lane + 1) & 1));
+        out.pos = __popcll(upto) - 1;
+        out.col = col;
+        out.val = p;
+    }
+    return true;
+}
+
 // --------------------------------------------------------------- validation
 
 // CSR preconditions of one matrix in two passes (a violation sets `flag` in
@@ -1308,17 +1443,29 @@ __global__ __launch_bounds__(256) void k_scatter(int m, const unsigned char *__r
 
 // ------------------------------------------------------- symbolic, LDS hash
 
+// Tables up to this size hold rows of at most 64 entries, nearly all of which
+// have at most 64 products.
+constexpr int kSmallLogT = 7;
+
 // Symbolic count of one light row by a group of WPR waves (gt: thread index
 // in the group; every thread of the group calls it): the distinct columns of
 // the row's A entries [e0, e1) times B, counted in an LDS key table of
 // 2^LOGT slots (step a3), are stored to *out by the group's first thread.
 template <int LOGT, int WPR>
 __device__ __forceinline__ void sym_row(int e0, int e1, const int *__restrict__ Acol, const int *__restrict__ Brp,
-                                        const int *__restrict__ Bcol, bool active, int gt, int *keys,
+                                        const int *__restrict__ Bcol, int ncols, bool active, int gt, int *keys,
                                         EnumScratch<float, WPR * kWave> &en, int *s_cnt, int *out, int *err)
 {
     constexpr int T = 1 << LOGT;
     constexpr int G = WPR * kWave;
+    if constexpr (WPR == 1 && LOGT <= kSmallLogT) {
+        SmallRow r;
+        if (!active) return;
+        if (small_row<float, false>(e0, e1, Acol, nullptr, Brp, Bcol, nullptr, ncols, en.pincl, r)) {
+            if (gt == 0) *out = r.count;
+            return;
+        }
+    }
     for (int t = gt; t < T; t += G) keys[t] = kEmpty;
     if (gt == 0) *s_cnt = 0;
     group_sync<WPR>();
@@ -1349,7 +1496,7 @@ template <int LOGT, int WPR, int RPW>
 __global__ __launch_bounds__(kWave *WPR *RPW) void k_sym_rows(const int *__restrict__ Arp, const int *__restrict__ Acol,
                                                               const int *__restrict__ Brp, const int *__restrict__ Bcol,
                                                               const int *__restrict__ perm, const BinHdr *h, int bin,
-                                                              int *__restrict__ nnzc, int *err)
+                                                              int ncols, int *__restrict__ nnzc, int *err)
 {
     static_assert(RPW == 1 || WPR == 1, "multi-row blocks use one wave per row");
     constexpr int G = WPR * kWave;
@@ -1366,7 +1513,7 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_sym_rows(const int *__restr
         const bool active = r < nrows;
         const int row = active ? rows[r] : 0;
         const int e0 = active ? Arp[row] : 0, e1 = active ? Arp[row + 1] : 0;
-        sym_row<LOGT, WPR>(e0, e1, Acol, Brp, Bcol, active, gt, s_keys[g], s_en[g], &s_cnt[g], &nnzc[row], err);
+        sym_row<LOGT, WPR>(e0, e1, Acol, Brp, Bcol, ncols, active, gt, s_keys[g], s_en[g], &s_cnt[g], &nnzc[row], err);
         group_sync<WPR>();
     }
 }
@@ -1617,6 +1764,18 @@ __device__ __forceinline__ void num_row(int e0, int e1, const int *__restrict__ 
     constexpr int SPT = T / G;          // slots per thread in the compaction
     static_assert(SPT >= 1, "table smaller than its group");
     const int lane = lane_id(), wg = gt / kWave;
+    if constexpr (WPR == 1 && LOGT <= kSmallLogT && HASH == 0) {
+        SmallRow r;
+        if (!active) return;
+        if (small_row<V, true>(e0, e1, Acol, Aval, Brp, Bcol, Bval, ncols, en.pincl, r)) {
+            if (gt == 0 && nc != r.count) atomicOr(err, kErrCount);
+            if (r.tail && r.pos < nc) {
+                store_c(&Ccol[rb + r.pos], r.col);
+                store_c(&Cval[rb + r.pos], (V)r.val);
+            }
+            return;
+        }
+    }
     const int lc = ceil_log2(ncols);
     const int shift = lc > LOGT ? lc - LOGT : 0;
     for (int t = gt; t < T; t += G) {

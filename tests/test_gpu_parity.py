@@ -486,3 +486,46 @@ def test_global_front_table(sm, ctx, oracle_mod, count, collide):
     ctx.set_option(sm.OPT_HEAVY_MODE, 1)
     full_check(sm, ctx, A, B, np.float64, oracle_mod, False, f"front {count} {collide}")
     assert ctx.stats()["rows_heavy"] == 2
+
+
+def _small_row_edges(dtype, n):
+    """Rows around 64 products (the most one wave merges in registers): 1, 63,
+    64 and 65, all columns distinct, all equal and in runs, empty B rows first,
+    between and last, 64 and 65 A entries."""
+    rows_b, rows_a = [], []
+
+    def row(*cols):
+        rows_a.append(list(range(len(rows_b), len(rows_b) + len(cols))))
+        rows_b.extend(np.asarray(sorted(set(int(x) for x in c)), np.int64) for c in cols)
+
+    far = n - 1
+    for k in (1, 2, 31, 32, 33, 63, 64, 65):
+        row(np.linspace(0, far, k).astype(np.int64))
+        row([], np.arange(k - 1) * (n // 97), [], [far], [])
+    for k in (2, 63, 64, 65):
+        row(*[[far]] * k)                                   # one entry of k terms
+        row(*[[i % 5, far - 3 * (i % 2)] for i in range(k // 2)])
+    row(*[np.arange(8) * 7 + i for i in range(8)])
+    row(*[np.arange(8) * 7 + i for i in range(8)], [3])     # 65 products
+    row(*[[]] * 64, [5, far])                               # 66 A entries
+    rp = np.zeros(len(rows_b) + 1, np.int32)
+    rp[1:] = np.cumsum([len(r) for r in rows_b])
+    nnz = int(rp[-1])
+    B = syn.CSR(len(rows_b), n, rp, np.concatenate(rows_b).astype(np.int32),
+                (2.0 * syn.uniform01(91, 0, nnz) - 1.0).astype(dtype))
+    ap = np.zeros(len(rows_a) + 1, np.int32)
+    ap[1:] = np.cumsum([len(r) for r in rows_a])
+    A = syn.CSR(len(rows_a), len(rows_b), ap, np.concatenate([np.array(r, np.int32) for r in rows_a]),
+                (2.0 * syn.uniform01(92, 0, int(ap[-1])) - 1.0).astype(dtype))
+    return A, B
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [1000, 1 << 25, (1 << 25) + 1])
+def test_small_row_edges(sm, ctx, oracle_mod, dtype, n):
+    A, B = _small_row_edges(dtype, n)
+    full_check(sm, ctx, A, B, dtype, oracle_mod, False, f"small rows n={n}")
+    ctx.set_option(sm.OPT_FUSED_SIZING, 1)
+    C = ctx.spgemm_fused(sm.to_device(A), sm.to_device(B))
+    check_rows(C.row_ptr.cpu().numpy(), C.col_idx.cpu().numpy(), C.val.cpu().numpy(), oracle_mod.spgemm(A, B), dtype,
+               f"small rows fused n={n}")
