@@ -454,6 +454,13 @@ smash_status launch_num_bin(smash_ctx c, hipStream_t s, const Plan &p, int cnt, 
 // Symbolic light rows: every bin is launched (its size is on the device).
 smash_status run_sym_bins(smash_ctx c, hipStream_t s, const Plan &p)
 {
+    if (p.m <= kFewRows) {
+        const unsigned grid = persistent_grid(c, k_sym_few, 256, 1, p.m);
+        return launch(c, K_SYM_ROWS, s, [&] {
+            k_sym_few<<<grid, 256, 0, s>>>(p.A.row_ptr, p.A.col_idx, p.B.row_ptr, p.B.col_idx, p.sym_perm,
+                                           &c->d_hdr->sym, (int)p.n, p.nnzc, perr(c));
+        });
+    }
     TRY(launch_sym_bin<6>(c, s, p));
     TRY(launch_sym_bin<7>(c, s, p));
     TRY(launch_sym_bin<8>(c, s, p));
@@ -469,6 +476,20 @@ smash_status run_num_bins(smash_ctx c, hipStream_t s, const Plan &p, const V *Av
 {
     const BinHdr &b = p.hdr.num;
     const int *perm = p.num_perm;
+    if (p.m <= kFewRows) {
+        const int items = few_count(b);
+        if (items == 0) return SMASH_OK;
+        return launch(c, K_NUM_ROWS, s, [&] {
+            if (p.row_hash)
+                k_num_few<V, 1><<<items, 256, 0, s>>>(p.A.row_ptr, p.A.col_idx, Aval, p.B.row_ptr, p.B.col_idx, Bval,
+                                                      perm, b, (const long long *)crp, ccol, cval, (int)p.n,
+                                                      c->d_numerr);
+            else
+                k_num_few<V, 0><<<items, 256, 0, s>>>(p.A.row_ptr, p.A.col_idx, Aval, p.B.row_ptr, p.B.col_idx, Bval,
+                                                      perm, b, (const long long *)crp, ccol, cval, (int)p.n,
+                                                      c->d_numerr);
+        });
+    }
 #define NUM_BIN(LT)                                                                                   \
     if (b.count[LT - kMinLogT])                                                                       \
         TRY(launch_num_bin<V, LT>(c, s, p, b.count[LT - kMinLogT], perm + b.offset[LT - kMinLogT], Aval, Bval, crp, \
@@ -485,6 +506,11 @@ smash_status bin_rows(smash_ctx c, hipStream_t s, const Plan &p, const unsigned 
                       const int *wt, BinHdr *dh, int *perm, const int *gsize_of, long long heavy_cap)
 {
     const int m = (int)p.m;
+    if (m <= kFewRows)
+        return launch(c, K_BIN_SCAN, s, [&] {
+            k_bin_few<<<1, kFewThreads, 0, s>>>(m, bin_of, ub, wt, dh, ub ? &c->d_hdr->products : nullptr, perm,
+                                                gsize_of, p.gsz, perr(c), heavy_cap);
+        });
     TRY(launch(c, K_BIN_COUNT, s, [&] {
         k_bin_count<<<p.nblk, 256, 0, s>>>(m, bin_of, ub, wt, p.bcount, ub ? p.bprod : nullptr, wt ? p.bw : nullptr,
                                            perr(c));
@@ -504,6 +530,9 @@ template <typename TIn>
 smash_status scan_counts(smash_ctx c, hipStream_t s, long long n, const TIn *cnt, long long *bsum,
                          long long *out, long long *total)
 {
+    if (n <= kFewRows)
+        return launch(c, K_SCAN_APPLY, s,
+                      [&] { k_scan_few<TIn><<<1, kFewThreads, 0, s>>>((int)n, cnt, total, out); });
     const int nb = (int)blocks_for(std::max<long long>(n, 1), kScanItems);
     TRY(launch(c, K_SCAN_REDUCE, s, [&] { k_scan_reduce<TIn><<<nb, kScanThreads, 0, s>>>(n, cnt, bsum); }));
     TRY(launch(c, K_SCAN_TOP, s, [&] { k_scan_top<<<1, kScanThreads, 0, s>>>(nb, bsum, total); }));

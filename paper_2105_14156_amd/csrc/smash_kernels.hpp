@@ -1441,6 +1441,73 @@ __global__ __launch_bounds__(256) void k_scatter(int m, const unsigned char *__r
     }
 }
 
+// Binning of at most kFewRows rows in one block (k_bin_count, k_bin_scan and
+// k_scatter in one launch): a product with so few rows is bound by the number
+// of launches, 3 to 5 us each.  A wave ranks its rows within each bin by
+// ballots.  wsum is filled for heavy rows only (the one that is read).
+constexpr int kFewRows = 8192;
+constexpr int kFewThreads = 1024;
+
+__global__ __launch_bounds__(kFewThreads) void k_bin_few(int m, const unsigned char *__restrict__ bin_of,
+                                                         const long long *__restrict__ ub, const int *__restrict__ wt,
+                                                         BinHdr *h, unsigned long long *products,
+                                                         int *__restrict__ perm, const int *__restrict__ gsize_of,
+                                                         long long *__restrict__ gsz, int *err, long long heavy_cap)
+{
+    if (stopped(err)) return;
+    constexpr int PER = kFewRows / kFewThreads;
+    __shared__ int s_cnt[kNumBins], s_off[kNumBins + 1];
+    __shared__ unsigned long long s_w, s_prod;
+    if (threadIdx.x < kNumBins) s_cnt[threadIdx.x] = 0;
+    if (threadIdx.x == 0) s_w = s_prod = 0;
+    __syncthreads();
+    int bin[PER], at[PER];
+    unsigned long long prod = 0, w = 0;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int i = q * kFewThreads + threadIdx.x;
+        bin[q] = i < m ? bin_of[i] : -1;
+        at[q] = 0;
+        if (__ballot(bin[q] >= 0) == 0) continue;
+        if (i < m && ub) prod += (unsigned long long)ub[i];
+        if (bin[q] == kBinHeavy && wt) w += (unsigned long long)wt[i];
+#pragma unroll
+        for (int b = 0; b < kNumBins; ++b) {
+            const unsigned long long mask = __ballot(bin[q] == b);
+            if (!mask) continue;
+            int base = 0;
+            if (lane_id() == 0) base = atomicAdd(&s_cnt[b], __popcll(mask));
+            base = __builtin_amdgcn_readfirstlane(base);
+            if (bin[q] == b) at[q] = base + __popcll(mask & ((1ull << lane_id()) - 1));
+        }
+    }
+    prod = wave_sum(prod);
+    w = wave_sum(w);
+    if (lane_id() == 0 && prod) atomicAdd(&s_prod, prod);
+    if (lane_id() == 0 && w) atomicAdd(&s_w, w);
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        int run = 0;
+        for (int b = 0; b < kNumBins; ++b) {
+            h->count[b] = s_cnt[b];
+            h->wsum[b] = b == kBinHeavy ? (long long)s_w : 0;
+            h->offset[b] = s_off[b] = run;
+            run += s_cnt[b];
+        }
+        h->offset[kNumBins] = run;
+        if (ub && products) *products = s_prod;
+        if (err && heavy_cap >= 0 && s_cnt[kBinHeavy] > heavy_cap) atomicOr(err, kErrCapacity);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int i = q * kFewThreads + threadIdx.x, b = bin[q];
+        if (b < 0 || b == kBinEmpty) continue;
+        perm[s_off[b] + at[q]] = i;
+        if (b == kBinHeavy && gsize_of) gsz[at[q]] = 1LL << gtable_log2(gsize_of[i]);
+    }
+}
+
 // ------------------------------------------------------- symbolic, LDS hash
 
 // Tables up to this size hold rows of at most 64 entries, nearly all of which
@@ -1515,6 +1582,68 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_sym_rows(const int *__restr
         const int e0 = active ? Arp[row] : 0, e1 = active ? Arp[row + 1] : 0;
         sym_row<LOGT, WPR>(e0, e1, Acol, Brp, Bcol, ncols, active, gt, s_keys[g], s_en[g], &s_cnt[g], &nnzc[row], err);
         group_sync<WPR>();
+    }
+}
+
+// Rows of all bins in one launch, for products of at most kFewRows rows (six
+// launches, one per bin, cost more than the rows): work item `it` of a grid of
+// 256-thread blocks is a row of the largest tables (one per item, all four
+// waves), or four rows of up to 512 slots (a wave each).  body(bin constant,
+// waves per row constant, first row, rows of the bin, its rows).
+template <typename F>
+__device__ __forceinline__ void few_items(const BinHdr &h, const int *__restrict__ perm, int it, F body)
+{
+    auto bin = [&](auto logt, auto wpr) {
+        constexpr int B = decltype(logt)::value - kMinLogT, RPW = 4 / decltype(wpr)::value;
+        const int items = (h.count[B] + RPW - 1) / RPW;
+        if (it >= 0 && it < items) body(logt, wpr, it * RPW, h.count[B], perm + h.offset[B]);
+        it -= items;
+    };
+    using std::integral_constant;
+    bin(integral_constant<int, 11>(), integral_constant<int, 4>());
+    bin(integral_constant<int, 10>(), integral_constant<int, 4>());
+    bin(integral_constant<int, 9>(), integral_constant<int, 1>());
+    bin(integral_constant<int, 8>(), integral_constant<int, 1>());
+    bin(integral_constant<int, 7>(), integral_constant<int, 1>());
+    bin(integral_constant<int, 6>(), integral_constant<int, 1>());
+}
+
+// Number of its work items.
+__host__ __device__ __forceinline__ int few_count(const BinHdr &h)
+{
+    int n = 0;
+    for (int b = 0; b < kLdsBins; ++b) n += b + kMinLogT >= 10 ? h.count[b] : (h.count[b] + 3) / 4;
+    return n;
+}
+
+template <int LOGT, int WPR>
+struct FewSymLds {
+    int keys[4 / WPR][1 << LOGT];
+    EnumScratch<float, WPR * kWave> en[4 / WPR];
+    int cnt[4 / WPR];
+};
+
+__global__ __launch_bounds__(256) void k_sym_few(const int *__restrict__ Arp, const int *__restrict__ Acol,
+                                                 const int *__restrict__ Brp, const int *__restrict__ Bcol,
+                                                 const int *__restrict__ perm, const BinHdr *h, int ncols,
+                                                 int *__restrict__ nnzc, int *err)
+{
+    if (stopped(err)) return;
+    constexpr size_t BYTES = sizeof(FewSymLds<9, 1>) > sizeof(FewSymLds<11, 4>) ? sizeof(FewSymLds<9, 1>)
+                                                                                : sizeof(FewSymLds<11, 4>);
+    __shared__ __align__(16) unsigned char raw[BYTES];
+    const int total = few_count(*h);
+    for (int it = blockIdx.x; it < total; it += gridDim.x) {
+        few_items(*h, perm, it, [&](auto logt, auto wpr, int r0, int cnt, const int *rows) {
+            constexpr int LOGT = decltype(logt)::value, WPR = decltype(wpr)::value;
+            auto &L = *reinterpret_cast<FewSymLds<LOGT, WPR> *>(raw);
+            const int g = threadIdx.x / kWave / WPR, r = r0 + g;
+            const bool active = r < cnt;
+            const int row = active ? rows[r] : 0;
+            sym_row<LOGT, WPR>(active ? Arp[row] : 0, active ? Arp[row + 1] : 0, Acol, Brp, Bcol, ncols, active,
+                               threadIdx.x - g * WPR * kWave, L.keys[g], L.en[g], &L.cnt[g], &nnzc[row], err);
+        });
+        __syncthreads();
     }
 }
 
@@ -1877,6 +2006,41 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_num_rows(
                                 s_en[g], s_scan[g], Ccol, Cval, ncols, err, &s_maxd[g]);
 }
 
+template <typename V, int LOGT, int WPR>
+struct FewNumLds {
+    double vals[4 / WPR][1 << LOGT];
+    int keys[4 / WPR][1 << LOGT];
+    EnumScratch<V, WPR * kWave> en[4 / WPR];
+    int scan[4 / WPR][WPR + 1];
+    int maxd[4 / WPR];
+};
+
+// Light rows of all bins of a product of few rows (see few_items): block b is
+// work item b.
+template <typename V, int HASH>
+__global__ __launch_bounds__(256) void k_num_few(const int *__restrict__ Arp, const int *__restrict__ Acol,
+                                                 const V *__restrict__ Aval, const int *__restrict__ Brp,
+                                                 const int *__restrict__ Bcol, const V *__restrict__ Bval,
+                                                 const int *__restrict__ perm, BinHdr h,
+                                                 const long long *__restrict__ Crp, int *__restrict__ Ccol,
+                                                 V *__restrict__ Cval, int ncols, int *err)
+{
+    constexpr size_t BYTES = sizeof(FewNumLds<V, 9, 1>) > sizeof(FewNumLds<V, 11, 4>) ? sizeof(FewNumLds<V, 9, 1>)
+                                                                                      : sizeof(FewNumLds<V, 11, 4>);
+    __shared__ __align__(16) unsigned char raw[BYTES];
+    few_items(h, perm, blockIdx.x, [&](auto logt, auto wpr, int r0, int cnt, const int *rows) {
+        constexpr int LOGT = decltype(logt)::value, WPR = decltype(wpr)::value;
+        auto &L = *reinterpret_cast<FewNumLds<V, LOGT, WPR> *>(raw);
+        const int g = threadIdx.x / kWave / WPR, r = r0 + g;
+        const bool active = r < cnt;
+        const int row = active ? rows[r] : 0;
+        const long long rb = active ? Crp[row] : 0;
+        num_row<V, LOGT, WPR, HASH>(active ? Arp[row] : 0, active ? Arp[row + 1] : 0, Acol, Aval, Brp, Bcol, Bval, rb,
+                                    active ? (int)(Crp[row + 1] - rb) : 0, active, threadIdx.x - g * WPR * kWave,
+                                    L.keys[g], L.vals[g], L.en[g], L.scan[g], Ccol, Cval, ncols, err, &L.maxd[g]);
+    });
+}
+
 // ---------------------------------------------------------------- row scan
 
 // out = exclusive prefix of cnt (int or int64 counts) in three passes over
@@ -1944,6 +2108,29 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(long long n, const 
         run += v[t];
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = *total;
+}
+
+// The same for at most kFewRows counts, in one block.
+template <typename TIn>
+__global__ __launch_bounds__(kFewThreads) void k_scan_few(int n, const TIn *__restrict__ cnt,
+                                                          long long *__restrict__ total, long long *__restrict__ out)
+{
+    constexpr int PER = kFewRows / kFewThreads;
+    __shared__ long long s_tmp[kFewThreads / kWave + 1];
+    const int base = threadIdx.x * PER;
+    long long v[PER], sum = 0, tot;
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        v[t] = base + t < n ? (long long)cnt[base + t] : 0;
+        sum += v[t];
+    }
+    long long run = block_excl_scan<long long, kFewThreads>(sum, s_tmp, tot);
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        if (base + t < n) out[base + t] = run;
+        run += v[t];
+    }
+    if (threadIdx.x == 0) out[n] = *total = tot;
 }
 
 // ------------------------------------------------------ heavy rows: chunks
