@@ -455,7 +455,7 @@ smash_status launch_num_bin(smash_ctx c, hipStream_t s, const Plan &p, int cnt, 
 smash_status run_sym_bins(smash_ctx c, hipStream_t s, const Plan &p)
 {
     if (p.m <= kFewRows) {
-        const unsigned grid = persistent_grid(c, k_sym_few, 256, 1, p.m);
+        const unsigned grid = (unsigned)std::min<long long>(p.m, 8LL * c->cus);
         return launch(c, K_SYM_ROWS, s, [&] {
             k_sym_few<<<grid, 256, 0, s>>>(p.A.row_ptr, p.A.col_idx, p.B.row_ptr, p.B.col_idx, p.sym_perm,
                                            &c->d_hdr->sym, (int)p.n, p.nnzc, perr(c));
@@ -635,14 +635,19 @@ smash_status run_fused_bins(smash_ctx c, hipStream_t s, const Plan &p)
     return SMASH_OK;
 }
 
-// Copies the device header (and the numeric error word) to the host and
-// waits: the one synchronisation of a symbolic call.
-smash_status read_hdr(smash_ctx c, hipStream_t s)
+// Waits for the stream: the one synchronisation of a symbolic call.
+smash_status wait_hdr(smash_ctx c, hipStream_t s)
 {
-    HIP_TRY(c, hipMemcpyAsync(c->h_hdr, c->d_hdr, kNumErrOffset + sizeof(int), hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     collect_times(c);
     return SMASH_OK;
+}
+
+// Copies the device header (and the numeric error word) to the host and waits.
+smash_status read_hdr(smash_ctx c, hipStream_t s)
+{
+    HIP_TRY(c, hipMemcpyAsync(c->h_hdr, c->d_hdr, kNumErrOffset + sizeof(int), hipMemcpyDeviceToHost, s));
+    return wait_hdr(c, s);
 }
 
 smash_status device_errors(smash_ctx c, int e)
@@ -881,12 +886,21 @@ smash_status plan_global_waves(smash_ctx c, hipStream_t s, const long long *goff
 // on s; a violation sets `flag` in *err.  With `starts` (a bitmap of
 // nnz / 32 + 1 words of the workspace) every precondition is checked;
 // without it, only what memory safety needs (row pointers, column ranges).
-smash_status validate_csr(smash_ctx c, hipStream_t s, const smash_csr &M, int flag, int *err, unsigned *starts)
+// `cleared`: the bitmap has been cleared already.
+long long starts_words(const smash_csr &M) { return M.rows <= kFewRows ? 0 : (M.nnz + 31) / 32 + 1; }
+
+smash_status validate_csr(smash_ctx c, hipStream_t s, const smash_csr &M, int flag, int *err, unsigned *starts,
+                          bool cleared = false)
 {
     if (M.rows == 0 && M.nnz == 0) return SMASH_OK;
-    const long long words = (M.nnz + 31) / 32 + 1;
+    if (M.rows <= kFewRows)
+        return launch(c, K_VALIDATE, s, [&] {
+            k_validate_few<<<blocks_for(std::max<int64_t>(std::max(M.rows, M.nnz), 1), 256), 256, 0, s>>>(
+                (int)M.rows, (int)M.cols, M.nnz, M.row_ptr, M.col_idx, starts != nullptr, flag, err);
+        });
+    const long long words = starts_words(M);
     TRY(launch(c, K_VALIDATE, s, [&] {
-        if (starts) k_fill_i32<<<blocks_for(words, 256), 256, 0, s>>>(words, (int *)starts, 0);
+        if (starts && !cleared) k_fill_i32<<<blocks_for(words, 256), 256, 0, s>>>(words, (int *)starts, 0);
         k_validate_rows<<<blocks_for(std::max<int64_t>(M.rows, 1), 256), 256, 0, s>>>((int)M.rows, M.nnz, M.row_ptr,
                                                                                       starts, flag, err);
         if (M.nnz > 0)
@@ -983,9 +997,12 @@ smash_status symbolic_impl(smash_ctx c, const smash_csr *A, const smash_csr *B, 
     p.ws_bytes = ws_bytes;
     c->stats.workspace_bytes = (int64_t)p.ws_fixed;
 
-    HIP_TRY(c, hipMemsetAsync(c->d_hdr, 0, sizeof(DevHdr), s));
+    const long long words = c->opt[SMASH_OPT_VALIDATE] ? starts_words(*A) : 0;
+    TRY(launch(c, K_FILL, s, [&] {
+        k_begin<<<blocks_for(std::max<long long>(words, 1), 1024), 256, 0, s>>>(c->d_hdr, words, p.valid_bm);
+    }));
     if (c->opt[SMASH_OPT_VALIDATE]) {
-        TRY(validate_csr(c, s, *A, kErrCsrA, perr(c), p.valid_bm));
+        TRY(validate_csr(c, s, *A, kErrCsrA, perr(c), p.valid_bm, true));
         if (!same_csr(*A, *B)) TRY(validate_csr(c, s, *B, kErrCsrB, perr(c), p.valid_bm));   // A * A: once
     }
     if (m == 0) {
@@ -1061,16 +1078,26 @@ smash_status symbolic_impl(smash_ctx c, const smash_csr *A, const smash_csr *B, 
         }
     }
 
-    // a4: C_row_ptr = exclusive scan of the row counts
-    TRY(scan_counts<int>(c, s, m, p.nnzc, p.bsum, (long long *)C_row_ptr, &c->d_hdr->nnz_c));
-    // numeric plan: bins of the light rows, segments of the heavy rows
-    TRY(launch(c, K_NUM_BINS, s, [&] {
-        k_num_bins<<<blocks_for(m, 256), 256, 0, s>>>((int)m, p.nnzc, p.sym_bin, p.num_bin);
-    }));
-    TRY(bin_rows(c, s, p, p.num_bin, nullptr, p.nnzc, &c->d_hdr->num, p.num_perm, global ? p.nnzc : nullptr, -1));
-    if (global && c->h_hdr->sym.count[kBinHeavy] > 0)
-        TRY(scan_counts<long long>(c, s, c->h_hdr->sym.count[kBinHeavy], p.gsz, p.bsum, p.goff_num,
-                                   (long long *)&c->d_hdr->gneed[1]));
+    // a4: C_row_ptr = exclusive scan of the row counts; numeric plan: bins of
+    // the light rows, segments of the heavy rows
+    const bool few = m <= kFewRows && !global;
+    const bool publish = few && p.hcap == 0;     // no kernel follows: the plan kernel hands the header over
+    if (few) {
+        TRY(launch(c, K_SCAN_APPLY, s, [&] {
+            k_plan_few<<<1, kFewThreads, 0, s>>>((int)m, p.nnzc, p.sym_bin, c->d_hdr, p.num_perm,
+                                                 (long long *)C_row_ptr, publish ? (int *)c->h_hdr : nullptr,
+                                                 (int)(kNumErrOffset / sizeof(int)) + 1);
+        }));
+    } else {
+        TRY(scan_counts<int>(c, s, m, p.nnzc, p.bsum, (long long *)C_row_ptr, &c->d_hdr->nnz_c));
+        TRY(launch(c, K_NUM_BINS, s, [&] {
+            k_num_bins<<<blocks_for(m, 256), 256, 0, s>>>((int)m, p.nnzc, p.sym_bin, p.num_bin);
+        }));
+        TRY(bin_rows(c, s, p, p.num_bin, nullptr, p.nnzc, &c->d_hdr->num, p.num_perm, global ? p.nnzc : nullptr, -1));
+        if (global && c->h_hdr->sym.count[kBinHeavy] > 0)
+            TRY(scan_counts<long long>(c, s, c->h_hdr->sym.count[kBinHeavy], p.gsz, p.bsum, p.goff_num,
+                                       (long long *)&c->d_hdr->gneed[1]));
+    }
     if (!global && p.hcap > 0) {
         const unsigned nhb = blocks_for(p.hcap, 256);
         TRY(launch(c, K_CHUNK_PREFIX, s, [&] {
@@ -1092,7 +1119,8 @@ smash_status symbolic_impl(smash_ctx c, const smash_csr *A, const smash_csr *B, 
                                            (const long long *)C_row_ptr, p.seg_bcount, &c->d_hdr->seg, p.segs, perr(c));
         }));
     }
-    TRY(read_hdr(c, s));
+    if (publish) TRY(wait_hdr(c, s));
+    else TRY(read_hdr(c, s));
     p.hdr = *c->h_hdr;
     const int H = p.hdr.sym.count[kBinHeavy];
     if (p.hdr.error & kErrCapacity) {

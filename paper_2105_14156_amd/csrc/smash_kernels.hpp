@@ -1069,6 +1069,48 @@ __global__ __launch_bounds__(256) void k_validate_cols(int cols, long long nnz, 
     if (__syncthreads_or(bad) && threadIdx.x == 0) atomicOr(err, flag);
 }
 
+// The same for a matrix of at most kFewRows rows in one launch and without the
+// bitmap: an entry not above its predecessor looks for itself among the row
+// pointers (a search of 13 steps, made about once per row).  Without `strict`
+// only what memory safety needs is checked.
+constexpr int kFewRows = 8192;
+
+__global__ __launch_bounds__(256) void k_validate_few(int rows, int cols, long long nnz, const int *__restrict__ rp,
+                                                      const int *__restrict__ ci, int strict, int flag, int *err)
+{
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x;
+    bool bad = t == 0 && (rp[0] != 0 || (long long)rp[rows] != nnz);
+    if (t < rows) {
+        const int a = rp[t], b = rp[t + 1];
+        if (b < a || a < 0 || (long long)b > nnz) bad = true;
+    }
+    if (t < nnz) {
+        const int c = ci[t];
+        if (c < 0 || c >= cols) {
+            bad = true;
+        } else if (strict && t > 0 && c <= ci[t - 1]) {
+            int lo = 0, hi = rows;                       // first row pointer >= t
+            while (lo < hi) {
+                const int mid = (lo + hi) >> 1;
+                if (rp[mid] < t) lo = mid + 1;
+                else hi = mid;
+            }
+            if (rp[lo] != t) bad = true;
+        }
+    }
+    if (__syncthreads_or(bad) && threadIdx.x == 0) atomicOr(err, flag);
+}
+
+// Start of a symbolic call: the header cleared, and the `words` words of the
+// validation bitmap.
+__global__ __launch_bounds__(256) void k_begin(DevHdr *h, long long words, unsigned *__restrict__ starts)
+{
+    static_assert(sizeof(DevHdr) % sizeof(int) == 0, "cleared as ints");
+    const long long t = (long long)blockIdx.x * blockDim.x + threadIdx.x, step = (long long)gridDim.x * blockDim.x;
+    for (long long i = t; i < (long long)(sizeof(DevHdr) / sizeof(int)); i += step) ((int *)h)[i] = 0;
+    for (long long i = t; i < words; i += step) starts[i] = 0u;
+}
+
 // --------------------------------------------------------- analysis & bins
 
 // Feature t (0..5) of the learned predictor for a row with na A entries:
@@ -1313,17 +1355,22 @@ __global__ __launch_bounds__(256) void k_ws_query(int m, int ncols, int lds_row_
     }
 }
 
-// Numeric bin of every row from its exact count (heavy rows stay heavy).
+// Numeric bin of a row from its symbolic bin and exact count: heavy rows stay
+// heavy, rows outside the plan (no products, or completed by the fused pass)
+// stay out.
+__device__ __forceinline__ int num_bin(int sym_bin, int nc)
+{
+    return sym_bin == kBinHeavy ? kBinHeavy : (sym_bin == kBinEmpty || nc == 0 ? kBinEmpty : lds_bin(nc));
+}
+
+// Numeric bin of every row.
 __global__ __launch_bounds__(256) void k_num_bins(int m, const int *__restrict__ nnzc,
                                                   const unsigned char *__restrict__ sym_bin_of,
                                                   unsigned char *__restrict__ bin_out)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= m) return;
-    const int b = sym_bin_of[i];
-    const int nc = nnzc[i];
-    // rows outside the plan (no products, or completed by the fused pass) stay out
-    bin_out[i] = (unsigned char)(b == kBinHeavy ? kBinHeavy : (b == kBinEmpty || nc == 0 ? kBinEmpty : lds_bin(nc)));
+    bin_out[i] = (unsigned char)num_bin(sym_bin_of[i], nnzc[i]);
 }
 
 // Per-block bin histograms (kBinBlockRows rows per block, no global atomics):
@@ -1445,16 +1492,14 @@ __global__ __launch_bounds__(256) void k_scatter(int m, const unsigned char *__r
 // k_scatter in one launch): a product with so few rows is bound by the number
 // of launches, 3 to 5 us each.  A wave ranks its rows within each bin by
 // ballots.  wsum is filled for heavy rows only (the one that is read).
-constexpr int kFewRows = 8192;
 constexpr int kFewThreads = 1024;
 
-__global__ __launch_bounds__(kFewThreads) void k_bin_few(int m, const unsigned char *__restrict__ bin_of,
-                                                         const long long *__restrict__ ub, const int *__restrict__ wt,
-                                                         BinHdr *h, unsigned long long *products,
-                                                         int *__restrict__ perm, const int *__restrict__ gsize_of,
-                                                         long long *__restrict__ gsz, int *err, long long heavy_cap)
+template <typename B>
+__device__ __forceinline__ void bin_few(int m, B bin_at, const long long *__restrict__ ub, const int *__restrict__ wt,
+                                        BinHdr *h, unsigned long long *products, int *__restrict__ perm,
+                                        const int *__restrict__ gsize_of, long long *__restrict__ gsz, int *err,
+                                        long long heavy_cap)
 {
-    if (stopped(err)) return;
     constexpr int PER = kFewRows / kFewThreads;
     __shared__ int s_cnt[kNumBins], s_off[kNumBins + 1];
     __shared__ unsigned long long s_w, s_prod;
@@ -1466,7 +1511,7 @@ __global__ __launch_bounds__(kFewThreads) void k_bin_few(int m, const unsigned c
 #pragma unroll
     for (int q = 0; q < PER; ++q) {
         const int i = q * kFewThreads + threadIdx.x;
-        bin[q] = i < m ? bin_of[i] : -1;
+        bin[q] = i < m ? bin_at(i) : -1;
         at[q] = 0;
         if (__ballot(bin[q] >= 0) == 0) continue;
         if (i < m && ub) prod += (unsigned long long)ub[i];
@@ -1506,6 +1551,16 @@ __global__ __launch_bounds__(kFewThreads) void k_bin_few(int m, const unsigned c
         perm[s_off[b] + at[q]] = i;
         if (b == kBinHeavy && gsize_of) gsz[at[q]] = 1LL << gtable_log2(gsize_of[i]);
     }
+}
+
+__global__ __launch_bounds__(kFewThreads) void k_bin_few(int m, const unsigned char *__restrict__ bin_of,
+                                                         const long long *__restrict__ ub, const int *__restrict__ wt,
+                                                         BinHdr *h, unsigned long long *products,
+                                                         int *__restrict__ perm, const int *__restrict__ gsize_of,
+                                                         long long *__restrict__ gsz, int *err, long long heavy_cap)
+{
+    if (stopped(err)) return;
+    bin_few(m, [&](int i) { return (int)bin_of[i]; }, ub, wt, h, products, perm, gsize_of, gsz, err, heavy_cap);
 }
 
 // ------------------------------------------------------- symbolic, LDS hash
@@ -2112,8 +2167,8 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(long long n, const 
 
 // The same for at most kFewRows counts, in one block.
 template <typename TIn>
-__global__ __launch_bounds__(kFewThreads) void k_scan_few(int n, const TIn *__restrict__ cnt,
-                                                          long long *__restrict__ total, long long *__restrict__ out)
+__device__ __forceinline__ void scan_few(int n, const TIn *__restrict__ cnt, long long *__restrict__ total,
+                                         long long *__restrict__ out)
 {
     constexpr int PER = kFewRows / kFewThreads;
     __shared__ long long s_tmp[kFewThreads / kWave + 1];
@@ -2131,6 +2186,33 @@ __global__ __launch_bounds__(kFewThreads) void k_scan_few(int n, const TIn *__re
         run += v[t];
     }
     if (threadIdx.x == 0) out[n] = *total = tot;
+}
+
+template <typename TIn>
+__global__ __launch_bounds__(kFewThreads) void k_scan_few(int n, const TIn *__restrict__ cnt,
+                                                          long long *__restrict__ total, long long *__restrict__ out)
+{
+    scan_few<TIn>(n, cnt, total, out);
+}
+
+// Row pointers, numeric bins (see k_num_bins) and their binning of at most
+// kFewRows rows in one launch.  With `host` (pinned memory) it is the symbolic
+// pass's last kernel and copies the header's `words` ints there, also when the
+// pass has stopped.
+__global__ __launch_bounds__(kFewThreads) void k_plan_few(int m, const int *__restrict__ nnzc,
+                                                          const unsigned char *__restrict__ sym_bin, DevHdr *h,
+                                                          int *__restrict__ perm, long long *__restrict__ Crp,
+                                                          int *__restrict__ host, int words)
+{
+    if (!stopped(&h->error)) {
+        scan_few<int>(m, nnzc, &h->nnz_c, Crp);
+        bin_few(m, [&](int i) { return num_bin(sym_bin[i], nnzc[i]); }, nullptr, nnzc, &h->num, nullptr, perm, nullptr,
+                nullptr, nullptr, -1);
+    }
+    if (!host) return;
+    __syncthreads();
+    for (int t = threadIdx.x; t < words; t += kFewThreads)
+        host[t] = __hip_atomic_load((const int *)h + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // ------------------------------------------------------ heavy rows: chunks

@@ -529,3 +529,45 @@ def test_small_row_edges(sm, ctx, oracle_mod, dtype, n):
     C = ctx.spgemm_fused(sm.to_device(A), sm.to_device(B))
     check_rows(C.row_ptr.cpu().numpy(), C.col_idx.cpu().numpy(), C.val.cpu().numpy(), oracle_mod.spgemm(A, B), dtype,
                f"small rows fused n={n}")
+
+
+@pytest.mark.parametrize("rows", [1, 1025, 8191, 8192, 8193])
+def test_row_count_split(sm, ctx, oracle_mod, rows):
+    """Products of at most 8192 rows take fewer launches (one-block binning and
+    scan, all light rows in one kernel, validation without a bitmap): the same
+    C on both sides of the limit, with light rows of every table size and heavy
+    ones, and every violation found."""
+    lens = np.array([0, 1, 2, 5, 9, 20, 40, 70])[(np.arange(rows) * 5 + 3) % 8]
+    ptr = np.zeros(rows + 1, np.int32)
+    ptr[1:] = np.cumsum(lens)
+    k = 3000
+    start = (syn.uniform01(3, 0, rows) * (k - 70 * 40)).astype(np.int64)
+    col = np.concatenate([start[i] + 40 * np.arange(n) for i, n in enumerate(lens)]).astype(np.int32)
+    A = syn.CSR(rows, k, ptr, col, 2.0 * syn.uniform01(4, 0, len(col)) - 1.0)
+    for n in (900, 30_000):                              # without and with heavy rows
+        B = syn.uniform_k_per_row(k, n, 16, 5, np.float64)
+        full_check(sm, ctx, A, B, np.float64, oracle_mod, False, f"{rows} rows, {n} columns")
+    assert rows < 8 or ctx.stats()["rows_heavy"] > 0
+
+    def bad(row_ptr=None, col_idx=None):
+        M = sm.to_device(syn.CSR(rows, k, ptr if row_ptr is None else row_ptr, col if col_idx is None else col_idx,
+                                 A.val))
+        with pytest.raises(sm.SmashError, match="INVALID_CSR"):
+            ctx.spgemm(M, sm.to_device(B))
+
+    i = int(np.nonzero(lens >= 2)[0][-1])                # last row with two entries
+    e = int(ptr[i])
+    for at, value in ((e + 1, col[e]), (e + 1, col[e] - 1), (e, -1), (e + 1, k), (len(col) - 1, k)):
+        c = col.copy()
+        c[at] = value
+        bad(col_idx=c)
+    p = ptr.copy()
+    p[0] = 1
+    bad(row_ptr=p)
+    p = ptr.copy()
+    p[-1] += 1
+    bad(row_ptr=p)
+    if rows > 8:
+        p = ptr.copy()
+        p[rows // 2] = ptr[rows // 2 - 1] - 1 if ptr[rows // 2 - 1] else ptr[-1] + 1
+        bad(row_ptr=p)
