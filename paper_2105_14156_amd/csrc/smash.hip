@@ -422,10 +422,29 @@ unsigned persistent_grid(smash_ctx c, K kernel, int threads, int rpw, long long 
     return (unsigned)std::max<long long>(1, std::min<long long>(res, blocks_for(m, rpw)));
 }
 
+// Whether the rows of a bin are merged by a column bitmap (kRankColsPerSlot):
+// tables of 256 slots on (smaller rows mostly merge in registers).
+template <int LOGT>
+bool rank_bin(const Plan &p)
+{
+    return LOGT >= 8 && p.n <= ((int64_t)kRankColsPerSlot << LOGT);
+}
+
 template <int LOGT>
 smash_status launch_sym_bin(smash_ctx c, hipStream_t s, const Plan &p)
 {
     using S = BinShape<LOGT>;
+    if constexpr (LOGT >= 8)
+        if (rank_bin<LOGT>(p)) {
+            auto kern = k_sym_rank_rows<S::WPR, S::RPW>;
+            const size_t lds = S::RPW * rank_sym_lds<S::WPR>((int)p.n);
+            const int res = resident_blocks(c, (const void *)kern, S::THREADS, lds);
+            const unsigned grid = (unsigned)std::max<long long>(1, std::min<long long>(res, blocks_for(p.m, S::RPW)));
+            return launch(c, K_SYM_ROWS, s, [&] {
+                kern<<<grid, S::THREADS, lds, s>>>(p.A.row_ptr, p.A.col_idx, p.B.row_ptr, p.B.col_idx, p.sym_perm,
+                                                   &c->d_hdr->sym, LOGT - kMinLogT, (int)p.n, p.nnzc, perr(c));
+            });
+        }
     auto kern = k_sym_rows<LOGT, S::WPR, S::RPW>;
     const unsigned grid = persistent_grid(c, kern, S::THREADS, S::RPW, p.m);
     return launch(c, K_SYM_ROWS, s, [&] {
@@ -439,6 +458,16 @@ smash_status launch_num_bin(smash_ctx c, hipStream_t s, const Plan &p, int cnt, 
                             const V *Bval, const int64_t *crp, int32_t *ccol, V *cval)
 {
     using S = BinShape<LOGT>;
+    if constexpr (LOGT >= 8)
+        if (rank_bin<LOGT>(p) && !p.row_hash) {
+            constexpr int cap = 1 << (LOGT - 1);
+            const size_t lds = S::RPW * rank_row_lds<V, S::WPR>((int)p.n, cap);
+            return launch(c, K_NUM_ROWS, s, [&] {
+                k_num_rank_rows<V, S::WPR, S::RPW><<<blocks_for(cnt, S::RPW), S::THREADS, lds, s>>>(
+                    p.A.row_ptr, p.A.col_idx, Aval, p.B.row_ptr, p.B.col_idx, Bval, rows, cnt, (const long long *)crp,
+                    ccol, cval, (int)p.n, cap, c->d_numerr);
+            });
+        }
     return launch(c, K_NUM_ROWS, s, [&] {
         if (p.row_hash)
             k_num_rows<V, LOGT, S::WPR, S::RPW, 1><<<blocks_for(cnt, S::RPW), S::THREADS, 0, s>>>(

@@ -487,14 +487,14 @@ __device__ __forceinline__ void group_products(int e0, int e1, int gt, EnumScrat
     }
 }
 
-// ------------------------------------------- product enumeration by 16-pieces
+// ---------------------------------------------- product enumeration by pieces
 //
-// piece_products enumerates the same products in pieces of at most 16 of one
-// B range, a row of 16 lanes per piece, four pieces per wave step.  A piece is
-// located once, by one lane (a binary search over the prefix of the entries'
-// piece counts), and its start, end and A value reach the 16 lanes that load
-// it by a DPP row broadcast: no LDS access and no search per product, and a
-// short range wastes at most 15 lanes.
+// piece_products enumerates the same products in pieces of at most PL = 16 (or
+// 8, for rows of short B ranges) of one B range: 64 / PL pieces per wave step,
+// each loaded by PL lanes.  A piece is located once, by one lane (a binary
+// search over the prefix of the entries' piece counts), and its start, end and
+// A value reach the lanes that load it by DPP row broadcasts: no LDS access
+// and no search per product, and a short range wastes at most PL - 1 lanes.
 constexpr int kPiece = 16;
 constexpr int kDppRowNewBcast = 0x150;   // lane t of each row of 16 to the whole row (gfx90a and later)
 
@@ -527,18 +527,32 @@ __device__ __forceinline__ double row_bcast(double v)
     return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
 }
 
+// The value of x in the lane of this lane's group of PL that located step T's
+// piece.
+template <int PL, int T, typename X>
+__device__ __forceinline__ X piece_bcast(X x)
+{
+    if constexpr (PL == 16) {
+        return row_bcast<T>(x);
+    } else {
+        static_assert(PL == 8, "half a row");
+        const X lo = row_bcast<T>(x), hi = row_bcast<T + 8>(x);
+        return lane_id() & 8 ? hi : lo;
+    }
+}
+
 // Lists one A entry per thread gt < GE (its B range [bs, bs + bl), empty beyond
 // the n entries of the step) in S: the prefix of the piece counts runs within
 // each 64 entries, so no barrier is needed inside.  Every thread of the group
 // calls it; readers of S come after a barrier.
-template <typename V, bool WITH_VAL, int GE>
+template <typename V, bool WITH_VAL, int GE, int PL = kPiece>
 __device__ __forceinline__ void piece_list(int n, int gt, int bs, int bl, V a, PieceScratch<V, GE> &S)
 {
     static_assert(GE % kWave == 0, "entry step");
     if (gt >= GE) return;                                          // whole waves
     int ip = 0;
     if (gt - lane_id() < n) {
-        ip = wave_incl_scan((bl + kPiece - 1) / kPiece);
+        ip = wave_incl_scan((bl + PL - 1) / PL);
         S.incl[gt] = ip;
         S.bs[gt] = bs;
         S.be[gt] = bs + bl;
@@ -558,7 +572,7 @@ __device__ __forceinline__ int piece_count(const PieceScratch<V, GE> &S)
 }
 
 // U wave steps of the located pieces (st, en, al) from step T on, loaded.
-template <typename V, bool WITH_VAL, int U>
+template <typename V, bool WITH_VAL, int U, int PL>
 struct PieceGroup {
     int pos[U], j[U];
     double av[U];
@@ -581,9 +595,9 @@ struct PieceGroup {
     __device__ __forceinline__ void take(int st, int en, V al)
     {
         if constexpr (N < U) {
-            const int q = row_bcast<T + N>(st) + (lane_id() & (kPiece - 1));
-            pos[N] = q < row_bcast<T + N>(en) ? q : -1;
-            if constexpr (WITH_VAL) av[N] = (double)row_bcast<T + N>(al);
+            const int q = piece_bcast<PL, T + N>(st) + (lane_id() & (PL - 1));
+            pos[N] = q < piece_bcast<PL, T + N>(en) ? q : -1;
+            if constexpr (WITH_VAL) av[N] = (double)piece_bcast<PL, T + N>(al);
             else av[N] = 0.0;
             take<T, N + 1>(st, en, al);
         }
@@ -605,16 +619,16 @@ struct PieceGroup {
 // Steps T, T + 1, ... of the located pieces to the sink, U at a time; the
 // loads of the next U are in flight while this U are handed over (`cur` holds
 // step T's).
-template <typename V, bool WITH_VAL, int U, int T, typename Sink>
+template <typename V, bool WITH_VAL, int U, int PL, int T, typename Sink>
 __device__ __forceinline__ void piece_steps(int left, int st, int en, V al, const int *__restrict__ Bcol,
-                                            const V *__restrict__ Bval, PieceGroup<V, WITH_VAL, U> &cur, Sink &sink)
+                                            const V *__restrict__ Bval, PieceGroup<V, WITH_VAL, U, PL> &cur, Sink &sink)
 {
-    if constexpr (T + U < kPiece) {
-        if ((T + U) * 4 < left) {                        // wave-uniform
-            PieceGroup<V, WITH_VAL, U> nxt;
+    if constexpr (T + U < PL) {
+        if ((T + U) * (kWave / PL) < left) {             // wave-uniform
+            PieceGroup<V, WITH_VAL, U, PL> nxt;
             nxt.template load<T + U>(st, en, al, Bcol, Bval);
             cur.emit(sink);
-            piece_steps<V, WITH_VAL, U, T + U>(left, st, en, al, Bcol, Bval, nxt, sink);
+            piece_steps<V, WITH_VAL, U, PL, T + U>(left, st, en, al, Bcol, Bval, nxt, sink);
             return;
         }
     }
@@ -622,15 +636,14 @@ __device__ __forceinline__ void piece_steps(int left, int st, int en, V al, cons
 }
 
 // Locates 64 of the listed pieces (of n entries), [p0, p1) at most: lane l
-// finds piece p0 + (l % 16) * 4 + l / 16, so that row g of the wave holds
-// pieces g, g + 4, ... and step t takes every row's lane t.  Absent pieces are
-// empty (st = en = 0).
-template <typename V, bool WITH_VAL, int GE>
+// finds piece p0 + (l % PL) * (64 / PL) + l / PL, so that step t takes lane t of
+// every PL lanes.  Absent pieces are empty (st = en = 0).
+template <typename V, bool WITH_VAL, int GE, int PL = kPiece>
 __device__ __forceinline__ void piece_locate(int p0, int p1, int n, const PieceScratch<V, GE> &S, int &st, int &en,
                                              V &al)
 {
     const int lane = lane_id();
-    int pc = p0 + (lane & 15) * 4 + (lane >> 4);
+    int pc = p0 + (lane & (PL - 1)) * (kWave / PL) + lane / PL;
     st = en = 0;
     al = V(0);
     if (pc < p1) {
@@ -654,35 +667,36 @@ __device__ __forceinline__ void piece_locate(int p0, int p1, int n, const PieceS
         }
         const int ex = src ? incl[src - 1] : 0;
         src += g;
-        st = S.bs[src] + (pc - ex) * kPiece;
+        st = S.bs[src] + (pc - ex) * PL;
         en = S.be[src];
         if constexpr (WITH_VAL) al = S.a[src];
     }
 }
 
 // Pieces of each wave when the waves of a group share P pieces in equal
-// contiguous parts (whole steps of four).
-template <int WG>
+// contiguous parts (whole steps).
+template <int WG, int PL = kPiece>
 __device__ __forceinline__ int piece_share(int P)
 {
-    return ((P + WG - 1) / WG + 3) & ~3;
+    constexpr int STEP = kWave / PL;
+    return ((P + WG - 1) / WG + STEP - 1) & ~(STEP - 1);
 }
 
 // Hands every product of the P pieces listed in S (of n entries) to the sink
 // (sink(j[U], p[U], ok[U]) or, without values, sink(j[U], ok[U])).
-template <typename V, bool WITH_VAL, int GE, int G, int U, typename Sink>
+template <typename V, bool WITH_VAL, int GE, int G, int U, int PL, typename Sink>
 __device__ __forceinline__ void piece_run(int P, int n, int gt, const PieceScratch<V, GE> &S,
                                           const int *__restrict__ Bcol, const V *__restrict__ Bval, Sink &sink)
 {
-    const int wg = __builtin_amdgcn_readfirstlane(gt / kWave), per = piece_share<G / kWave>(P);
+    const int wg = __builtin_amdgcn_readfirstlane(gt / kWave), per = piece_share<G / kWave, PL>(P);
     const int p1 = (wg + 1) * per < P ? (wg + 1) * per : P;
     for (int p0 = wg * per; p0 < p1; p0 += kWave) {
         int st, en;
         V al;
-        piece_locate<V, WITH_VAL, GE>(p0, p1, n, S, st, en, al);
-        PieceGroup<V, WITH_VAL, U> first;
+        piece_locate<V, WITH_VAL, GE, PL>(p0, p1, n, S, st, en, al);
+        PieceGroup<V, WITH_VAL, U, PL> first;
         first.template load<0>(st, en, al, Bcol, Bval);
-        piece_steps<V, WITH_VAL, U, 0>(p1 - p0, st, en, al, Bcol, Bval, first, sink);
+        piece_steps<V, WITH_VAL, U, PL, 0>(p1 - p0, st, en, al, Bcol, Bval, first, sink);
     }
 }
 
@@ -693,21 +707,22 @@ __device__ __forceinline__ void piece_run(int P, int n, int gt, const PieceScrat
 // is run, so that a hub row's steps do not each wait for two dependent
 // gathers.  Every thread of the group of G calls it; S is free again when it
 // returns.  AHEAD = false leaves that out, where registers are short.
-template <typename V, bool WITH_VAL, int GE, int G, int U, bool AHEAD = true, typename Sink>
+template <typename V, bool WITH_VAL, int GE, int G, int U, bool AHEAD = true, int PL = kPiece, typename Sink>
 __device__ __forceinline__ void piece_products(int e0, int e1, int gt, PieceScratch<V, GE> &S,
                                                const int *__restrict__ Acol, const V *__restrict__ Aval,
                                                const int *__restrict__ split, long long per, int d,
                                                const int *__restrict__ Bcol, const V *__restrict__ Bval, Sink &sink)
 {
     constexpr int WG = G / kWave;
+    const unsigned len = (unsigned)(e1 - e0);
     long long k = -1;
     V a = V(0), a1 = V(0);
     int bs = 0, be = 0;
-    auto column = [&](int e, V &val) {
+    auto column = [&](unsigned r, V &val) {              // entry e0 + r
         k = -1;
-        if (gt < GE && e < e1) {
-            k = Acol[e] * per;
-            if constexpr (WITH_VAL) val = Aval[e];
+        if (gt < GE && r < len) {
+            k = Acol[e0 + (int)r] * per;
+            if constexpr (WITH_VAL) val = Aval[e0 + (int)r];
         }
     };
     auto range = [&]() {
@@ -717,23 +732,23 @@ __device__ __forceinline__ void piece_products(int e0, int e1, int gt, PieceScra
             be = split[k + d];
         }
     };
-    column(e0 + gt, a);
+    column(gt, a);
     range();
-    if constexpr (AHEAD) column(e0 + GE + gt, a1);
-    for (int base = e0; base < e1; base += GE) {
-        const int n = e1 - base < GE ? e1 - base : GE;
-        piece_list<V, WITH_VAL, GE>(n, gt, bs, be - bs, a, S);
+    if constexpr (AHEAD) column(GE + gt, a1);
+    for (unsigned base = 0; base < len; base += GE) {
+        const int n = len - base < GE ? (int)(len - base) : GE;
+        piece_list<V, WITH_VAL, GE, PL>(n, gt, bs, be - bs, a, S);
         group_sync<WG>();
         if constexpr (AHEAD) {
-            if (base + GE < e1) {
+            if (base + GE < len) {
                 range();
                 a = a1;
                 column(base + 2 * GE + gt, a1);
             }
         }
-        piece_run<V, WITH_VAL, GE, G, U>(piece_count(S), n, gt, S, Bcol, Bval, sink);
+        piece_run<V, WITH_VAL, GE, G, U, PL>(piece_count(S), n, gt, S, Bcol, Bval, sink);
         if constexpr (!AHEAD) {
-            if (base + GE < e1) {
+            if (base + GE < len) {
                 column(base + GE + gt, a);
                 range();
             }
@@ -742,15 +757,15 @@ __device__ __forceinline__ void piece_products(int e0, int e1, int gt, PieceScra
     }
 }
 
-// f(integral_constant<int, T>) for T = 0 .. N - 1 while 4 T < left
+// f(integral_constant<int, T>) for T = 0 .. N - 1 while pieces are left
 // (wave-uniform): the steps of a wave with `left` located pieces.
-template <int N, typename F, int T = 0>
+template <int N, int PL = kPiece, typename F, int T = 0>
 __device__ __forceinline__ void piece_each(int left, F &f)
 {
     if constexpr (T < N) {
-        if (T * 4 >= left) return;
+        if (T * (kWave / PL) >= left) return;
         f(std::integral_constant<int, T>());
-        piece_each<N, F, T + 1>(left, f);
+        piece_each<N, PL, F, T + 1>(left, f);
     }
 }
 
@@ -1561,6 +1576,246 @@ __global__ __launch_bounds__(kFewThreads) void k_bin_few(int m, const unsigned c
 {
     if (stopped(err)) return;
     bin_few(m, [&](int i) { return (int)bin_of[i]; }, ub, wt, h, products, perm, gsize_of, gsz, err, heavy_cap);
+}
+
+// ------------------------------------------ light rows by a column bitmap
+//
+// Where B is at most kRankColsPerSlot times as wide as the row's hash table
+// would be long, a light row needs no table: its columns are marked in an LDS
+// bitmap over all of B's columns, the bitmap's prefix counts rank every product,
+// and the products are added at their ranks (as in the ranked segments of
+// heavy rows).  The hashed form clears and reads back a table of twice the
+// entries, probes it, and orders what it holds by the same bitmap; and its LDS
+// is 12 bytes a slot whatever B's width.  Bound by instruction issue and the
+// latency of the gathers.  RMAT scale 21 times a 4096-column matrix, FP32, rows
+// of 65 to 1024 entries: numeric 867 -> 554 us, symbolic 470 -> 225 (pieces of
+// 16 products instead of 8: 689 and 225).  A wider B costs a longer bitmap per
+// row; at the limit it is two words a slot, as the hashed form's ordering.
+constexpr int kRankColsPerSlot = 64;
+constexpr int kRankPiece = 8;
+constexpr int kRankMaxCols = kRankColsPerSlot << kMaxLogT;      // 2^17: 16-bit columns and one bit more
+
+__host__ __device__ __forceinline__ int rank_words(int ncols) { return ((ncols + 31) / 32 + 7) & ~7; }
+
+// LDS of one group of WPR waves (a multiple of 16): bitmap, prefix counts,
+// sums and columns of cap entries, entry list, scan scratch.
+template <typename V, int WPR>
+__host__ __device__ __forceinline__ size_t rank_row_lds(int ncols, int cap)
+{
+    return (((size_t)rank_words(ncols) * 6 + (size_t)cap * 10 + sizeof(PieceScratch<V, WPR * kWave>) +
+             WPR * sizeof(int)) + 15) & ~(size_t)15;
+}
+
+template <int WPR>
+__host__ __device__ __forceinline__ size_t rank_sym_lds(int ncols)
+{
+    return (((size_t)rank_words(ncols) * 4 + sizeof(PieceScratch<float, WPR * kWave>) + sizeof(int)) + 15) & ~(size_t)15;
+}
+
+// Symbolic count of one light row by a group of WPR waves, stored to *out.
+// raw: rank_sym_lds bytes.  B is at most ncols wide.
+template <int WPR>
+__device__ __forceinline__ void rank_sym_row(int e0, int e1, const int *__restrict__ Acol,
+                                             const int *__restrict__ Brp, const int *__restrict__ Bcol, int ncols,
+                                             int gt, unsigned char *raw, int *out)
+{
+    constexpr int G = WPR * kWave;
+    const int W = rank_words(ncols);
+    unsigned *bm = reinterpret_cast<unsigned *>(raw);
+    auto &S = *reinterpret_cast<PieceScratch<float, G> *>(bm + W);
+    int *cnt = reinterpret_cast<int *>(&S + 1);
+    for (int t = gt * 4; t < W; t += 4 * G) *(uint4 *)&bm[t] = make_uint4(0, 0, 0, 0);
+    if (gt == 0) *cnt = 0;                                  // the products' first barrier follows
+    auto mark = [&](const auto &j, const auto &ok) {
+        constexpr int N = sizeof(j) / sizeof(j[0]);
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (ok[u]) atomicOr(&bm[j[u] >> 5], 1u << (j[u] & 31));
+    };
+    piece_products<float, false, G, G, 4, true, kRankPiece>(e0, e1, gt, S, Acol, (const float *)nullptr, Brp, 1, 1,
+                                                            Bcol, (const float *)nullptr, mark);
+    int pc = 0;
+    for (int t = gt * 4; t < W; t += 4 * G) {
+        const uint4 v = *(const uint4 *)&bm[t];
+        pc += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+    pc = wave_sum(pc);
+    if constexpr (WPR > 1) {
+        if (lane_id() == 0 && pc) atomicAdd(cnt, pc);
+        __syncthreads();
+        pc = *cnt;
+        __syncthreads();
+    }
+    if (gt == 0) *out = pc;
+}
+
+// Numeric pass of one row by a group of WPR waves: its products merged and
+// written in column order at C's offset rb (nc entries expected), cap entries
+// at a time (rows of more entries repeat the second pass).  raw: rank_row_lds
+// bytes for lds_cols >= ncols columns.  Products stay in registers between the
+// passes where the row's A entries fit one list and its pieces one locating.
+template <typename V, int WPR>
+__device__ __forceinline__ void rank_num_row(int e0, int e1, const int *__restrict__ Acol, const V *__restrict__ Aval,
+                                             const int *__restrict__ Brp, const int *__restrict__ Bcol,
+                                             const V *__restrict__ Bval, long long rb, int nc, int ncols, int lds_cols,
+                                             int cap, int gt, unsigned char *raw, int *__restrict__ Ccol,
+                                             V *__restrict__ Cval, int *err)
+{
+    constexpr int G = WPR * kWave, PL = kRankPiece;
+    const int lane = lane_id(), wg = __builtin_amdgcn_readfirstlane(gt / kWave);
+    const int W = rank_words(ncols), WL = rank_words(lds_cols);
+    double *vals = reinterpret_cast<double *>(raw);
+    unsigned *bm = reinterpret_cast<unsigned *>(vals + cap);
+    unsigned short *pref = reinterpret_cast<unsigned short *>(bm + WL);
+    unsigned short *cols = pref + WL;
+    auto &S = *reinterpret_cast<PieceScratch<V, G> *>(cols + cap);     // cap: a multiple of 32
+    int *scan = reinterpret_cast<int *>(&S + 1);
+    for (int t = gt * 4; t < W; t += 4 * G) *(uint4 *)&bm[t] = make_uint4(0, 0, 0, 0);
+    for (int t = gt; t < (nc < cap ? nc : cap); t += G) vals[t] = 0.0;
+    int hc[PL], left = 0;
+    V hv[PL], al = V(0);
+    bool hok[PL], held = false;
+    // every product of the row, 64 pieces of a wave at a time, through use(step);
+    // the last ones stay in hc, hv, hok and al
+    auto pass = [&](auto &use) {
+        for (unsigned base = 0, len = (unsigned)(e1 - e0); base < len; base += G) {
+            const int n = len - base < G ? (int)(len - base) : G;
+            int bs = 0, bl = 0;
+            V a = V(0);
+            if (gt < n) {
+                const int k = Acol[e0 + (int)base + gt];
+                a = Aval[e0 + (int)base + gt];
+                bs = Brp[k];
+                bl = Brp[k + 1] - bs;
+            }
+            piece_list<V, true, G, PL>(n, gt, bs, bl, a, S);
+            group_sync<WPR>();
+            const int P = piece_count(S), share = piece_share<WPR, PL>(P);
+            const int p1 = (wg + 1) * share < P ? (wg + 1) * share : P;
+            held = len <= G && share <= kWave;
+            for (int p0 = wg * share; p0 < p1; p0 += kWave) {
+                int st, en;
+                piece_locate<V, true, G, PL>(p0, p1, n, S, st, en, al);
+                left = p1 - p0;
+                auto load = [&](auto t) {
+                    constexpr int T = decltype(t)::value;
+                    const int q = piece_bcast<PL, T>(st) + (lane & (PL - 1));
+                    hok[T] = q < piece_bcast<PL, T>(en);
+                    const int at = hok[T] ? q : 0;
+                    hc[T] = Bcol[at];
+                    hv[T] = Bval[at];
+                };
+                piece_each<PL, PL>(left, load);
+                piece_each<PL, PL>(left, use);
+            }
+            group_sync<WPR>();
+        }
+    };
+    auto mark = [&](auto t) {
+        constexpr int T = decltype(t)::value;
+        if (hok[T]) atomicOr(&bm[hc[T] >> 5], 1u << (hc[T] & 31));
+    };
+    pass(mark);
+    // prefix counts: every thread the same number of consecutive 4-word groups
+    const int q4 = (W / 4 + G - 1) / G;
+    const int w0 = gt * q4 * 4, w1 = w0 + q4 * 4 < W ? w0 + q4 * 4 : W;
+    int pc = 0;
+    for (int w = w0; w < w1; w += 4) {
+        const uint4 v = *(const uint4 *)&bm[w];
+        pc += __popc(v.x) + __popc(v.y) + __popc(v.z) + __popc(v.w);
+    }
+    const int inc = wave_incl_scan(pc);
+    int run = 0, total = 0;
+    if constexpr (WPR > 1) {
+        if (lane == kWave - 1) scan[wg] = inc;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WPR; ++w) {
+            const int t = scan[w];
+            if (w < wg) run += t;
+            total += t;
+        }
+    } else {
+        total = __builtin_amdgcn_readlane(inc, kWave - 1);
+    }
+    unsigned at = (unsigned)(run + inc - pc);
+    for (int w = w0; w < w1; w += 4) {
+        const uint4 v = *(const uint4 *)&bm[w];
+        const unsigned a1 = at + __popc(v.x), a2 = a1 + __popc(v.y), a3 = a2 + __popc(v.z);
+        *(uint2 *)&pref[w] = make_uint2(at | a1 << 16, a2 | a3 << 16);
+        at = a3 + __popc(v.w);
+    }
+    group_sync<WPR>();
+    if (gt == 0 && total != nc) atomicOr(err, kErrCount);
+    const int cnt = total < nc ? total : nc;
+    // entries from `half` on lie in columns of 65536 and more
+    const int half = W > 2048 ? pref[2048] : cnt;
+    for (int r0 = 0; r0 < cnt; r0 += cap) {
+        const int n = cnt - r0 < cap ? cnt - r0 : cap;
+        if (r0 > 0) {
+            for (int t = gt; t < n; t += G) vals[t] = 0.0;
+            group_sync<WPR>();
+        }
+        auto put = [&](auto t) {
+            constexpr int T = decltype(t)::value;
+            const double p = (double)piece_bcast<PL, T>(al) * (double)hv[T];
+            if (!hok[T]) return;
+            const int j = hc[T];
+            const unsigned r = pref[j >> 5] + __popc(bm[j >> 5] & ((1u << (j & 31)) - 1u)) - r0;
+            if (r < (unsigned)n) {
+                atomicAdd(&vals[r], p);
+                cols[r] = (unsigned short)j;
+            }
+        };
+        if (held) piece_each<PL, PL>(left, put);
+        else pass(put);
+        group_sync<WPR>();
+        for (int t = gt; t < n; t += G) {
+            store_c(&Ccol[rb + r0 + t], (int)cols[t] + (r0 + t >= half ? 65536 : 0));
+            store_c(&Cval[rb + r0 + t], (V)vals[t]);
+        }
+        if (r0 + cap < cnt) group_sync<WPR>();
+    }
+}
+
+// Light rows of one bin (see k_sym_rows and k_num_rows) by a column bitmap;
+// dynamic LDS: RPW times the group's.
+template <int WPR, int RPW>
+__global__ __launch_bounds__(kWave *WPR *RPW) void k_sym_rank_rows(
+    const int *__restrict__ Arp, const int *__restrict__ Acol, const int *__restrict__ Brp,
+    const int *__restrict__ Bcol, const int *__restrict__ perm, const BinHdr *h, int bin, int ncols,
+    int *__restrict__ nnzc, const int *err)
+{
+    static_assert(RPW == 1 || WPR == 1, "multi-row blocks use one wave per row");
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    if (stopped(err)) return;
+    const int g = threadIdx.x / kWave / WPR, gt = threadIdx.x - g * WPR * kWave;
+    unsigned char *raw = s_raw + g * rank_sym_lds<WPR>(ncols);
+    const int nrows = h->count[bin];
+    const int *rows = perm + h->offset[bin];
+    for (int r = blockIdx.x * RPW + g; r < nrows; r += gridDim.x * RPW) {
+        const int row = rows[r];
+        rank_sym_row<WPR>(Arp[row], Arp[row + 1], Acol, Brp, Bcol, ncols, gt, raw, &nnzc[row]);
+        group_sync<WPR>();
+    }
+}
+
+template <typename V, int WPR, int RPW>
+__global__ __launch_bounds__(kWave *WPR *RPW) void k_num_rank_rows(
+    const int *__restrict__ Arp, const int *__restrict__ Acol, const V *__restrict__ Aval,
+    const int *__restrict__ Brp, const int *__restrict__ Bcol, const V *__restrict__ Bval,
+    const int *__restrict__ rows, int nrows, const long long *__restrict__ Crp, int *__restrict__ Ccol,
+    V *__restrict__ Cval, int ncols, int cap, int *err)
+{
+    static_assert(RPW == 1 || WPR == 1, "multi-row blocks use one wave per row");
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    const int g = threadIdx.x / kWave / WPR, gt = threadIdx.x - g * WPR * kWave;
+    const int r = blockIdx.x * RPW + g;
+    if (r >= nrows) return;                                 // whole groups
+    const int row = rows[r];
+    const long long rb = Crp[row];
+    rank_num_row<V, WPR>(Arp[row], Arp[row + 1], Acol, Aval, Brp, Bcol, Bval, rb, (int)(Crp[row + 1] - rb), ncols,
+                         ncols, cap, gt, s_raw + g * rank_row_lds<V, WPR>(ncols, cap), Ccol, Cval, err);
 }
 
 // ------------------------------------------------------- symbolic, LDS hash

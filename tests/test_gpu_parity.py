@@ -571,3 +571,44 @@ def test_row_count_split(sm, ctx, oracle_mod, rows):
         p = ptr.copy()
         p[rows // 2] = ptr[rows // 2 - 1] - 1 if ptr[rows // 2 - 1] else ptr[-1] + 1
         bad(row_ptr=p)
+
+
+def _rank_row_edges(dtype, n):
+    """Light rows of 65 to 1024 entries (the tables of 256 to 2048 slots) at the
+    edges of their capacities, from two B rows, from many short ones (more A
+    entries than one list) and with repeated columns (more pieces than one wave
+    locates), columns up to the last."""
+    rows_b, rows_a = [], []
+
+    def row(cols):
+        rows_a.append(list(range(len(rows_b), len(rows_b) + len(cols))))
+        rows_b.extend(np.unique(np.asarray(c, np.int64)) for c in cols)
+
+    for count in (65, 127, 128, 129, 255, 256, 257, 511, 512, 513, 1023, 1024):
+        c = np.linspace(0, n - 1, count).astype(np.int64)
+        row([c[::2], c[1::2]])
+        row([c[i::90] for i in range(90)] if count > 90 else [c[i::65] for i in range(65)])
+        row([c] * max(1, 1024 // count))
+        row([np.append(c[i::7], c[i % count]) for i in range(7)])
+    row([[0, 65535 % n, 65536 % n, n - 1], np.arange(100) * (n // 101)])
+    rp = np.zeros(len(rows_b) + 1, np.int32)
+    rp[1:] = np.cumsum([len(r) for r in rows_b])
+    nnz = int(rp[-1])
+    B = syn.CSR(len(rows_b), n, rp, np.concatenate(rows_b).astype(np.int32),
+                (2.0 * syn.uniform01(101, 0, nnz) - 1.0).astype(dtype))
+    rows_a = rows_a * 200                                # more than 8192 rows
+    ap = np.zeros(len(rows_a) + 1, np.int32)
+    ap[1:] = np.cumsum([len(r) for r in rows_a])
+    A = syn.CSR(len(rows_a), len(rows_b), ap, np.concatenate([np.array(r, np.int32) for r in rows_a]),
+                (2.0 * syn.uniform01(102, 0, int(ap[-1])) - 1.0).astype(dtype))
+    return A, B
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [1100, 16384, 16385, 65536, 65537, 131072, 131073])
+def test_rank_row_edges(sm, ctx, oracle_mod, dtype, n):
+    """Light rows merged by a column bitmap and, where B is wider than 64 slots
+    of their table, by hashing, at both sides of every limit."""
+    A, B = _rank_row_edges(dtype, n)
+    full_check(sm, ctx, A, B, dtype, oracle_mod, False, f"rank rows n={n}")
+    assert A.rows > 8192 and ctx.stats()["rows_lds"] == A.rows, ctx.stats()
