@@ -1607,6 +1607,9 @@ struct smash_batch_plan_s {
     long long gcap = 0;                  // its slots
     long long cap_total = 0;             // sum of the row bounds (pool capacity)
     int wide_words = 1;                  // LDS bitmap words of the widest problem up to kWideMaxCols
+    int max_cols = 1;                    // columns of the widest problem
+    int rank_cols = 0;                   // and of the widest up to kRankMaxCols
+    bool any_window = false;             // a problem of more than kRankMaxCols, at most kWideMaxCols columns
     bool any_global = false;             // a problem wider than kWideMaxCols (global tables)
     // caller-owned output pool
     long long *crp = nullptr;
@@ -1634,9 +1637,10 @@ struct BShape {
     static constexpr int THREADS = kWave * WPR * RPW;
 };
 
-unsigned bgrid(const BPlan &p, long long items)
+// (`small`: how many times smaller than the usual 256 threads its blocks are)
+unsigned bgrid(const BPlan &p, long long items, int small = 1)
 {
-    const long long g = (long long)p.cfg.blocks_per_cu * p.ncu;
+    const long long g = (long long)p.cfg.blocks_per_cu * p.ncu * small;
     return (unsigned)std::max<long long>(1, std::min<long long>(g, items));
 }
 
@@ -1668,9 +1672,24 @@ void batch_analyze(const BPlan &p, hipStream_t s)
                                                             p.sym_bin, p.gsz);
 }
 
+// Whether a bin's rows are merged by a column bitmap (kBatchRankCols).
+template <int LT>
+bool batch_rank_bin(const BPlan &p)
+{
+    return LT >= 8 && p.max_cols <= std::min<long long>((long long)kBatchRankCols << LT, kRankMaxCols);
+}
+
 template <int LT, int WIDE>
 void bsym_bin(const BPlan &p, hipStream_t s)
 {
+    if constexpr (LT >= 8)
+        if (batch_rank_bin<LT>(p)) {
+            using S = BinShape<LT>;
+            k_bsym_rank_rows<S::WPR, S::RPW>
+                <<<bgrid(p, blocks_for(p.M, S::RPW), 256 / S::THREADS), S::THREADS, S::RPW * rank_sym_lds<S::WPR>(p.max_cols), s>>>(
+                    p.d_desc, p.rd, &p.d_hdr->sym, LT - kMinLogT, p.max_cols, p.nnzc);
+            return;
+        }
     using S = BShape<LT, WIDE>;
     k_bsym_rows<LT, S::WPR, S::RPW><<<bgrid(p, blocks_for(p.M, S::RPW)), S::THREADS, 0, s>>>(
         p.d_desc, p.rd, &p.d_hdr->sym, LT - kMinLogT, p.nnzc, &p.d_hdr->error);
@@ -1679,6 +1698,16 @@ void bsym_bin(const BPlan &p, hipStream_t s)
 template <typename V, int LT, int WIDE>
 void bnum_bin(const BPlan &p, hipStream_t s)
 {
+    if constexpr (LT >= 8)
+        if (batch_rank_bin<LT>(p) && !p.cfg.row_hash) {
+            using S = BinShape<LT>;
+            constexpr int cap = 1 << (LT - 1);
+            k_bnum_rank_rows<V, S::WPR, S::RPW>
+                <<<bgrid(p, blocks_for(p.M, S::RPW), 256 / S::THREADS), S::THREADS, S::RPW * rank_row_lds<V, S::WPR>(p.max_cols, cap), s>>>(
+                    p.d_desc, p.rd, p.d_hdr, LT - kMinLogT, p.max_cols, cap, p.ccap, p.ccol, (V *)p.cval,
+                    &p.d_hdr->error);
+            return;
+        }
     using S = BShape<LT, WIDE>;
     const unsigned grid = bgrid(p, blocks_for(p.M, S::RPW));
     if (p.cfg.row_hash)
@@ -1716,9 +1745,14 @@ void batch_numeric(const BPlan &p, hipStream_t s)
 {
     if (p.cfg.wide_groups) bnum_bins<V, 1>(p, s);
     else bnum_bins<V, 0>(p, s);
-    k_bnum_wide<V><<<bgrid(p, p.M), kWideThreads, kWideWin * sizeof(double), s>>>(
-        p.d_desc, p.prob, p.d_hdr, p.num_perm, p.ccap, p.crp, p.ccol, (V *)p.cval, &p.d_hdr->error,
-        &p.d_hdr->wide_queue);
+    if (p.rank_cols > 0)
+        k_bnum_wide_rank<V><<<bgrid(p, p.M), kWideRankThreads, rank_row_lds<V, kWideWaves>(p.rank_cols, kWideCap), s>>>(
+            p.d_desc, p.prob, p.d_hdr, p.num_perm, p.ccap, p.crp, p.rank_cols, p.ccol, (V *)p.cval, &p.d_hdr->error,
+            &p.d_hdr->rank_queue);
+    if (p.any_window)
+        k_bnum_wide<V><<<bgrid(p, p.M), kWideThreads, kWideWin * sizeof(double), s>>>(
+            p.d_desc, p.prob, p.d_hdr, p.num_perm, p.ccap, p.crp, p.ccol, (V *)p.cval, &p.d_hdr->error,
+            &p.d_hdr->wide_queue);
     if (p.any_global)
         k_bnum_global<V><<<bgrid(p, p.M), kGlobalThreads, global_rank_lds(kGlobalRankBits), s>>>(
         p.d_desc, p.prob, p.d_hdr, p.num_perm, p.goff, p.gcap, p.pool, p.ccap, p.crp, p.ccol,
@@ -1840,6 +1874,9 @@ smash_status smash_batch_plan_create(smash_ctx c, smash_dtype dtype, int32_t cou
     }
     p->M = p->row0[count];
     for (int q = 0; q < count; ++q) {
+        p->max_cols = std::max(p->max_cols, (int)B[q].cols);
+        if (B[q].cols <= kRankMaxCols) p->rank_cols = std::max(p->rank_cols, (int)B[q].cols);
+        else if (B[q].cols <= kWideMaxCols) p->any_window = true;
         if (B[q].cols <= kWideMaxCols) p->wide_words = std::max(p->wide_words, (int)((B[q].cols + 31) / 32));
         else p->any_global = true;
     }
@@ -1869,7 +1906,11 @@ smash_status smash_batch_plan_create(smash_ctx c, smash_dtype dtype, int32_t cou
     if (!p->ws) return bail(fail(c, SMASH_ERR_OUT_OF_MEMORY, "allocation callback returned NULL (workspace)"));
     if (hipHostMalloc((void **)&p->h_hdr, sizeof(BatchHdr), hipHostMallocDefault) != hipSuccess)
         return bail(fail(c, SMASH_ERR_HIP, "pinned header"));
-    if (hipFuncSetAttribute((const void *)k_bsym_wide, hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute((const void *)k_bnum_wide_rank<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)rank_row_lds<float, kWideWaves>(kRankMaxCols, kWideCap)) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_bnum_wide_rank<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)rank_row_lds<double, kWideWaves>(kRankMaxCols, kWideCap)) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_bsym_wide, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)(p->wide_words * sizeof(unsigned))) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bnum_global<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)global_rank_lds(kGlobalRankBits)) != hipSuccess ||

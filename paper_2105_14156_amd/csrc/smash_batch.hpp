@@ -35,6 +35,7 @@ struct BatchHdr {
     long long nnz_c;            // total entries of all C_p
     long long gneed;            // global table slots of the heavy rows
     int error;
+    int rank_queue;             // next heavy row of the bitmap numeric kernel
     int wide_queue;             // next heavy row of the windowed numeric kernel
 };
 
@@ -252,6 +253,66 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_bnum_rows(const BatchDesc *
     }
 }
 
+// The LDS bins from 256 slots on by a column bitmap (rank_sym_row and
+// rank_num_row), in batches whose problems are at most kBatchRankCols columns
+// per slot wide; lds_cols: the widest.  Dynamic LDS: RPW times the group's.  The
+// limit is twice the single product's: a wave still clears and counts at most
+// four words a slot, and most rows of a mixed batch belong to its widest
+// problems.  Batch of 512: these rows take 1.84 ms numeric and 0.94 symbolic,
+// hashed 3.08 and 1.17; with a limit of 64 (the 256-slot rows hashed) 2.11 and
+// 0.94.
+constexpr int kBatchRankCols = 128;
+
+template <int WPR, int RPW>
+__global__ __launch_bounds__(kWave *WPR *RPW) void k_bsym_rank_rows(const BatchDesc *__restrict__ desc,
+                                                                    const RowDesc *__restrict__ rd, const BinHdr *h,
+                                                                    int bin, int lds_cols, int *__restrict__ nnzc)
+{
+    static_assert(RPW == 1 || WPR == 1, "multi-row blocks use one wave per row");
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    const int g = threadIdx.x / kWave / WPR, gt = threadIdx.x - g * WPR * kWave;
+    unsigned char *raw = s_raw + g * rank_sym_lds<WPR>(lds_cols);
+    const int cnt = h->count[bin], stride = gridDim.x * RPW;
+    const RowDesc *rows = rd + h->offset[bin];
+    RowDesc nxt{};
+    int r = blockIdx.x * RPW + g;
+    if (r < cnt) nxt = rows[r];
+    for (; r < cnt; r += stride) {
+        const RowDesc cur = nxt;
+        if (r + stride < cnt) nxt = rows[r + stride];
+        const BatchDesc &d = desc[cur.prob];
+        rank_sym_row<WPR>(cur.e0, cur.e1, d.Acol, d.Brp, d.Bcol, d.cols, gt, raw, &nnzc[cur.grow]);
+        group_sync<WPR>();
+    }
+}
+
+template <typename V, int WPR, int RPW>
+__global__ __launch_bounds__(kWave *WPR *RPW) void k_bnum_rank_rows(const BatchDesc *__restrict__ desc,
+                                                                    const RowDesc *__restrict__ rd,
+                                                                    const BatchHdr *bh, int bin, int lds_cols, int cap,
+                                                                    long long ccap, int *__restrict__ Ccol,
+                                                                    V *__restrict__ Cval, int *err)
+{
+    static_assert(RPW == 1 || WPR == 1, "multi-row blocks use one wave per row");
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    if (bh->nnz_c > ccap) return;
+    const int g = threadIdx.x / kWave / WPR, gt = threadIdx.x - g * WPR * kWave;
+    unsigned char *raw = s_raw + g * rank_row_lds<V, WPR>(lds_cols, cap);
+    const int cnt = bh->num.count[bin], stride = gridDim.x * RPW;
+    const RowDesc *rows = rd + bh->num.offset[bin];
+    RowDesc nxt{};
+    int r = blockIdx.x * RPW + g;
+    if (r < cnt) nxt = rows[r];
+    for (; r < cnt; r += stride) {
+        const RowDesc cur = nxt;
+        if (r + stride < cnt) nxt = rows[r + stride];
+        const BatchDesc &d = desc[cur.prob];
+        rank_num_row<V, WPR>(cur.e0, cur.e1, d.Acol, (const V *)d.Aval, d.Brp, d.Bcol, (const V *)d.Bval, cur.rb,
+                             cur.nc, d.cols, lds_cols, cap, gt, raw, Ccol, Cval, err);
+        group_sync<WPR>();
+    }
+}
+
 // Symbolic, heavy rows: one block per row, key table at goff[row] in the
 // global pool (cleared here; gcap slots in all).
 __global__ __launch_bounds__(kGlobalThreads) void k_bsym_global(const BatchDesc *__restrict__ desc,
@@ -324,7 +385,7 @@ __global__ __launch_bounds__(kWideThreads) void k_bsym_wide(const BatchDesc *__r
                                                             const int *__restrict__ perm, int *__restrict__ nnzc)
 {
     extern __shared__ unsigned s_bmw[];
-    __shared__ EnumScratch<float, kWideThreads> S;
+    __shared__ PieceScratch<float, kWideThreads> S;
     __shared__ int s_cnt;
     const int cnt = h->count[kBinHeavy];
     const int *rows = perm + h->offset[kBinHeavy];
@@ -334,23 +395,18 @@ __global__ __launch_bounds__(kWideThreads) void k_bsym_wide(const BatchDesc *__r
         const BatchDesc &d = desc[prob[grow]];
         if (d.cols > kWideMaxCols) continue;
         const int nw = (d.cols + 31) >> 5;
-        const int *Acol = d.Acol, *Brp = d.Brp;
         const int arow = (int)(grow - d.row0);
         for (int t = gt; t < nw; t += kWideThreads) s_bmw[t] = 0u;
-        if (gt == 0) s_cnt = 0;
-        __syncthreads();
-        group_products<float, false, kWideThreads, 2>(
-            d.Arp[arow], d.Arp[arow + 1], gt, S, d.Bcol, (const float *)nullptr,
-            [&](int e, int &bs, int &bl, float &) {
-                const int k = Acol[e];
-                bs = Brp[k];
-                bl = Brp[k + 1] - bs;
-            },
-            [&](int j) {
-                const unsigned bit = 1u << (j & 31);
-                if (!(s_bmw[j >> 5] & bit)) atomicOr(&s_bmw[j >> 5], bit);
-            });
-        __syncthreads();
+        if (gt == 0) s_cnt = 0;                            // the products' first barrier follows
+        auto mark = [&](const auto &j, const auto &ok) {
+            constexpr int N = sizeof(j) / sizeof(j[0]);
+#pragma unroll
+            for (int u = 0; u < N; ++u)
+                if (ok[u]) atomicOr(&s_bmw[j[u] >> 5], 1u << (j[u] & 31));
+        };
+        piece_products<float, false, kWideThreads, kWideThreads, 4, true, kRankPiece>(
+            d.Arp[arow], d.Arp[arow + 1], gt, S, d.Acol, (const float *)nullptr, d.Brp, 1, 1, d.Bcol,
+            (const float *)nullptr, mark);
         int c = 0;
         for (int t = gt; t < nw; t += kWideThreads) c += __popc(s_bmw[t]);
         c = wave_sum(c);
@@ -360,8 +416,49 @@ __global__ __launch_bounds__(kWideThreads) void k_bsym_wide(const BatchDesc *__r
     }
 }
 
-// Numeric, heavy rows of problems with at most kWideMaxCols columns: one
-// block per row takes B's columns in windows of kWideWin; in each window the
+// Numeric, heavy rows of problems with at most kRankMaxCols columns: one block
+// per row (from a queue: long and short rows balance across the persistent
+// blocks) merges it by a column bitmap, kWideCap entries at a time.  Windows of
+// 8192 columns (below) scan every slot of every window, thousands for the few
+// hundred entries a row has there: 2.50 ms in a batch of 512 problems of up to
+// 32768 columns, against 1.39 (four waves per row instead of eight: 1.67;
+// 5120 entries at a time, two blocks per CU: 1.47).
+constexpr int kWideCap = 3072;
+constexpr int kWideRankThreads = 512;
+constexpr int kWideWaves = kWideRankThreads / kWave;
+
+template <typename V>
+__global__ __launch_bounds__(kWideRankThreads) void k_bnum_wide_rank(const BatchDesc *__restrict__ desc,
+                                                                 const int *__restrict__ prob, const BatchHdr *bh,
+                                                                 const int *__restrict__ perm, long long ccap,
+                                                                 const long long *__restrict__ Crp, int lds_cols,
+                                                                 int *__restrict__ Ccol, V *__restrict__ Cval, int *err,
+                                                                 int *queue)
+{
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    __shared__ int s_r;
+    if (bh->nnz_c > ccap) return;
+    const int cnt = bh->num.count[kBinHeavy];
+    const int *rows = perm + bh->num.offset[kBinHeavy];
+    for (;;) {
+        __syncthreads();                                // the previous row is done with s_r and the LDS
+        if (threadIdx.x == 0) s_r = atomicAdd(queue, 1);
+        __syncthreads();
+        const int r = s_r;
+        if (r >= cnt) break;
+        const int grow = rows[r];
+        const BatchDesc &d = desc[prob[grow]];
+        if (d.cols > kRankMaxCols) continue;
+        const int arow = (int)(grow - d.row0);
+        const long long rb = Crp[grow];
+        rank_num_row<V, kWideWaves>(d.Arp[arow], d.Arp[arow + 1], d.Acol, (const V *)d.Aval, d.Brp, d.Bcol,
+                                    (const V *)d.Bval, rb, (int)(Crp[grow + 1] - rb), d.cols, lds_cols, kWideCap,
+                                    threadIdx.x, s_raw, Ccol, Cval, err);
+    }
+}
+
+// Numeric, heavy rows of problems with more than kRankMaxCols and at most
+// kWideMaxCols columns: one block per row takes B's columns in windows of kWideWin; in each window the
 // row's products with columns inside it are added into an LDS array of
 // doubles indexed by column (occupancy marked by the -0.0 start value, as in
 // the dense chunks of single products), and each wave ranks its share of the
@@ -399,7 +496,7 @@ __global__ __launch_bounds__(kWideThreads) void k_bnum_wide(const BatchDesc *__r
         if (r >= cnt) break;
         const int grow = rows[r];
         const BatchDesc &d = desc[prob[grow]];
-        if (d.cols > kWideMaxCols) continue;
+        if (d.cols <= kRankMaxCols || d.cols > kWideMaxCols) continue;
         const int *Acol = d.Acol, *Brp = d.Brp;
         const V *Aval = (const V *)d.Aval;
         const int arow = (int)(grow - d.row0);

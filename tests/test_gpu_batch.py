@@ -238,3 +238,28 @@ def test_batch_full_512(env, oracle_mod):
         check_rows(C.row_ptr.cpu().numpy(), C.col_idx.cpu().numpy(), C.val.cpu().numpy(), oracle_mod.spgemm(A, B),
                    np.float32, f"512 batch problem {p}")
     plan.close()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("widths", [(2000, 32768), (32769, 65537), (131072,), (131072, 131073, 1 << 20, (1 << 20) + 1)])
+def test_batch_widths(env, oracle_mod, dtype, widths):
+    """The heavy and LDS rows of a batch at every limit of B's width: bitmap rows
+    (up to 128 columns per table slot, and 2^17), windows (2^20), global tables
+    above.  Rows of 40 to 6000 entries: light rows of every table, heavy rows of
+    one and of several passes, A rows longer than one list."""
+    torch, smash, ctx = env
+    probs = []
+    for q, n in enumerate(widths):
+        B = syn.uniform_k_per_row(900, n, 20, 300 + q, dtype)
+        lens = [2, 5, 13, 26, 52, 55, 130, 310, 700]
+        ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        col = np.concatenate([np.arange(k) + 11 * i for i, k in enumerate(lens)]).astype(np.int32)
+        probs.append((syn.CSR(len(lens), 900, ptr, col, (2.0 * syn.uniform01(7, 0, len(col)) - 1.0).astype(dtype)), B))
+    refs = [oracle_mod.spgemm(A, B) for A, B in probs]
+    for row_hash in (0, 1):
+        plan = _make_plan(smash, ctx, probs, dict(lds_row_max=1024, table_shift=1, wide_groups=0, blocks_per_cu=8,
+                                                  row_hash=row_hash))
+        for rep in range(2):
+            plan.run()
+            _check_plan(plan, probs, refs, oracle_mod, f"widths {widths} hash {row_hash} run {rep}")
+        plan.close()
