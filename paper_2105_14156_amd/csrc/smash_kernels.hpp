@@ -510,7 +510,7 @@ struct PieceScratch {
 template <int T>
 __device__ __forceinline__ int row_bcast(int v)
 {
-    return __builtin_amdgcn_update_dpp(0, v, kDppRowNewBcast + T, 0xf, 0xf, false);
+    return __builtin_amdgcn_mov_dpp(v, kDppRowNewBcast + T, 0xf, 0xf, true);   // every lane has a source
 }
 
 template <int T>
@@ -575,8 +575,8 @@ __device__ __forceinline__ int piece_count(const PieceScratch<V, GE> &S)
 template <typename V, bool WITH_VAL, int U, int PL>
 struct PieceGroup {
     int pos[U], j[U];
-    double av[U];
-    V raw[U];
+    bool ok[U];
+    V a[U], raw[U];
 
     template <int T>
     __device__ __forceinline__ void load(int st, int en, V al, const int *__restrict__ Bcol,
@@ -584,10 +584,9 @@ struct PieceGroup {
     {
         take<T, 0>(st, en, al);
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int q = pos[u] >= 0 ? pos[u] : 0;
-            j[u] = Bcol[q];
-            if constexpr (WITH_VAL) raw[u] = Bval[q];
+        for (int u = 0; u < U; ++u) {                              // an absent product loads entry 0
+            j[u] = Bcol[pos[u]];
+            if constexpr (WITH_VAL) raw[u] = Bval[pos[u]];
         }
     }
 
@@ -596,9 +595,9 @@ struct PieceGroup {
     {
         if constexpr (N < U) {
             const int q = piece_bcast<PL, T + N>(st) + (lane_id() & (PL - 1));
-            pos[N] = q < piece_bcast<PL, T + N>(en) ? q : -1;
-            if constexpr (WITH_VAL) av[N] = (double)piece_bcast<PL, T + N>(al);
-            else av[N] = 0.0;
+            ok[N] = q < piece_bcast<PL, T + N>(en);
+            pos[N] = ok[N] ? q : 0;
+            if constexpr (WITH_VAL) a[N] = piece_bcast<PL, T + N>(al);
             take<T, N + 1>(st, en, al);
         }
     }
@@ -606,13 +605,14 @@ struct PieceGroup {
     template <typename Sink>
     __device__ __forceinline__ void emit(Sink &sink)
     {
-        double bv[U];
+        if constexpr (WITH_VAL) {
+            double p[U];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if constexpr (WITH_VAL) bv[u] = (double)raw[u];
-            else bv[u] = 0.0;
+            for (int u = 0; u < U; ++u) p[u] = (double)a[u] * (double)raw[u];
+            sink(j, p, ok);
+        } else {
+            sink(j, ok);
         }
-        emit_products<WITH_VAL, U, true>(sink, pos, j, av, bv);
     }
 };
 
