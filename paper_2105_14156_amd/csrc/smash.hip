@@ -717,7 +717,7 @@ smash_status fused_stage(smash_ctx c, hipStream_t s, Plan &p, smash_alloc_fn all
     if (learned) {      // the features came with the analysis
         TRY(launch(c, K_MLP_PREDICT, s, [&] {
             k_mlp_predict<<<blocks_for(m, 256), 256, 0, s>>>(m, (int)p.n, p.feats, prm, prm + kParams,
-                                                             c->pred_delta, p.ub, p.maxb, nullptr, p.cap_pred,
+                                                             c->pred_delta, p.ub, p.maxb, p.cap_pred,
                                                              p.lds_row_max);
         }));
     }
@@ -1359,8 +1359,9 @@ smash_status smash_mlp_predict(smash_ctx c, int64_t m, const float *feats, const
     if (!feats || !params || !ms || !yhat) return fail(c, SMASH_ERR_INVALID_ARG, "null pointer");
     DeviceGuard g(c->device);
     TRY(launch(c, K_MLP_PREDICT, s, [&] {
-        k_mlp_predict<<<blocks_for(m, 256), 256, 0, s>>>((int)m, 0, feats, params, ms, 0.f, nullptr, nullptr, yhat,
-                                                         nullptr, -1);
+        // two blocks of four waves per CU at most: the weights are loaded once
+        const unsigned grid = std::min<unsigned>(blocks_for(m, 4 * kMlpRows), 2u * (unsigned)c->cus);
+        k_mlp_rows<<<grid, 256, 0, s>>>((int)m, feats, params, ms, yhat);
     }));
     return SMASH_OK;
 }

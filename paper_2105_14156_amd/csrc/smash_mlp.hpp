@@ -86,9 +86,8 @@ __device__ __forceinline__ int predicted_capacity(float y, float delta, long lon
 // time, a hidden unit per lane, instead of a row per lane.
 constexpr int kMlpSparseRows = 8;
 
-// Inference: predicted log2(1 + nnz) and, when cap is given, the capacity
-// (predicted_capacity).  With only_above >= 0 the network is evaluated only
-// for rows whose exact bound min(ub, cols) exceeds it (the rows a
+// Predicted capacities (predicted_capacity): the network is evaluated only
+// for rows whose exact bound min(ub, cols) exceeds only_above (the rows a
 // prediction can move into the LDS tables); the others get the bound
 // itself, and a block without such rows loads no weights.  A wave with many
 // candidate rows evaluates a row per lane; a wave with few (where the
@@ -100,8 +99,8 @@ constexpr int kMlpSparseRows = 8;
 __global__ __launch_bounds__(256) void k_mlp_predict(int m, int ncols, const float *__restrict__ feats,
                                                      const float *__restrict__ theta, const float *__restrict__ ms,
                                                      float delta, const long long *__restrict__ ub,
-                                                     const int *__restrict__ maxb, float *__restrict__ yhat_out,
-                                                     int *__restrict__ cap_out, int only_above)
+                                                     const int *__restrict__ maxb, int *__restrict__ cap_out,
+                                                     int only_above)
 {
     static_assert(kHid == kWave, "one hidden unit per lane");
     __shared__ float s_w[kParams];
@@ -109,17 +108,17 @@ __global__ __launch_bounds__(256) void k_mlp_predict(int m, int ncols, const flo
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     const int lane = threadIdx.x & (kWave - 1);
     const bool live = i < m;
-    const long long ub_i = live && ub ? ub[i] : 0;
+    const long long ub_i = live ? ub[i] : 0;
     const long long bound = ub_i < ncols ? ub_i : ncols;
-    const bool cand = live && (only_above < 0 || bound > only_above);
+    const bool cand = live && bound > only_above;
     if (!__syncthreads_or(cand)) {
-        if (live && cap_out) cap_out[i] = (int)bound;
+        if (live) cap_out[i] = (int)bound;
         return;
     }
     load_params(s_w, theta);
     if (threadIdx.x < 2 * kFeat) s_ms[threadIdx.x] = ms[threadIdx.x];
     __syncthreads();
-    if (live && !cand && cap_out) cap_out[i] = (int)bound;
+    if (live && !cand) cap_out[i] = (int)bound;
     const unsigned long long cm = __builtin_amdgcn_ballot_w64(cand);
     if (__popcll(cm) > kMlpSparseRows) {
         if (!cand) return;
@@ -127,8 +126,7 @@ __global__ __launch_bounds__(256) void k_mlp_predict(int m, int ncols, const flo
 #pragma unroll
         for (int f = 0; f < kFeat; ++f) x[f] = (feats[(long long)i * kFeat + f] - s_ms[f]) / s_ms[kFeat + f];
         const float y = mlp_eval(s_w, x);
-        if (yhat_out) yhat_out[i] = y;
-        if (cap_out) cap_out[i] = predicted_capacity(y, delta, ub[i], maxb[i], ncols);
+        cap_out[i] = predicted_capacity(y, delta, ub[i], maxb[i], ncols);
         return;
     }
     if (!cm) return;
@@ -161,10 +159,90 @@ __global__ __launch_bounds__(256) void k_mlp_predict(int m, int ncols, const flo
 #pragma unroll
         for (int q = 0; q < kHid; ++q)
             y = fmaf(s_w[kOW3 + q], __int_as_float(__builtin_amdgcn_readlane(__float_as_int(h2), q)), y);
-        if (lane == l) {
-            if (yhat_out) yhat_out[r] = y;
-            if (cap_out) cap_out[r] = predicted_capacity(y, delta, ub[r], maxb[r], ncols);
+        if (lane == l) cap_out[r] = predicted_capacity(y, delta, ub[r], maxb[r], ncols);
+    }
+}
+
+// Inference for every row (smash_mlp_predict): 32 rows per wave and step on
+// V_MFMA_F32_32X32X2 (D += A B: lane l gives A[l % 32][k] and B[k][l % 32] with
+// k = l / 32, and holds rows 8 (r / 4) + 4 (l / 32) + r % 4, r = 0..15, column
+// l % 32 of D).  Units are rows and samples columns of D, so a layer's output
+// registers are the next one's B operands as they are: step r contracts the
+// two units that register r holds in the two half-waves, and the weights are
+// loaded in that order.  They stay in registers; nothing else touches LDS.
+// Bound by the matrix unit (70 instructions of 64 cycles per 32 rows) and the
+// weights' first load: features and prediction of 131072 rows take 48 us with
+// their launches, 58 where a lane took a row with a fused multiply-add per
+// weight.  FP32 sums, in another order than there (error against 64 bits
+// 7e-8 of the largest output, 1.1e-7 there).
+constexpr int kMlpRows = 32;
+
+typedef float mlp_f32x16 __attribute__((ext_vector_type(16)));
+
+__global__ __launch_bounds__(256, 2) void k_mlp_rows(int m, const float *__restrict__ feats,
+                                                     const float *__restrict__ theta, const float *__restrict__ ms,
+                                                     float *__restrict__ yhat)
+{
+    constexpr int LD = kHid + 1;
+    __shared__ float s_w2[kHid * LD];
+    const int lane = lane_id(), s = lane & 31, h = lane >> 5;
+    for (int t = threadIdx.x; t < kHid * kHid; t += 256) s_w2[t / kHid * LD + t % kHid] = theta[kOW2 + t];
+    __syncthreads();
+    float w1[2][3], w2[2][2][16];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int t = 0; t < 3; ++t) w1[i][t] = theta[kOW1 + (i * 32 + s) * kFeat + 2 * t + h];
+    }
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                w2[j][i][r] = s_w2[(j * 32 + s) * LD + i * 32 + 8 * (r >> 2) + 4 * h + (r & 3)];
+    float mean[3], dev[3];
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+        mean[t] = ms[2 * t + h];
+        dev[t] = ms[kFeat + 2 * t + h];
+    }
+    mlp_f32x16 b1[2], b2[2], w3[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int u = i * 32 + 8 * (r >> 2) + 4 * h + (r & 3);
+            b1[i][r] = theta[kOB1 + u];
+            b2[i][r] = theta[kOB2 + u];
+            w3[i][r] = theta[kOW3 + u];
         }
+    const int tiles = (int)(((long long)m + kMlpRows - 1) / kMlpRows);
+    for (int tile = blockIdx.x * 4 + threadIdx.x / kWave; tile < tiles; tile += gridDim.x * 4) {
+        const unsigned row = (unsigned)tile * kMlpRows + s;
+        mlp_f32x16 z1[2] = {b1[0], b1[1]}, z2[2] = {b2[0], b2[1]};
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            const float x = row < (unsigned)m ? (feats[(long long)row * kFeat + 2 * t + h] - mean[t]) / dev[t] : 0.f;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) z1[i] = __builtin_amdgcn_mfma_f32_32x32x2f32(w1[i][t], x, z1[i], 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float a = z1[i][r] > 0.f ? z1[i][r] : 0.f;
+#pragma unroll
+                for (int j = 0; j < 2; ++j)
+                    z2[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w2[j][i][r], a, z2[j], 0, 0, 0);
+            }
+        float y = 0.f;
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) y = fmaf(w3[j][r], z2[j][r] > 0.f ? z2[j][r] : 0.f, y);
+        y += __shfl_xor(y, 32, kWave);
+        if (h == 0 && row < (unsigned)m) yhat[row] = y + theta[kOB3];
     }
 }
 

@@ -83,6 +83,28 @@ def test_predict_and_gradient_parity(env):
         pos += k
 
 
+@pytest.mark.parametrize("m", [1, 31, 32, 33, 129, 65536, 65573])
+def test_predict_tile_edges(env, m):
+    """Row counts around one tile of 32 rows, one block of four tiles and the
+    largest grid (512 blocks: 65536 rows), where a wave takes a second tile.
+    FP32 sums of 64 terms: as in the parity test above.  A NaN feature
+    stays in its row."""
+    torch, smash, ctx = env
+    F, y, ms, th, t = _setup(torch, n=65573, seed=17)
+    F = F[:m]
+    X = (F - ms[:6]) / ms[6:]
+    ref, _ = mlp.forward(th, X)
+    feats = t(F)
+    out = ctx.mlp_predict(feats, t(th), t(ms))
+    assert out.shape[0] == m
+    yhat = out.cpu().numpy()
+    assert np.max(np.abs(yhat - ref)) < 1e-4 * max(1.0, np.abs(ref).max())
+    feats[m // 2, 3] = float("nan")
+    again = ctx.mlp_predict(feats, t(th), t(ms)).cpu().numpy()
+    keep = np.arange(m) != m // 2
+    assert np.array_equal(again[keep], yhat[keep])
+
+
 @pytest.mark.parametrize("n", [1, 64, 65, 16384, 16449])
 def test_gradient_tile_edges(env, n):
     """Batches around one tile of 64 samples and around one tile per block of
