@@ -263,3 +263,27 @@ def test_batch_widths(env, oracle_mod, dtype, widths):
             plan.run()
             _check_plan(plan, probs, refs, oracle_mod, f"widths {widths} hash {row_hash} run {rep}")
         plan.close()
+
+
+@pytest.mark.parametrize("rows", [[1], [63, 0, 1, 64, 65], [255, 1, 300]])
+def test_batch_row_bounds(env, oracle_mod, rows):
+    """Rows around the limits of the bound's split: lanes of a group of eight
+    (7..9 entries), the longest row of a group and the shortest of a wave
+    (128, 129), one and two steps of a wave (512, 513), rows without entries,
+    over problems that start inside a wave's 64 rows.  Sums of B-row lengths
+    decide the bins and capacities, so a wrong one changes the result;
+    structure and row counts exact."""
+    torch, smash, ctx = env
+    lens = np.array([129, 0, 1, 7, 8, 9, 128, 130, 513, 512, 31, 33, 1025, 64, 3])
+    probs = []
+    for p, m in enumerate(rows):
+        k = lens[(np.arange(m) + p) % len(lens)]
+        ptr = np.concatenate([[0], np.cumsum(k)]).astype(np.int32)
+        col = np.concatenate([np.zeros(0, np.int32)] + [np.arange(n, dtype=np.int32) + i % 200 for i, n in enumerate(k)])
+        A = syn.CSR(m, 2048, ptr, col, np.ones(len(col), np.float32))
+        probs.append((A, syn.rmat_rect(2048, 2, 9 + p, np.float32)))
+    refs = [oracle_mod.spgemm(A, B) for A, B in probs]
+    plan = _make_plan(smash, ctx, probs)
+    plan.run()
+    _check_plan(plan, probs, refs, oracle_mod, f"rows {rows}")
+    plan.close()
