@@ -749,7 +749,7 @@ smash_status fused_copy(smash_ctx c, hipStream_t s, const Plan &p, const int64_t
     const int nf = p.hdr.fz.offset[kLdsBins];
     if (!p.fused || nf == 0) return SMASH_OK;
     return launch(c, K_FUSED_COPY, s, [&] {
-        k_fused_copy<V><<<blocks_for(nf, 4), 256, 0, s>>>(p.f_perm, nf, p.fstatus, p.stage_off, p.stage_col,
+        k_fused_copy<V><<<blocks_for(nf, 4 * kCopyRows), 256, 0, s>>>(p.f_perm, nf, p.fstatus, p.stage_off, p.stage_col,
                                                          (const V *)p.stage_val, (const long long *)crp, ccol, cval);
     });
 }

@@ -238,8 +238,15 @@ __global__ __launch_bounds__(256) void k_fused_mark(int m, const unsigned char *
     }
 }
 
-// Copies the staged rows of the fused pass to their final offsets in C
-// (one wave per row, coalesced, non-temporal stores).
+// Copies the staged rows of the fused pass to their final offsets in C.  Bound
+// by memory, once the four dependent reads before a row's first entry are
+// shared: a wave reads those of kCopyRows rows at once, a row per lane, and
+// then copies the rows' entries as one sequence (coalesced within a row,
+// kCopyU entries per lane in flight, non-temporal stores).  Rectangular
+// 131072-row product: 111 us; with a wave per row, 130.
+constexpr int kCopyRows = 8;
+constexpr int kCopyU = 4;
+
 template <typename V>
 __global__ __launch_bounds__(256) void k_fused_copy(const int *__restrict__ rows, int nrows,
                                                     const unsigned char *__restrict__ status,
@@ -248,15 +255,55 @@ __global__ __launch_bounds__(256) void k_fused_copy(const int *__restrict__ rows
                                                     const long long *__restrict__ Crp, int *__restrict__ Ccol,
                                                     V *__restrict__ Cval)
 {
-    const int r = blockIdx.x * 4 + threadIdx.x / kWave;
-    if (r >= nrows) return;
-    const int row = rows[r];
-    if (status[row] != 1) return;
-    const long long o = stage_off[row], d = Crp[row];
-    const int n = (int)(Crp[row + 1] - d);
-    for (int t = lane_id(); t < n; t += kWave) {
-        store_c(&Ccol[d + t], scol[o + t]);
-        store_c(&Cval[d + t], sval[o + t]);
+    const int lane = lane_id();
+    const long long r = ((long long)blockIdx.x * 4 + threadIdx.x / kWave) * kCopyRows + lane;
+    long long src = 0, dst = 0;
+    int n = 0;
+    if (lane < kCopyRows && r < nrows) {
+        const int row = rows[r];
+        if (status[row] == 1) {
+            src = stage_off[row];
+            dst = Crp[row];
+            n = (int)(Crp[row + 1] - dst);
+        }
+    }
+    // rows of the sequence: first[q] .. first[q + 1]
+    long long o[kCopyRows], d[kCopyRows];
+    int first[kCopyRows];
+    int total = 0;
+#pragma unroll
+    for (int q = 0; q < kCopyRows; ++q) {
+        first[q] = total;
+        o[q] = __shfl(src, q, kWave) - total;
+        d[q] = __shfl(dst, q, kWave) - total;
+        total += __builtin_amdgcn_readlane(n, q);
+    }
+    for (int t0 = lane; t0 < total; t0 += kCopyU * kWave) {
+        int c[kCopyU];
+        V v[kCopyU];
+        long long at[kCopyU];
+#pragma unroll
+        for (int u = 0; u < kCopyU; ++u) {
+            const int t = t0 + u * kWave;
+            long long from = o[0], to = d[0];
+#pragma unroll
+            for (int q = 1; q < kCopyRows; ++q)
+                if (t >= first[q]) {
+                    from = o[q];
+                    to = d[q];
+                }
+            at[u] = to + t;
+            if (t < total) {
+                c[u] = scol[from + t];
+                v[u] = sval[from + t];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kCopyU; ++u)
+            if (t0 + u * kWave < total) {
+                store_c(&Ccol[at[u]], c[u]);
+                store_c(&Cval[at[u]], v[u]);
+            }
     }
 }
 

@@ -218,3 +218,18 @@ def test_learned_sizing_gain(env, oracle_mod):
     moved = bd["rows_heavy"] - ln["rows_heavy"]
     assert ln["fused_rows"] - bd["fused_rows"] == moved
     assert moved >= 0.5 * int(recoverable.sum()), "the network fused fewer than half of the recoverable rows"
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("rows", [1, 7, 8, 9, 33, 67])
+def test_fused_copy_row_groups(env, oracle_mod, rows, dtype):
+    """Numbers of fused rows around a wave's eight and a block's 32 in the copy
+    to C, rows of 1 to 300 entries around a step of 64 and of 256, rows that
+    the pass leaves out (empty) between them."""
+    lens = np.array([1, 63, 64, 0, 65, 255, 256, 257, 300, 2])[np.arange(rows) % 10]
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col = np.concatenate([np.arange(k) + 3 * i for i, k in enumerate(lens)]).astype(np.int32)
+    A = syn.CSR(rows, 512, ptr, col, (2.0 * syn.uniform01(7, 0, len(col)) - 1.0).astype(dtype))
+    B = syn.uniform_k_per_row(512, 1000, 1, 0x5EED0609, dtype)
+    st = fused_check(env, A, B, dtype, oracle_mod, f"fused copy {rows}")
+    assert st["fused_rows"] == int((lens > 0).sum())
