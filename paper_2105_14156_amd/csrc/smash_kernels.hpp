@@ -163,12 +163,6 @@ __device__ __forceinline__ int wave_scan_dpp(int v, int id, Op op)
     return v;
 }
 
-// The value of the lane below (lane 0 gets `id`).
-__device__ __forceinline__ int wave_shift_up1(int v, int id)
-{
-    return __builtin_amdgcn_update_dpp(id, v, kDppWaveShr1, 0xf, 0xf, false);
-}
-
 template <typename T>
 __device__ __forceinline__ T wave_incl_scan(T v)
 {
@@ -327,8 +321,7 @@ __device__ __forceinline__ void emit_products(Sink &sink, const int (&pos)[U], c
 // q = gt, gt + G, ... and finds its A entry by binary search (consecutive
 // lanes then read consecutive B entries where a range continues).  U products
 // per thread are located and loaded before any is merged.
-template <typename V, bool WITH_VAL, int G, int U, typename Get, typename Sink, bool ARRAY_SINK = false,
-          bool PIPELINE = false>
+template <typename V, bool WITH_VAL, int G, int U, typename Get, typename Sink, bool ARRAY_SINK = false>
 __device__ __forceinline__ void group_products(int e0, int e1, int gt, EnumScratch<V, G> &S,
                                                const int *__restrict__ Bcol, const V *__restrict__ Bval,
                                                Get get, Sink sink)
@@ -365,9 +358,7 @@ __device__ __forceinline__ void group_products(int e0, int e1, int gt, EnumScrat
         group_sync<WG>();
         const int ptot = S.pincl[G - 1], stot = S.sincl[G - 1];
         // long ranges, piece by piece: wave wg takes U consecutive pieces per
-        // round; with PIPELINE the pieces of the next round are located (LDS
-        // searches) while the loads of this round are in flight.  A wave's
-        // pieces only move forward, so it keeps a cursor `cur` (no piece of
+        // round.  A wave's pieces only move forward, so it keeps a cursor `cur` (no piece of
         // it lies in an A entry before cur) and finds the A entry of piece
         // pc from one wave-wide read: lane l holds the boundary
         // pincl[cur + l - 1] (lane 0 the one before cur, never above pc),
@@ -406,33 +397,17 @@ __device__ __forceinline__ void group_products(int e0, int e1, int gt, EnumScrat
             cur = last;
         };
         {
-            int pos[U];
-            double av[U];
-            int pc0 = wg * U;
-            if constexpr (PIPELINE)
-                if (pc0 < ptot) locate_pieces(pc0, pos, av);
-            for (; pc0 < ptot; pc0 += WG * U) {
-                int j[U];
-                double bv[U];
-                if constexpr (!PIPELINE) locate_pieces(pc0, pos, av);
+            int pos[U], j[U];
+            double av[U], bv[U];
+            for (int pc0 = wg * U; pc0 < ptot; pc0 += WG * U) {
+                locate_pieces(pc0, pos, av);
                 load_products<V, WITH_VAL, U>(Bcol, Bval, pos, j, bv);
-                int posn[U];
-                double avn[U];
-                if constexpr (PIPELINE)
-                    if (pc0 + WG * U < ptot) locate_pieces(pc0 + WG * U, posn, avn);
                 emit_products<WITH_VAL, U, ARRAY_SINK>(sink, pos, j, av, bv);
-                if constexpr (!PIPELINE) continue;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    pos[u] = posn[u];
-                    av[u] = avn[u];
-                }
             }
         }
         // short ranges, flat: thread gt takes products q = q0 + u * G + gt
         // and finds its A entry by binary search (consecutive lanes then read
-        // consecutive B entries where a range continues); with PIPELINE the
-        // next round is located while this round's loads are in flight
+        // consecutive B entries where a range continues)
         auto locate_flat = [&](int q0, int (&pos)[U], double (&av)[U]) {
             // the U searches advance step by step together, so that their
             // LDS reads are in flight at once
@@ -461,26 +436,12 @@ __device__ __forceinline__ void group_products(int e0, int e1, int gt, EnumScrat
             }
         };
         {
-            int pos[U];
-            double av[U];
-            if constexpr (PIPELINE)
-                if (stot > 0) locate_flat(0, pos, av);
+            int pos[U], j[U];
+            double av[U], bv[U];
             for (int q0 = 0; q0 < stot; q0 += G * U) {
-                int j[U];
-                double bv[U];
-                if constexpr (!PIPELINE) locate_flat(q0, pos, av);
+                locate_flat(q0, pos, av);
                 load_products<V, WITH_VAL, U>(Bcol, Bval, pos, j, bv);
-                int posn[U];
-                double avn[U];
-                if constexpr (PIPELINE)
-                    if (q0 + G * U < stot) locate_flat(q0 + G * U, posn, avn);
                 emit_products<WITH_VAL, U, ARRAY_SINK>(sink, pos, j, av, bv);
-                if constexpr (!PIPELINE) continue;
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    pos[u] = posn[u];
-                    av[u] = avn[u];
-                }
             }
         }
         group_sync<WG>();
@@ -790,11 +751,6 @@ __device__ __forceinline__ int lds_insert_key_at(int *keys, int logT, int key, u
     return 0;
 }
 
-__device__ __forceinline__ int lds_insert_key(int *keys, int logT, int key, int *err)
-{
-    return lds_insert_key_at(keys, logT, key, slot_of(key, logT), err);
-}
-
 // Claims or finds the slot of `key`, probing from slot h, and adds `p` to its
 // value (values are accumulated in double: the LDS FP64 atomic add is the
 // fast one on gfx950).
@@ -815,11 +771,6 @@ __device__ __forceinline__ void lds_insert_add_at(int *keys, double *vals, int l
         h = (h + 1) & mask;
     }
     atomicOr(err, kErrProbe);
-}
-
-__device__ __forceinline__ void lds_insert_add(int *keys, double *vals, int logT, int key, double p, int *err)
-{
-    lds_insert_add_at(keys, vals, logT, key, p, slot_of(key, logT), err);
 }
 
 // U products of one thread at once, each starting with a compare-and-swap
@@ -3075,12 +3026,13 @@ __device__ __forceinline__ void wave_store_ranked(const double (&vr)[ROUNDS], co
 // atomic per `claim` chunks), so that long and short chunks balance across
 // CUs, and each wave puts -0.0 back in its slots once its entries are out, so
 // the array is ready for the next chunk without a separate clearing pass.
-// Bound by instruction issue (about half the cycles) and LDS adds (a third):
-// RMAT scale 19 A * A FP32 (844K chunks, 4.9e9 products) takes 14.8 ms; with
-// a search per product instead of per piece of 16 it was 17.9, with four
-// instead of up to eight products per thread in flight 16.9.  Chunks dealt
-// ahead, their A entries and split points fetched while the one before is
-// ranked, were no faster (15.1).
+// Bound by traffic, with instruction issue close behind: RMAT scale 19 A * A
+// FP32 (844K chunks, 4.9e9 products) moves 63 GB to and from the L2s in 14.7
+// ms, 4.3 TB/s where a copy reaches 5.1 (one B entry per product, C once).
+// With a search per product instead of per piece of 16 it was 17.9 ms, with
+// four instead of up to eight products per thread in flight 16.9.  Chunks
+// dealt ahead, their A entries and split points fetched while the one before
+// is ranked, were no faster (15.1).
 constexpr int kDenseThreads = 512;
 // dense chunks a block claims with one atomic on the queue when every block
 // has many to do (one atomic per chunk from every resident block serialises
