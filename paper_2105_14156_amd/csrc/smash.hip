@@ -1610,7 +1610,8 @@ struct smash_batch_plan_s {
     int wide_words = 1;                  // LDS bitmap words of the widest problem up to kWideMaxCols
     int max_cols = 1;                    // columns of the widest problem
     int rank_cols = 0;                   // and of the widest up to kRankMaxCols
-    bool any_window = false;             // a problem of more than kRankMaxCols, at most kWideMaxCols columns
+    bool any_wide = false;               // a problem of at most kWideMaxCols columns
+    bool any_window = false;             // such a problem, wide enough for a row that takes the windows
     bool any_global = false;             // a problem wider than kWideMaxCols (global tables)
     // caller-owned output pool
     long long *crp = nullptr;
@@ -1746,14 +1747,12 @@ void batch_numeric(const BPlan &p, hipStream_t s)
 {
     if (p.cfg.wide_groups) bnum_bins<V, 1>(p, s);
     else bnum_bins<V, 0>(p, s);
-    if (p.rank_cols > 0)
+    if (p.any_wide)
         k_bnum_wide_rank<V><<<bgrid(p, p.M), kWideRankThreads, rank_row_lds<V, kWideWaves>(p.rank_cols, kWideCap), s>>>(
-            p.d_desc, p.prob, p.d_hdr, p.num_perm, p.ccap, p.crp, p.rank_cols, p.ccol, (V *)p.cval, &p.d_hdr->error,
-            &p.d_hdr->rank_queue);
+            p.d_desc, p.prob, p.d_hdr, p.num_perm, p.ccap, p.crp, p.rank_cols, p.ccol, (V *)p.cval, p.sym_perm);
     if (p.any_window)
         k_bnum_wide<V><<<bgrid(p, p.M), kWideThreads, kWideWin * sizeof(double), s>>>(
-            p.d_desc, p.prob, p.d_hdr, p.num_perm, p.ccap, p.crp, p.ccol, (V *)p.cval, &p.d_hdr->error,
-            &p.d_hdr->wide_queue);
+            p.d_desc, p.prob, p.d_hdr, p.sym_perm, p.ccap, p.crp, p.ccol, (V *)p.cval);
     if (p.any_global)
         k_bnum_global<V><<<bgrid(p, p.M), kGlobalThreads, global_rank_lds(kGlobalRankBits), s>>>(
         p.d_desc, p.prob, p.d_hdr, p.num_perm, p.goff, p.gcap, p.pool, p.ccap, p.crp, p.ccol,
@@ -1877,9 +1876,13 @@ smash_status smash_batch_plan_create(smash_ctx c, smash_dtype dtype, int32_t cou
     for (int q = 0; q < count; ++q) {
         p->max_cols = std::max(p->max_cols, (int)B[q].cols);
         if (B[q].cols <= kRankMaxCols) p->rank_cols = std::max(p->rank_cols, (int)B[q].cols);
-        else if (B[q].cols <= kWideMaxCols) p->any_window = true;
-        if (B[q].cols <= kWideMaxCols) p->wide_words = std::max(p->wide_words, (int)((B[q].cols + 31) / 32));
-        else p->any_global = true;
+        if (B[q].cols <= kWideMaxCols) {
+            p->any_wide = true;
+            p->any_window |= B[q].cols > kWideRankMaxEntries;
+            p->wide_words = std::max(p->wide_words, (int)((B[q].cols + 31) / 32));
+        } else {
+            p->any_global = true;
+        }
     }
     smash_status st = SMASH_OK;
     auto bail = [&](smash_status e) {

@@ -36,7 +36,8 @@ struct BatchHdr {
     long long gneed;            // global table slots of the heavy rows
     int error;
     int rank_queue;             // next heavy row of the bitmap numeric kernel
-    int wide_queue;             // next heavy row of the windowed numeric kernel
+    int wide_rows;              // heavy rows it leaves to the windowed numeric kernel
+    int wide_queue;             // next of these
 };
 
 // Heavy rows of problems with at most kWideMaxCols columns are counted with
@@ -434,24 +435,34 @@ __global__ __launch_bounds__(kWideThreads) void k_bsym_wide(const BatchDesc *__r
     }
 }
 
-// Numeric, heavy rows of problems with at most kRankMaxCols columns: one block
-// per row (from a queue: long and short rows balance across the persistent
-// blocks) merges it by a column bitmap, kWideCap entries at a time.  Windows of
-// 8192 columns (below) scan every slot of every window, thousands for the few
-// hundred entries a row has there: 2.50 ms in a batch of 512 problems of up to
-// 32768 columns, against 1.39 (four waves per row instead of eight: 1.67;
-// 5120 entries at a time, two blocks per CU: 1.47).
+// Whether a heavy row of nc entries in a problem of `cols` columns is merged by
+// the column bitmap: rank_num_row's prefix counts are 16 bits wide, and a row
+// of 65536 entries has ranks that need one more.  Such rows take the windows.
+constexpr int kWideRankMaxEntries = 65535;
+
+__device__ __forceinline__ bool wide_rank_row(int cols, int nc)
+{
+    return cols <= kRankMaxCols && nc <= kWideRankMaxEntries;
+}
+
+// Numeric, heavy rows: one block per row (from a queue: long and short rows
+// balance across the persistent blocks) merges it by a column bitmap, kWideCap
+// entries at a time, or lists it (wide, bh->wide_rows of them) for the windows.
+// Windows of 8192 columns (below) scan every slot of every window, thousands
+// for the few hundred entries a row has there: 2.50 ms in a batch of 512
+// problems of up to 32768 columns, against 1.39 (four waves per row instead of
+// eight: 1.67; 5120 entries at a time, two blocks per CU: 1.47).
 constexpr int kWideCap = 3072;
 constexpr int kWideRankThreads = 512;
 constexpr int kWideWaves = kWideRankThreads / kWave;
 
 template <typename V>
 __global__ __launch_bounds__(kWideRankThreads) void k_bnum_wide_rank(const BatchDesc *__restrict__ desc,
-                                                                 const int *__restrict__ prob, const BatchHdr *bh,
+                                                                 const int *__restrict__ prob, BatchHdr *bh,
                                                                  const int *__restrict__ perm, long long ccap,
                                                                  const long long *__restrict__ Crp, int lds_cols,
-                                                                 int *__restrict__ Ccol, V *__restrict__ Cval, int *err,
-                                                                 int *queue)
+                                                                 int *__restrict__ Ccol, V *__restrict__ Cval,
+                                                                 int *__restrict__ wide)
 {
     extern __shared__ __align__(16) unsigned char s_raw[];
     __shared__ int s_r;
@@ -460,37 +471,41 @@ __global__ __launch_bounds__(kWideRankThreads) void k_bnum_wide_rank(const Batch
     const int *rows = perm + bh->num.offset[kBinHeavy];
     for (;;) {
         __syncthreads();                                // the previous row is done with s_r and the LDS
-        if (threadIdx.x == 0) s_r = atomicAdd(queue, 1);
+        if (threadIdx.x == 0) s_r = atomicAdd(&bh->rank_queue, 1);
         __syncthreads();
         const int r = s_r;
         if (r >= cnt) break;
         const int grow = rows[r];
         const BatchDesc &d = desc[prob[grow]];
-        if (d.cols > kRankMaxCols) continue;
-        const int arow = (int)(grow - d.row0);
         const long long rb = Crp[grow];
+        const int nc = (int)(Crp[grow + 1] - rb);
+        if (!wide_rank_row(d.cols, nc)) {
+            if (threadIdx.x == 0 && d.cols <= kWideMaxCols) wide[atomicAdd(&bh->wide_rows, 1)] = grow;
+            continue;
+        }
+        const int arow = (int)(grow - d.row0);
         rank_num_row<V, kWideWaves>(d.Arp[arow], d.Arp[arow + 1], d.Acol, (const V *)d.Aval, d.Brp, d.Bcol,
-                                    (const V *)d.Bval, rb, (int)(Crp[grow + 1] - rb), d.cols, lds_cols, kWideCap,
-                                    threadIdx.x, s_raw, Ccol, Cval, err);
+                                    (const V *)d.Bval, rb, nc, d.cols, lds_cols, kWideCap, threadIdx.x, s_raw, Ccol,
+                                    Cval, &bh->error);
     }
 }
 
-// Numeric, heavy rows of problems with more than kRankMaxCols and at most
-// kWideMaxCols columns: one block per row takes B's columns in windows of kWideWin; in each window the
-// row's products with columns inside it are added into an LDS array of
-// doubles indexed by column (occupancy marked by the -0.0 start value, as in
-// the dense chunks of single products), and each wave ranks its share of the
-// window with ballots and stores its entries in column order through its own
-// slots (dynamic LDS: the kWideWin doubles).  Each window enumerates only the B entries inside
-// it: a row with at most kWideThreads A entries keeps, per thread, a cursor
-// into its B row that the windows advance (one search per window); longer
-// rows search both window bounds in every B row they visit.
+// Numeric, the heavy rows that k_bnum_wide_rank lists: one block per row takes
+// B's columns in windows of kWideWin; in each window the row's products with
+// columns inside it are added into an LDS array of doubles indexed by column
+// (occupancy marked by the -0.0 start value, as in the dense chunks of single
+// products), and each wave ranks its share of the window with ballots and
+// stores its entries in column order through its own slots (dynamic LDS: the
+// kWideWin doubles).  Each window enumerates only the B entries inside it: a
+// row with at most kWideThreads A entries keeps, per thread, a cursor into its
+// B row that the windows advance (one search per window); longer rows search
+// both window bounds in every B row they visit.
 template <typename V>
 __global__ __launch_bounds__(kWideThreads) void k_bnum_wide(const BatchDesc *__restrict__ desc,
-                                                            const int *__restrict__ prob, const BatchHdr *bh,
-                                                            const int *__restrict__ perm, long long ccap,
+                                                            const int *__restrict__ prob, BatchHdr *bh,
+                                                            const int *__restrict__ rows, long long ccap,
                                                             const long long *__restrict__ Crp, int *__restrict__ Ccol,
-                                                            V *__restrict__ Cval, int *err, int *queue)
+                                                            V *__restrict__ Cval)
 {
     constexpr int NW = kWideThreads / kWave;
     constexpr int CPW = kWideWin / NW;                  // columns ranked by each wave
@@ -501,20 +516,18 @@ __global__ __launch_bounds__(kWideThreads) void k_bnum_wide(const BatchDesc *__r
     __shared__ int s_wt[NW];
     __shared__ int s_r;
     if (bh->nnz_c > ccap) return;
-    const int cnt = bh->num.count[kBinHeavy];
-    const int *rows = perm + bh->num.offset[kBinHeavy];
+    const int cnt = bh->wide_rows;
     const int gt = threadIdx.x, lane = lane_id(), wg = gt / kWave;
     // heavy rows from a queue (one atomic per row): long and short rows
     // balance across the persistent blocks
     for (;;) {
         __syncthreads();                                // the previous row is done with s_r and the window
-        if (gt == 0) s_r = atomicAdd(queue, 1);
+        if (gt == 0) s_r = atomicAdd(&bh->wide_queue, 1);
         __syncthreads();
         const int r = s_r;
         if (r >= cnt) break;
         const int grow = rows[r];
         const BatchDesc &d = desc[prob[grow]];
-        if (d.cols <= kRankMaxCols || d.cols > kWideMaxCols) continue;
         const int *Acol = d.Acol, *Brp = d.Brp;
         const V *Aval = (const V *)d.Aval;
         const int arow = (int)(grow - d.row0);
@@ -577,7 +590,7 @@ __global__ __launch_bounds__(kWideThreads) void k_bnum_wide(const BatchDesc *__r
             done += tot;
             __syncthreads();
         }
-        if (gt == 0 && done != nc) atomicOr(err, kErrCount);
+        if (gt == 0 && done != nc) atomicOr(&bh->error, kErrCount);
     }
 }
 

@@ -1601,7 +1601,8 @@ __device__ __forceinline__ void rank_sym_row(int e0, int e1, const int *__restri
 }
 
 // Numeric pass of one row by a group of WPR waves: its products merged and
-// written in column order at C's offset rb (nc entries expected), cap entries
+// written in column order at C's offset rb (nc entries expected, at most 65535:
+// the bitmap's prefix counts are 16 bits wide), cap entries
 // at a time (rows of more entries repeat the second pass).  raw: rank_row_lds
 // bytes for lds_cols >= ncols columns.  Products stay in registers between the
 // passes where the row's A entries fit one list and its pieces one locating.

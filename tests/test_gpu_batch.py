@@ -287,3 +287,52 @@ def test_batch_row_bounds(env, oracle_mod, rows):
     plan.run()
     _check_plan(plan, probs, refs, oracle_mod, f"rows {rows}")
     plan.close()
+
+
+def _long_rows(n, dtype):
+    """B of n > 65536 columns with rows of 65535, 65536 (columns 0 to 65535),
+    65537 and n entries and some of 3000, and an A whose rows are B's long
+    rows alone and merged with shorter ones."""
+    allc = np.arange(n, dtype=np.int32)
+    rows = [np.delete(allc, 77)[n - 65536:], allc[:65536], np.delete(allc[:65538], 30000), allc]
+    rows += [np.sort((syn.uniform01(17 + q, 0, 6000) * n).astype(np.int32)) for q in range(6)]
+    rows = [np.unique(r)[:3000] if q > 3 else r for q, r in enumerate(rows)]
+    ptr = np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32)
+    col = np.concatenate(rows)
+    B = syn.CSR(len(rows), n, ptr, col, (2.0 * syn.uniform01(n, 0, len(col)) - 1.0).astype(dtype))
+    sets = [[0], [1], [2], [3], [0, 4], [1, 5, 6], [2, 3], [4, 5, 6, 7, 8, 9], list(range(10))]
+    aptr = np.concatenate([[0], np.cumsum([len(x) for x in sets])]).astype(np.int32)
+    acol = np.concatenate(sets).astype(np.int32)
+    A = syn.CSR(len(sets), len(rows), aptr, acol, (2.0 * syn.uniform01(5, 0, len(acol)) - 1.0).astype(dtype))
+    assert [int(np.diff(ptr)[q]) for q in range(4)] == [65535, 65536, 65537, n]
+    return A, B
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+def test_batch_long_rows(env, oracle_mod, dtype):
+    """Heavy rows of 65535 to 131072 entries: more than 16 bits count, in
+    problems narrow enough for the bitmap form of heavy rows."""
+    torch, smash, ctx = env
+    probs = [_long_rows(n, dtype) for n in (65540, 100000, 131072)]
+    refs = [oracle_mod.spgemm(A, B) for A, B in probs]
+    plan = _make_plan(smash, ctx, probs)
+    for rep in range(2):
+        plan.run()
+        _check_plan(plan, probs, refs, oracle_mod, f"long rows run {rep}")
+    plan.close()
+    A = syn.rmat(17, 16, 3, dtype)                # its longest row of A * A has more than 65536 entries
+    prods = np.diff(A.row_ptr)[A.col_idx]
+    prods = np.add.reduceat(np.append(prods, 0), A.row_ptr[:-1]) * (np.diff(A.row_ptr) > 0)
+    rows = np.sort(np.argsort(-prods)[:24]).astype(np.int64)
+    plan = _make_plan(smash, ctx, [(A, A)])
+    plan.run()
+    plan.result()
+    C = plan.problem(0)
+    ptr = C.row_ptr.cpu().numpy()
+    assert np.diff(ptr).max() > 65536
+    sel = [slice(int(ptr[r]), int(ptr[r + 1])) for r in rows]
+    check_rows(np.concatenate([[0], np.cumsum(np.diff(ptr)[rows])]),
+               np.concatenate([C.col_idx[s].cpu().numpy() for s in sel]),
+               np.concatenate([C.val[s].cpu().numpy() for s in sel]), oracle_mod.spgemm(A, A, rows=rows), dtype,
+               "rmat 17 longest rows")
+    plan.close()
