@@ -3304,7 +3304,7 @@ struct GlobalNumLds {
     PieceScratch<V, kGlobalThreads> S;
     int tmp[kGlobalThreads / kWave + 1];
     int base[kGlobalThreads];
-    int ntouched;
+    int nfront, ntouched;                  // columns in the front table and in the row's table
 };
 
 template <typename V>
@@ -3324,17 +3324,19 @@ __device__ __forceinline__ void num_global_row(const int *__restrict__ Arp, cons
         L.fkey[t] = kEmpty;
         L.fval[t] = 0.0;
     }
-    if (threadIdx.x == 0) L.ntouched = 0;
+    if (threadIdx.x == 0) L.nfront = L.ntouched = 0;
     __syncthreads();
+    int mine = 0;
     auto sink = [&](const auto &j, const auto &p, const auto &ok) {
         constexpr int N = sizeof(j) / sizeof(j[0]);
         int slot[N];
         bool far[N];
 #pragma unroll
         for (int u = 0; u < N; ++u) {
-            bool fresh;
+            bool fresh = false;
             const int f = ok[u] ? front_find(L.fkey, j[u], fresh) : 0;
             far[u] = f < 0;
+            mine += fresh;
             if (ok[u] && f >= 0) atomicAdd(&L.fval[f], p[u]);
         }
         gfind<N>(logT, j, far, slot, err, [&](int h) { return &tab[h].key; }, [&](int h) {
@@ -3348,9 +3350,11 @@ __device__ __forceinline__ void num_global_row(const int *__restrict__ Arp, cons
     };
     piece_products<V, true, G, G, 4>(Arp[arow], Arp[arow + 1], threadIdx.x, L.S, Acol, Aval, Brp, 1, 1, Bcol, Bval,
                                      sink);
+    mine = wave_sum(mine);
+    if (lane_id() == 0 && mine) atomicAdd(&L.nfront, mine);
     __syncthreads();
     // the row's entries: the front table's slots, then the list
-    const int nt = L.ntouched < nc ? L.ntouched : nc;
+    const int nt = L.ntouched < nc ? L.ntouched : nc, listed = L.nfront + nt;
     const int nf = 1 << kFrontLog;
     auto key_of = [&](int t) { return t < nf ? L.fkey[t] : gload(&tab[tab[t - nf].list].key); };
     const int top = ncols < kGlobalRankBits ? ncols : kGlobalRankBits;
@@ -3388,9 +3392,9 @@ __device__ __forceinline__ void num_global_row(const int *__restrict__ Arp, cons
         }
         done += tot;
         __syncthreads();
-        if (done >= nc || hi == ncols) break;     // every entry is out
+        if (done >= listed || hi == ncols) break;     // every entry is out
     }
-    if (threadIdx.x == 0 && done != nc) atomicOr(err, kErrCount);
+    if (threadIdx.x == 0 && (done != nc || L.nfront + L.ntouched != nc)) atomicOr(err, kErrCount);
 }
 
 // Numeric phase of heavy rows in global mode: one block per row.

@@ -111,3 +111,32 @@ def test_numeric_errors_reported_at_sync(env):
     assert e.value.status == smash.CAPACITY
     ctx.sync()
     ctx.close()
+
+
+@pytest.mark.parametrize("kept", [0, 40])
+def test_global_numeric_error_behind_first_window(env, kept):
+    """Global mode, B wider than one rank window: a C_row_ptr that holds just
+    the entries of the first window (or none, with none there) is found wrong
+    too."""
+    torch, smash = env
+    f32 = np.float32
+    n = (1 << 19) + 5000
+    first = np.arange(kept, dtype=np.int32) * 7
+    rest = (1 << 19) + np.arange(50, dtype=np.int32) * 3
+    B = syn.CSR(2, n, np.array([0, kept, kept + 50], np.int32), np.concatenate([first, rest]), np.ones(kept + 50, f32))
+    A = syn.CSR(1, 2, np.array([0, 2], np.int32), np.array([0, 1], np.int32), np.ones(2, f32))
+    dA, dB = smash.to_device(A), smash.to_device(B)
+    ctx = smash.Context(0)
+    ctx.set_option(smash.OPT_HEAVY_MODE, 1)
+    ctx.set_option(smash.OPT_LDS_ROW_MAX, 32)
+    rp = torch.empty(2, dtype=torch.int64, device="cuda")
+    assert ctx.symbolic(dA, dB, rp) == kept + 50
+    assert ctx.stats()["rows_heavy"] == 1
+    col = torch.empty(kept + 50, dtype=torch.int32, device="cuda")
+    val = torch.empty(kept + 50, dtype=torch.float32, device="cuda")
+    rp[1] = kept
+    ctx.numeric(dA, dB, rp, col, val, check=False)
+    with pytest.raises(smash.SmashError) as e:
+        ctx.sync()
+    assert e.value.status == smash.CAPACITY
+    ctx.close()
