@@ -541,15 +541,15 @@ smash_status bin_rows(smash_ctx c, hipStream_t s, const Plan &p, const unsigned 
                                                 gsize_of, p.gsz, perr(c), heavy_cap);
         });
     TRY(launch(c, K_BIN_COUNT, s, [&] {
-        k_bin_count<<<p.nblk, 256, 0, s>>>(m, bin_of, ub, wt, p.bcount, ub ? p.bprod : nullptr, wt ? p.bw : nullptr,
+        k_bin_count<kNumBins><<<p.nblk, 256, 0, s>>>(m, bin_of, ub, wt, p.bcount, ub ? p.bprod : nullptr, wt ? p.bw : nullptr,
                                            perr(c));
     }));
     TRY(launch(c, K_BIN_SCAN, s, [&] {
-        k_bin_scan<<<1, 256, 0, s>>>(p.nblk, p.bcount, ub ? p.bprod : nullptr, wt ? p.bw : nullptr, dh,
+        k_bin_scan<kNumBins><<<1, kNumBins * kWave, 0, s>>>(p.nblk, p.bcount, ub ? p.bprod : nullptr, wt ? p.bw : nullptr, dh,
                                      ub ? &c->d_hdr->products : nullptr, perr(c), heavy_cap);
     }));
     TRY(launch(c, K_SCATTER, s, [&] {
-        k_scatter<<<p.nblk, 256, 0, s>>>(m, bin_of, p.bcount, dh, perm, gsize_of, p.gsz, perr(c));
+        k_scatter<kNumBins><<<p.nblk, 256, 0, s>>>(m, bin_of, p.bcount, dh, perm, gsize_of, p.gsz, perr(c));
     }));
     return SMASH_OK;
 }
@@ -1607,11 +1607,10 @@ struct smash_batch_plan_s {
     GSlot *pool = nullptr;
     long long gcap = 0;                  // its slots
     long long cap_total = 0;             // sum of the row bounds (pool capacity)
-    int wide_words = 1;                  // LDS bitmap words of the widest problem up to kWideMaxCols
-    int max_cols = 1;                    // columns of the widest problem
+    int max_cols = 1;                    // columns of the widest problem,
+    int wide_cols = 0;                   // of the widest up to kWideMaxCols
     int rank_cols = 0;                   // and of the widest up to kRankMaxCols
-    bool any_wide = false;               // a problem of at most kWideMaxCols columns
-    bool any_window = false;             // such a problem, wide enough for a row that takes the windows
+    bool any_window = false;             // heavy rows may take the windows
     bool any_global = false;             // a problem wider than kWideMaxCols (global tables)
     // caller-owned output pool
     long long *crp = nullptr;
@@ -1658,11 +1657,11 @@ void bscan(const BPlan &p, hipStream_t s, long long n, const TIn *in, long long 
 void bbin(const BPlan &p, hipStream_t s, const unsigned char *bin_of, BinHdr *h, int *perm, bool products)
 {
     const int m = (int)p.M;
-    k_bin_count<<<p.nblk, 256, 0, s>>>(m, bin_of, products ? p.ub : nullptr, nullptr, p.bcount,
+    k_bin_count<kBatchBins><<<p.nblk, 256, 0, s>>>(m, bin_of, products ? p.ub : nullptr, nullptr, p.bcount,
                                        products ? p.bprod : nullptr, nullptr, nullptr);
-    k_bin_scan<<<1, 256, 0, s>>>(p.nblk, p.bcount, products ? p.bprod : nullptr, nullptr, h,
+    k_bin_scan<kBatchBins><<<1, kBatchBins * kWave, 0, s>>>(p.nblk, p.bcount, products ? p.bprod : nullptr, nullptr, h,
                                  products ? &p.d_hdr->products : nullptr, nullptr, -1);
-    k_scatter<<<p.nblk, 256, 0, s>>>(m, bin_of, p.bcount, h, perm, nullptr, nullptr, nullptr);
+    k_scatter<kBatchBins><<<p.nblk, 256, 0, s>>>(m, bin_of, p.bcount, h, perm, nullptr, nullptr, nullptr);
 }
 
 // clears the header and runs the per-row analysis (graph-safe)
@@ -1673,6 +1672,9 @@ void batch_analyze(const BPlan &p, hipStream_t s)
                                                             p.cfg.table_shift, p.prob, p.ub, p.cap, p.nnzc,
                                                             p.sym_bin, p.gsz);
 }
+
+// LDS bitmap words of the widest problem up to kWideMaxCols.
+size_t wide_words(const BPlan &p) { return std::max((p.wide_cols + 31) / 32, 1); }
 
 // Whether a bin's rows are merged by a column bitmap (kBatchRankCols).
 template <int LT>
@@ -1747,12 +1749,12 @@ void batch_numeric(const BPlan &p, hipStream_t s)
 {
     if (p.cfg.wide_groups) bnum_bins<V, 1>(p, s);
     else bnum_bins<V, 0>(p, s);
-    if (p.any_wide)
+    if (p.wide_cols > 0)
         k_bnum_wide_rank<V><<<bgrid(p, p.M), kWideRankThreads, rank_row_lds<V, kWideWaves>(p.rank_cols, kWideCap), s>>>(
-            p.d_desc, p.prob, p.d_hdr, p.num_perm, p.ccap, p.crp, p.rank_cols, p.ccol, (V *)p.cval, p.sym_perm);
+            p.d_desc, p.prob, p.d_hdr, p.num_perm, p.ccap, p.crp, p.rank_cols, p.ccol, (V *)p.cval);
     if (p.any_window)
         k_bnum_wide<V><<<bgrid(p, p.M), kWideThreads, kWideWin * sizeof(double), s>>>(
-            p.d_desc, p.prob, p.d_hdr, p.sym_perm, p.ccap, p.crp, p.ccol, (V *)p.cval);
+            p.d_desc, p.prob, p.d_hdr, p.num_perm, p.ccap, p.crp, p.ccol, (V *)p.cval);
     if (p.any_global)
         k_bnum_global<V><<<bgrid(p, p.M), kGlobalThreads, global_rank_lds(kGlobalRankBits), s>>>(
         p.d_desc, p.prob, p.d_hdr, p.num_perm, p.goff, p.gcap, p.pool, p.ccap, p.crp, p.ccol,
@@ -1773,15 +1775,15 @@ void batch_enqueue(const BPlan &p, hipStream_t s)
                                                                p.rd);
     if (p.cfg.wide_groups) bsym_bins<1>(p, s);
     else bsym_bins<0>(p, s);
-    k_bsym_wide<<<bgrid(p, p.M), kWideThreads, p.wide_words * sizeof(unsigned), s>>>(
+    k_bsym_wide<<<bgrid(p, p.M), kWideThreads, wide_words(p) * sizeof(unsigned), s>>>(
         p.d_desc, p.prob, &p.d_hdr->sym, p.sym_perm, p.nnzc);
     if (p.any_global)
         k_bsym_global<<<bgrid(p, p.M), kGlobalThreads, 0, s>>>(p.d_desc, p.prob, &p.d_hdr->sym, p.sym_perm, p.cap,
                                                            p.goff, p.gcap, p.pool, p.nnzc, &p.d_hdr->error);
     bscan<int>(p, s, p.M, p.nnzc, p.crp, &p.d_hdr->nnz_c);
     k_bcheck<<<1, 64, 0, s>>>(p.d_hdr, p.ccap);
-    k_bnum_bins<<<bgrid(p, blocks_for(p.M, 256)), 256, 0, s>>>(p.M, p.cfg.table_shift, p.nnzc, p.sym_bin,
-                                                               p.num_bin);
+    k_bnum_bins<<<bgrid(p, blocks_for(p.M, 256)), 256, 0, s>>>(p.M, p.cfg.table_shift, p.d_desc, p.prob, p.ub, p.nnzc,
+                                                               p.sym_bin, p.num_bin, p.any_window);
     bbin(p, s, p.num_bin, &p.d_hdr->num, p.num_perm, false);
     k_browdesc<<<bgrid(p, blocks_for(p.M, 256)), 256, 0, s>>>(p.d_desc, p.prob, &p.d_hdr->num, p.num_perm, p.crp,
                                                                p.rd);
@@ -1797,13 +1799,18 @@ smash_status batch_sync(BPlan &p, hipStream_t s)
     return SMASH_OK;
 }
 
-// sizes the global tables for the plan's configuration (analysis + scan)
+// sizes the global tables for the plan's configuration (analysis + scan), and
+// finds out whether heavy rows may take the windows: a row of more entries than
+// the bitmap form can hold has to, also if the structure changes later
 smash_status batch_size_tables(BPlan &p, hipStream_t s)
 {
     if (p.M == 0) return SMASH_OK;
     batch_analyze(p, s);
     bscan<long long>(p, s, p.M, p.gsz, p.goff, &p.d_hdr->gneed);
+    k_bwindows<<<bgrid(p, blocks_for(p.M, 256)), 256, 0, s>>>(p.M, p.d_desc, p.prob, p.ub, p.cap, p.sym_bin,
+                                                              &p.d_hdr->windows);
     TRY(batch_sync(p, s));
+    p.any_window = p.wide_cols > kWideRankMaxEntries || p.h_hdr->windows;
     const long long need = std::max<long long>(p.h_hdr->gneed, 1);
     if (need > p.gcap) {
         // larger tables from the caller's allocation callback (the caller
@@ -1876,13 +1883,8 @@ smash_status smash_batch_plan_create(smash_ctx c, smash_dtype dtype, int32_t cou
     for (int q = 0; q < count; ++q) {
         p->max_cols = std::max(p->max_cols, (int)B[q].cols);
         if (B[q].cols <= kRankMaxCols) p->rank_cols = std::max(p->rank_cols, (int)B[q].cols);
-        if (B[q].cols <= kWideMaxCols) {
-            p->any_wide = true;
-            p->any_window |= B[q].cols > kWideRankMaxEntries;
-            p->wide_words = std::max(p->wide_words, (int)((B[q].cols + 31) / 32));
-        } else {
-            p->any_global = true;
-        }
+        if (B[q].cols <= kWideMaxCols) p->wide_cols = std::max(p->wide_cols, (int)B[q].cols);
+        else p->any_global = true;
     }
     smash_status st = SMASH_OK;
     auto bail = [&](smash_status e) {
@@ -1899,7 +1901,7 @@ smash_status smash_batch_plan_create(smash_ctx c, smash_dtype dtype, int32_t cou
     const size_t need = carve_size({p->desc.size() * sizeof(BatchDesc), ((size_t)count + 1) * 8, (size_t)M * 4,
                                     (size_t)M * 8, (size_t)M * 4, (size_t)M * 4, (size_t)M, (size_t)M,
                                     (size_t)M * 8, (size_t)(M + 1) * 8, (size_t)M * 4, (size_t)M * 4,
-                                    (size_t)p->nblk * kNumBins * 4, (size_t)p->nblk * 8, (size_t)(nsb + 1) * 8,
+                                    (size_t)p->nblk * kBatchBins * 4, (size_t)p->nblk * 8, (size_t)(nsb + 1) * 8,
                                     (size_t)std::max(count, 1) * 8, sizeof(BatchHdr), (size_t)M * sizeof(RowDesc),
                                     bm_words * 4});
     // the plan's workspace and, later, its global tables come from the
@@ -1915,7 +1917,7 @@ smash_status smash_batch_plan_create(smash_ctx c, smash_dtype dtype, int32_t cou
         hipFuncSetAttribute((const void *)k_bnum_wide_rank<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)rank_row_lds<double, kWideWaves>(kRankMaxCols, kWideCap)) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bsym_wide, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(p->wide_words * sizeof(unsigned))) != hipSuccess ||
+                            (int)(wide_words(*p) * sizeof(unsigned))) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bnum_global<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)global_rank_lds(kGlobalRankBits)) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bnum_global<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1938,7 +1940,7 @@ smash_status smash_batch_plan_create(smash_ctx c, smash_dtype dtype, int32_t cou
     p->goff = cv.take<long long>(M + 1);
     p->sym_perm = cv.take<int>(M);
     p->num_perm = cv.take<int>(M);
-    p->bcount = cv.take<int>((size_t)p->nblk * kNumBins);
+    p->bcount = cv.take<int>((size_t)p->nblk * kBatchBins);
     p->bprod = cv.take<unsigned long long>(p->nblk);
     p->bsum = cv.take<long long>(nsb + 1);
     p->pnnz = cv.take<long long>(std::max(count, 1));

@@ -35,9 +35,9 @@ struct BatchHdr {
     long long nnz_c;            // total entries of all C_p
     long long gneed;            // global table slots of the heavy rows
     int error;
+    int windows;                // a heavy row may take the windowed numeric kernel (k_bwindows)
     int rank_queue;             // next heavy row of the bitmap numeric kernel
-    int wide_rows;              // heavy rows it leaves to the windowed numeric kernel
-    int wide_queue;             // next of these
+    int wide_queue;             // next heavy row of the windowed numeric kernel
 };
 
 // Heavy rows of problems with at most kWideMaxCols columns are counted with
@@ -46,6 +46,34 @@ struct BatchHdr {
 constexpr int kWideMaxCols = 1 << 20;
 constexpr int kWideWin = 8192;
 constexpr int kWideThreads = 512;
+
+// Whether a heavy row of nc entries, with `entries` A entries and `products`
+// products in a problem of `cols` columns, is merged by the column bitmap,
+// kWideCap entries at a time (k_bnum_wide_rank), or in windows (k_bnum_wide).
+// The bitmap's prefix counts are 16 bits wide, so a row of 65536 entries takes
+// the windows.  So does a row whose products the bitmap form would go through
+// too often: it does so once per kWideCap entries (the first time costs little
+// more than in the windows), where the windows take each product once, but
+// clear and scan 8192 slots per window, some 7000 products' time, and, with
+// more than kWideThreads A entries, search every selected B row twice, 10
+// products' time.  Those have to gain a third besides, since a few of them do
+// not fill a launch of their own.  Replay of 1000 rows in us, bitmap and
+// windows: 22500 products in 3000 columns 282 and 288, in 8192 columns 343 and
+// 294, in 131072 columns 517 and 449; 10000 products there 255 and 323; 8000
+// rows of 14000 products from 700 A entries, in 16384 columns 1477 and 1140, in
+// 32768 columns 1480 and 1760.  RMAT scale 16, edge factor 16, A * A: 6.7 ms
+// all by bitmap, 4.5 all in windows, 3.05 so.
+constexpr int kWideCap = 3072;
+constexpr int kWideRankThreads = 512;
+constexpr int kWideWaves = kWideRankThreads / kWave;
+constexpr int kWideRankMaxEntries = 65535;
+
+__device__ __forceinline__ bool wide_rank_row(int cols, int nc, int entries, long long products)
+{
+    const long long passes = ((unsigned)nc + kWideCap - 1) / kWideCap, windows = ((unsigned)cols + kWideWin - 1) / kWideWin;
+    const long long window = entries > kWideThreads ? 8192 + 16LL * entries : 7168;
+    return cols <= kRankMaxCols && nc <= kWideRankMaxEntries && (5 * passes - 4) * products <= 5 * windows * window;
+}
 
 // What an LDS-bin kernel needs of one row, gathered in permutation order by
 // k_browdesc so that the bin kernels read one contiguous record per row
@@ -164,17 +192,48 @@ __global__ __launch_bounds__(256) void k_banalyze(long long M, int count, const 
     if (here) finish(g, pr, ub);
 }
 
+constexpr int kWideLong = 262144;
+
+// Numeric bin of a heavy row: windows, or none of its own.
+__device__ __forceinline__ int heavy_bin(const BatchDesc &d, long long g, int nc, long long products)
+{
+    const int *rp = d.Arp + (g - d.row0);
+    if (d.cols > kWideMaxCols || wide_rank_row(d.cols, nc, rp[1] - rp[0], products)) return kBinHeavy;
+    return products > kWideLong ? kBinWinLong : kBinWin;
+}
+
+// Whether a heavy row may take the windows, from the rows' bounds (when a plan
+// is made or configured).
+__global__ __launch_bounds__(256) void k_bwindows(long long M, const BatchDesc *__restrict__ desc,
+                                                  const int *__restrict__ prob, const long long *__restrict__ ub,
+                                                  const int *__restrict__ cap,
+                                                  const unsigned char *__restrict__ sym_bin, int *windows)
+{
+    for (long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x; g < M;
+         g += (long long)gridDim.x * blockDim.x)
+        if (sym_bin[g] == kBinHeavy && heavy_bin(desc[prob[g]], g, cap[g], ub[g]) != kBinHeavy) *windows = 1;
+}
+
 // Numeric bins from the exact counts: heavy rows stay heavy, rows without
-// entries drop out, LDS rows take the class of their count.
-__global__ __launch_bounds__(256) void k_bnum_bins(long long M, int shift, const int *__restrict__ nnzc,
+// entries drop out, LDS rows take the class of their count.  Heavy rows that
+// take the windows have bins of their own (windows: whether there may be any,
+// as k_bwindows found, or rows of more entries than the bitmap form holds): those of more
+// than kWideLong products come first, as each of them keeps a block busy for
+// half a millisecond (RMAT scale 16, edge factor 16, A * A: 3.05 ms, 3.46 with
+// all of them in row order; with rows numbered from another vertex 3.14, 3.65).
+__global__ __launch_bounds__(256) void k_bnum_bins(long long M, int shift, const BatchDesc *__restrict__ desc,
+                                                   const int *__restrict__ prob, const long long *__restrict__ ub,
+                                                   const int *__restrict__ nnzc,
                                                    const unsigned char *__restrict__ sym_bin,
-                                                   unsigned char *__restrict__ num_bin)
+                                                   unsigned char *__restrict__ num_bin, bool windows)
 {
     for (long long g = (long long)blockIdx.x * blockDim.x + threadIdx.x; g < M;
          g += (long long)gridDim.x * blockDim.x) {
-        const int b = sym_bin[g], nc = nnzc[g];
-        num_bin[g] = (unsigned char)(b == kBinHeavy ? kBinHeavy
-                                                    : (b == kBinEmpty || nc == 0 ? kBinEmpty : lds_bin_shift(nc, shift)));
+        const int nc = nnzc[g];
+        int b = sym_bin[g];
+        if (b < kLdsBins) b = nc ? lds_bin_shift(nc, shift) : kBinEmpty;
+        if (windows && b == kBinHeavy) b = heavy_bin(desc[prob[g]], g, nc, ub[g]);
+        num_bin[g] = (unsigned char)b;
     }
 }
 
@@ -435,40 +494,27 @@ __global__ __launch_bounds__(kWideThreads) void k_bsym_wide(const BatchDesc *__r
     }
 }
 
-// Whether a heavy row of nc entries in a problem of `cols` columns is merged by
-// the column bitmap: rank_num_row's prefix counts are 16 bits wide, and a row
-// of 65536 entries has ranks that need one more.  Such rows take the windows.
-constexpr int kWideRankMaxEntries = 65535;
-
-__device__ __forceinline__ bool wide_rank_row(int cols, int nc)
-{
-    return cols <= kRankMaxCols && nc <= kWideRankMaxEntries;
-}
-
-// Numeric, heavy rows: one block per row (from a queue: long and short rows
-// balance across the persistent blocks) merges it by a column bitmap, kWideCap
-// entries at a time, or lists it (wide, bh->wide_rows of them) for the windows.
+// Numeric, heavy rows (but those that take the windows): one block per row
+// (from a queue: long and short rows balance across the persistent blocks; no
+// more blocks than rows use it, as thousands on one counter take 25 us) merges
+// it by a column bitmap, kWideCap entries at a time.
 // Windows of 8192 columns (below) scan every slot of every window, thousands
 // for the few hundred entries a row has there: 2.50 ms in a batch of 512
 // problems of up to 32768 columns, against 1.39 (four waves per row instead of
 // eight: 1.67; 5120 entries at a time, two blocks per CU: 1.47).
-constexpr int kWideCap = 3072;
-constexpr int kWideRankThreads = 512;
-constexpr int kWideWaves = kWideRankThreads / kWave;
-
 template <typename V>
 __global__ __launch_bounds__(kWideRankThreads) void k_bnum_wide_rank(const BatchDesc *__restrict__ desc,
                                                                  const int *__restrict__ prob, BatchHdr *bh,
                                                                  const int *__restrict__ perm, long long ccap,
                                                                  const long long *__restrict__ Crp, int lds_cols,
-                                                                 int *__restrict__ Ccol, V *__restrict__ Cval,
-                                                                 int *__restrict__ wide)
+                                                                 int *__restrict__ Ccol, V *__restrict__ Cval)
 {
     extern __shared__ __align__(16) unsigned char s_raw[];
     __shared__ int s_r;
     if (bh->nnz_c > ccap) return;
     const int cnt = bh->num.count[kBinHeavy];
     const int *rows = perm + bh->num.offset[kBinHeavy];
+    if ((int)blockIdx.x >= cnt) return;
     for (;;) {
         __syncthreads();                                // the previous row is done with s_r and the LDS
         if (threadIdx.x == 0) s_r = atomicAdd(&bh->rank_queue, 1);
@@ -477,21 +523,17 @@ __global__ __launch_bounds__(kWideRankThreads) void k_bnum_wide_rank(const Batch
         if (r >= cnt) break;
         const int grow = rows[r];
         const BatchDesc &d = desc[prob[grow]];
-        const long long rb = Crp[grow];
-        const int nc = (int)(Crp[grow + 1] - rb);
-        if (!wide_rank_row(d.cols, nc)) {
-            if (threadIdx.x == 0 && d.cols <= kWideMaxCols) wide[atomicAdd(&bh->wide_rows, 1)] = grow;
-            continue;
-        }
+        if (d.cols > kWideMaxCols) continue;
         const int arow = (int)(grow - d.row0);
+        const long long rb = Crp[grow];
         rank_num_row<V, kWideWaves>(d.Arp[arow], d.Arp[arow + 1], d.Acol, (const V *)d.Aval, d.Brp, d.Bcol,
-                                    (const V *)d.Bval, rb, nc, d.cols, lds_cols, kWideCap, threadIdx.x, s_raw, Ccol,
-                                    Cval, &bh->error);
+                                    (const V *)d.Bval, rb, (int)(Crp[grow + 1] - rb), d.cols, lds_cols, kWideCap,
+                                    threadIdx.x, s_raw, Ccol, Cval, &bh->error);
     }
 }
 
-// Numeric, the heavy rows that k_bnum_wide_rank lists: one block per row takes
-// B's columns in windows of kWideWin; in each window the row's products with
+// Numeric, the heavy rows in the windows' bins: one block per row takes B's
+// columns in windows of kWideWin; in each window the row's products with
 // columns inside it are added into an LDS array of doubles indexed by column
 // (occupancy marked by the -0.0 start value, as in the dense chunks of single
 // products), and each wave ranks its share of the window with ballots and
@@ -503,7 +545,7 @@ __global__ __launch_bounds__(kWideRankThreads) void k_bnum_wide_rank(const Batch
 template <typename V>
 __global__ __launch_bounds__(kWideThreads) void k_bnum_wide(const BatchDesc *__restrict__ desc,
                                                             const int *__restrict__ prob, BatchHdr *bh,
-                                                            const int *__restrict__ rows, long long ccap,
+                                                            const int *__restrict__ perm, long long ccap,
                                                             const long long *__restrict__ Crp, int *__restrict__ Ccol,
                                                             V *__restrict__ Cval)
 {
@@ -516,10 +558,11 @@ __global__ __launch_bounds__(kWideThreads) void k_bnum_wide(const BatchDesc *__r
     __shared__ int s_wt[NW];
     __shared__ int s_r;
     if (bh->nnz_c > ccap) return;
-    const int cnt = bh->wide_rows;
+    const int cnt = bh->num.count[kBinWinLong] + bh->num.count[kBinWin];
+    const int *rows = perm + bh->num.offset[kBinWinLong];
     const int gt = threadIdx.x, lane = lane_id(), wg = gt / kWave;
-    // heavy rows from a queue (one atomic per row): long and short rows
-    // balance across the persistent blocks
+    // heavy rows from a queue, as above
+    if ((int)blockIdx.x >= cnt) return;
     for (;;) {
         __syncthreads();                                // the previous row is done with s_r and the window
         if (gt == 0) s_r = atomicAdd(&bh->wide_queue, 1);

@@ -53,6 +53,9 @@ constexpr int kLdsBins = kMaxLogT - kMinLogT + 1;
 constexpr int kBinHeavy = kLdsBins;
 constexpr int kBinEmpty = kLdsBins + 1;
 constexpr int kNumBins = kLdsBins + 2;
+constexpr int kBinWinLong = kNumBins;     // a batch's heavy rows that take column windows: long ones
+constexpr int kBinWin = kNumBins + 1;     // and the others
+constexpr int kBatchBins = kNumBins + 2;
 constexpr int kChunkCols = 8192;        // column granularity of heavy-row counts
 constexpr int kChunkWords = kChunkCols / 32;
 constexpr int kSymWinChunks = 16;       // symbolic heavy window: 16 chunks, 16 KiB bitmap
@@ -83,9 +86,9 @@ __device__ __forceinline__ bool stopped(const int *err)
 }
 
 struct BinHdr {
-    long long wsum[kNumBins]; // sum of the per-row weights (output entries) per bin
-    int count[kNumBins];      // rows per bin
-    int offset[kNumBins + 1]; // exclusive offsets of the bins in the row permutation
+    long long wsum[kBatchBins]; // sum of the per-row weights (output entries) per bin
+    int count[kBatchBins];      // rows per bin
+    int offset[kBatchBins + 1]; // exclusive offsets of the bins in the row permutation
 };
 
 struct SegHdr {
@@ -1340,19 +1343,20 @@ __global__ __launch_bounds__(256) void k_num_bins(int m, const int *__restrict__
 }
 
 // Per-block bin histograms (kBinBlockRows rows per block, no global atomics):
-// bcount[blk * kNumBins + b], the block's per-bin sum of the row weights wt
+// bcount[blk * NB + b], the block's per-bin sum of the row weights wt
 // (bw, when wt is given) and the block's sum of products (bprod, when ub is
 // given).
+template <int NB>
 __global__ __launch_bounds__(256) void k_bin_count(int m, const unsigned char *__restrict__ bin_of,
                                                    const long long *__restrict__ ub, const int *__restrict__ wt,
                                                    int *__restrict__ bcount, unsigned long long *__restrict__ bprod,
                                                    long long *__restrict__ bw, const int *err)
 {
     if (stopped(err)) return;
-    __shared__ int s_hist[kNumBins];
-    __shared__ unsigned long long s_w[kNumBins];
+    __shared__ int s_hist[NB];
+    __shared__ unsigned long long s_w[NB];
     __shared__ unsigned long long s_prod;
-    if (threadIdx.x < kNumBins) {
+    if (threadIdx.x < NB) {
         s_hist[threadIdx.x] = 0;
         s_w[threadIdx.x] = 0;
     }
@@ -1371,15 +1375,17 @@ __global__ __launch_bounds__(256) void k_bin_count(int m, const unsigned char *_
     prod = wave_sum(prod);
     if (lane_id() == 0 && prod) atomicAdd(&s_prod, prod);
     __syncthreads();
-    if (threadIdx.x < kNumBins) {
-        bcount[blockIdx.x * kNumBins + threadIdx.x] = s_hist[threadIdx.x];
-        if (bw) bw[blockIdx.x * kNumBins + threadIdx.x] = (long long)s_w[threadIdx.x];
+    if (threadIdx.x < NB) {
+        bcount[blockIdx.x * NB + threadIdx.x] = s_hist[threadIdx.x];
+        if (bw) bw[blockIdx.x * NB + threadIdx.x] = (long long)s_w[threadIdx.x];
     }
     if (threadIdx.x == 0 && bprod) bprod[blockIdx.x] = s_prod;
 }
 
-// Bin totals and offsets, and every block's base inside each bin (one block).
-__global__ __launch_bounds__(256) void k_bin_scan(int nblk, int *__restrict__ bcount,
+// Bin totals and offsets, and every block's base inside each bin (one block of
+// a wave per bin).
+template <int NB>
+__global__ __launch_bounds__(NB *kWave) void k_bin_scan(int nblk, int *__restrict__ bcount,
                                                   const unsigned long long *__restrict__ bprod,
                                                   const long long *__restrict__ bw, BinHdr *h,
                                                   unsigned long long *products, int *err, long long heavy_cap)
@@ -1387,22 +1393,23 @@ __global__ __launch_bounds__(256) void k_bin_scan(int nblk, int *__restrict__ bc
     // err: with heavy_cap >= 0, more heavy rows than the workspace holds
     // raise kErrCapacity (every later kernel of the pipeline then stops)
     if (stopped(err)) return;
-    __shared__ int s_tot[kNumBins];
-    __shared__ long long s_wt[kNumBins];
+    __shared__ int s_tot[NB];
+    __shared__ long long s_wt[NB];
     // one wave per bin scans the block counts in place (exclusive)
     const int lane = lane_id(), wave = threadIdx.x / kWave;
-    for (int b = wave; b < kNumBins; b += 256 / kWave) {
+    {
+        const int b = wave;
         int run = 0;
         for (int c0 = 0; c0 < nblk; c0 += kWave) {
             const int c = c0 + lane;
-            const int v = c < nblk ? bcount[c * kNumBins + b] : 0;
+            const int v = c < nblk ? bcount[c * NB + b] : 0;
             const int incl = wave_incl_scan(v);
-            if (c < nblk) bcount[c * kNumBins + b] = run + incl - v;
+            if (c < nblk) bcount[c * NB + b] = run + incl - v;
             run += __shfl(incl, kWave - 1, kWave);
         }
         long long ws = 0;
         if (bw)
-            for (int c = lane; c < nblk; c += kWave) ws += bw[c * kNumBins + b];
+            for (int c = lane; c < nblk; c += kWave) ws += bw[c * NB + b];
         ws = wave_sum(ws);
         if (lane == 0) {
             s_tot[b] = run;
@@ -1411,21 +1418,25 @@ __global__ __launch_bounds__(256) void k_bin_scan(int nblk, int *__restrict__ bc
     }
     unsigned long long p = 0;
     if (bprod)
-        for (int c = threadIdx.x; c < nblk; c += 256) p += bprod[c];
+        for (int c = threadIdx.x; c < nblk; c += NB * kWave) p += bprod[c];
     p = wave_sum(p);
-    __shared__ unsigned long long s_p[4];
+    __shared__ unsigned long long s_p[NB];
     if (lane == 0) s_p[wave] = p;
     __syncthreads();
     if (threadIdx.x == 0) {
         int run = 0;
-        for (int b = 0; b < kNumBins; ++b) {
+        for (int b = 0; b < NB; ++b) {
             h->count[b] = s_tot[b];
             h->wsum[b] = s_wt[b];
             h->offset[b] = run;
             run += s_tot[b];
         }
-        h->offset[kNumBins] = run;
-        if (bprod && products) *products = s_p[0] + s_p[1] + s_p[2] + s_p[3];
+        h->offset[NB] = run;
+        if (bprod && products) {
+            unsigned long long sum = 0;
+            for (int w = 0; w < NB; ++w) sum += s_p[w];
+            *products = sum;
+        }
         if (err && heavy_cap >= 0 && s_tot[kBinHeavy] > heavy_cap) atomicOr(err, kErrCapacity);
     }
 }
@@ -1433,14 +1444,15 @@ __global__ __launch_bounds__(256) void k_bin_scan(int nblk, int *__restrict__ bc
 // Groups row ids by bin (empty rows are left out): perm[offset[b] + block base
 // + rank in block].  For the heavy bin, also records the row's global-hash
 // table size (gsz, by heavy index) when gsize_of is given.
+template <int NB>
 __global__ __launch_bounds__(256) void k_scatter(int m, const unsigned char *__restrict__ bin_of,
                                                  const int *__restrict__ bbase, const BinHdr *h,
                                                  int *__restrict__ perm, const int *__restrict__ gsize_of,
                                                  long long *__restrict__ gsz, const int *err)
 {
     if (stopped(err)) return;
-    __shared__ int s_cnt[kNumBins];
-    if (threadIdx.x < kNumBins) s_cnt[threadIdx.x] = 0;
+    __shared__ int s_cnt[NB];
+    if (threadIdx.x < NB) s_cnt[threadIdx.x] = 0;
     __syncthreads();
     for (int r = threadIdx.x; r < kBinBlockRows; r += 256) {
         const long long i = (long long)blockIdx.x * kBinBlockRows + r;
@@ -1448,7 +1460,7 @@ __global__ __launch_bounds__(256) void k_scatter(int m, const unsigned char *__r
         const int b = bin_of[i];
         const int local = atomicAdd(&s_cnt[b], 1);
         if (b == kBinEmpty) continue;
-        const int pos = h->offset[b] + bbase[blockIdx.x * kNumBins + b] + local;
+        const int pos = h->offset[b] + bbase[blockIdx.x * NB + b] + local;
         perm[pos] = (int)i;
         if (b == kBinHeavy && gsize_of) gsz[pos - h->offset[kBinHeavy]] = 1LL << gtable_log2(gsize_of[i]);
     }

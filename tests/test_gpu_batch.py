@@ -336,3 +336,32 @@ def test_batch_long_rows(env, oracle_mod, dtype):
                np.concatenate([C.val[s].cpu().numpy() for s in sel]), oracle_mod.spgemm(A, A, rows=rows), dtype,
                "rmat 17 longest rows")
     plan.close()
+
+
+@pytest.mark.parametrize("widths", [(3000,), (8193, 16384), (40000, 300, (1 << 20) + 5)])
+def test_batch_windows_rule(env, oracle_mod, widths):
+    """Heavy rows on both sides of the line between bitmap and windows (few and
+    many products; at most 512 A entries and more; over 262144 products), next
+    to light rows, problems without any, and rows in global tables; replayed."""
+    torch, smash, ctx = env
+    probs = []
+    for q, n in enumerate(widths):
+        B = syn.uniform_k_per_row(1200, n, 150, 40 + q, np.float32)
+        lens = [8, 30, 100, 150, 512, 513, 1100, 2, 0] if n > 1000 else [1, 2]
+        if n > 1 << 20:
+            lens = [40, 3]
+        if q == 0:
+            B = syn.uniform_k_per_row(1200, n, 400, 50, np.float32)
+        ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        col = np.concatenate([np.arange(k) + 7 * i for i, k in enumerate(lens)]).astype(np.int32)
+        probs.append((syn.CSR(len(lens), 1200, ptr, col, (2.0 * syn.uniform01(9, 0, len(col)) - 1.0).astype(np.float32)), B))
+    refs = [oracle_mod.spgemm(A, B) for A, B in probs]
+    plan = _make_plan(smash, ctx, probs)
+    stream = torch.cuda.Stream()
+    plan.capture(stream)
+    for rep in range(3):
+        plan.C_col.fill_(-7)
+        torch.cuda.synchronize()
+        plan.launch(stream)
+        _check_plan(plan, probs, refs, oracle_mod, f"widths {widths} replay {rep}", stream)
+    plan.close()
