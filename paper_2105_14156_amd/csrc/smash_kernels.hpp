@@ -1113,9 +1113,13 @@ __device__ __forceinline__ float row_feature(int t, int na, long long ub, double
 // at lie an odd stride apart, since hub rows come in clusters (consecutive
 // rows in RMAT matrices).  RMAT scale 21, edge factor 8 (rows of up to 40K
 // entries): 0.23 ms; with eight consecutive rows per wave, long ones summed by
-// the wave in turn, 0.58.  A limit of 32 or 64 entries: 0.24 and 0.23.
+// the wave in turn, 0.58.  The limit: a wave has at most a few entries per lane
+// of rows just above it and waits for each row's gathers in turn (features of a
+// million rows of 150 entries with a limit of 128: 0.93 ms, 256: 0.67), eight
+// lanes take longer with longer rows (RMAT scale 20, edge factor 8: 0.150 ms,
+// 512: 0.176).
 constexpr int kRowLanes = 8;
-constexpr int kShortRow = 128;
+constexpr int kShortRow = 256;
 constexpr int kRowThreads = 256;
 constexpr int kBlockRows = kRowThreads / kRowLanes;
 
@@ -1146,15 +1150,7 @@ __device__ __forceinline__ void row_part(const int *__restrict__ Acol, const int
             }
         }
     }
-    for (; e < e1; e += step) {
-        const int len = Brp[Acol[e] + 1] - Brp[Acol[e]];
-        r.ub += len;
-        if constexpr (FEATS) {
-            r.sq += (double)len * (double)len;
-            r.mx = len > r.mx ? len : r.mx;
-            r.mn = len < r.mn ? len : r.mn;
-        }
-    }
+    if constexpr (U > 1) row_part<FEATS, U / 2>(Acol, Brp, e, e1, step, r);
 }
 
 // Reduction of RowPart over lanes that differ in the bits of `width - 1`.
@@ -1198,8 +1194,16 @@ __device__ __forceinline__ RowPart wave_rows(int e0, int e1, const int *__restri
 
 // Blocks for the long rows and for all rows of an analysis of m rows; the long
 // ones come first in the grid.  All but one of the long blocks' waves look at
-// rows, 64 each (an odd number of waves is the stride).
-__host__ __device__ __forceinline__ int long_row_blocks(int m) { return (int)(((long long)m + kWave - 1) / kRowThreads) + 1; }
+// rows (an odd number of waves is the stride): 64 each from a million rows on,
+// and fewer where that is too few waves for rows that may all be long.
+// Features of 8192 rows of 1000 entries: 51 us, with 64 rows a wave 303; of 400
+// rows of 30000 entries 58 and 2040.
+__host__ __device__ __forceinline__ int long_row_blocks(int m)
+{
+    const int k = 31 - __builtin_clz(m | 1);
+    const int per = k >= 20 ? 6 : k >= 16 ? k - 14 : k >= 14 ? 2 : k >= 12 ? k - 12 : 0;      // log2 rows per wave
+    return (int)((((long long)m + (1 << per) - 1) >> per) / (kRowThreads / kWave)) + 1;
+}
 __host__ __device__ __forceinline__ int row_blocks(int m)
 {
     return long_row_blocks(m) + (m + kBlockRows - 1) / kBlockRows;

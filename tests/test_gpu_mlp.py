@@ -54,6 +54,25 @@ def test_features_row_split(env, m):
     np.testing.assert_allclose(F, mlp.features(X, Y), rtol=2e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("m", [1, 400, 4095, 4096, 16383, 16384, 65536, 131073])
+def test_features_long_row_split(env, m):
+    """Rows at the limit between eight lanes and a wave (256 entries) and long
+    ones at every number of rows that a wave looks at (1 to 64, by m)."""
+    torch, smash, ctx = env
+    lens = np.array([257, 1, 0, 255, 2, 256, 3, 1500])[(np.arange(m) + 7) % 8]
+    if m > 5000:
+        lens = np.where(np.arange(m) % 41 == 0, lens, np.arange(m) % 4)
+    lens[-1] = 300
+    cols = 2500
+    ptr = np.zeros(m + 1, np.int32)
+    ptr[1:] = np.cumsum(lens)
+    col = (np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens) + np.repeat(np.arange(m) % 900, lens)).astype(np.int32)
+    X = syn.CSR(m, cols, ptr, col, np.ones(len(col), np.float32))
+    Y = syn.rmat_rect(cols, 4, 9, np.float32)
+    F = ctx.features(smash.to_device(X), smash.to_device(Y)).cpu().numpy()
+    np.testing.assert_allclose(F, mlp.features(X, Y), rtol=2e-6, atol=1e-6)
+
+
 def _setup(torch, n=3000, seed=3):
     F = np.abs(syn.normal01(seed, 0, n * 6).reshape(n, 6)) * 4
     y = F[:, 1] * 0.7 + np.sin(F[:, 0]) + 0.1 * syn.normal01(seed + 1, 0, n)
