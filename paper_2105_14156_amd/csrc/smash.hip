@@ -435,7 +435,7 @@ smash_status launch_sym_bin(smash_ctx c, hipStream_t s, const Plan &p)
 {
     using S = BinShape<LOGT>;
     if constexpr (LOGT >= 8)
-        if (rank_bin<LOGT>(p)) {
+        if (rank_bin<LOGT>(p) && !short_ranges(3, p.B.nnz, p.B.rows)) {
             auto kern = k_sym_rank_rows<S::WPR, S::RPW>;
             const size_t lds = S::RPW * rank_sym_lds<S::WPR>((int)p.n);
             const int res = resident_blocks(c, (const void *)kern, S::THREADS, lds);
@@ -459,7 +459,8 @@ smash_status launch_num_bin(smash_ctx c, hipStream_t s, const Plan &p, int cnt, 
 {
     using S = BinShape<LOGT>;
     if constexpr (LOGT >= 8)
-        if (rank_bin<LOGT>(p) && !p.row_hash) {
+        if (rank_bin<LOGT>(p) && !p.row_hash &&
+            !short_ranges(LOGT == 8 && p.n <= 4096 ? 9 : 7, (long long)p.hdr.products, p.A.nnz)) {
             constexpr int cap = 1 << (LOGT - 1);
             const size_t lds = S::RPW * rank_row_lds<V, S::WPR>((int)p.n, cap);
             return launch(c, K_NUM_ROWS, s, [&] {
@@ -595,7 +596,10 @@ smash_status numeric_impl(smash_ctx c, hipStream_t s, const Plan &p, const V *Av
         // segments of up to 128 entries are hashed by one wave (table of 256
         // slots), larger ones ranked
         TRY(launch_seg_bin<V, 8, 64>(c, s, p, 0, Aval, Bval, crp, ccol, cval));
-        if (const int nr = p.hdr.seg.count[1]) {
+        const int nr = p.hdr.seg.count[1];
+        if (nr && short_ranges(7, (long long)p.hdr.products, p.A.nnz)) {
+            TRY(launch_seg_bin<V, 12, 512>(c, s, p, 1, Aval, Bval, crp, ccol, cval));
+        } else if (nr) {
             const int grid = std::min(nr, resident_blocks(c, (const void *)k_num_rank<V>, kRankThreads, 0));
             TRY(launch(c, K_NUM_SEG, s, [&] {
                 k_num_rank<V><<<grid, kRankThreads, 0, s>>>(p.A.col_idx, Aval, p.B.col_idx, Bval, p.bsplit,
@@ -1703,7 +1707,8 @@ template <typename V, int LT, int WIDE>
 void bnum_bin(const BPlan &p, hipStream_t s)
 {
     if constexpr (LT >= 8)
-        if (batch_rank_bin<LT>(p) && !p.cfg.row_hash) {
+        if (batch_rank_bin<LT>(p) && !p.cfg.row_hash &&
+            !short_ranges(p.max_cols <= kRankColsPerSlot << LT ? 7 : LT == 9 ? 5 : 3, (long long)p.products, p.nnz_a)) {
             using S = BinShape<LT>;
             constexpr int cap = 1 << (LT - 1);
             k_bnum_rank_rows<V, S::WPR, S::RPW>

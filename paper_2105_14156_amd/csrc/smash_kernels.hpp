@@ -1562,6 +1562,22 @@ constexpr int kRankColsPerSlot = 64;
 constexpr int kRankPiece = 8;
 constexpr int kRankMaxCols = kRankColsPerSlot << kMaxLogT;      // 2^17: 16-bit columns and one bit more
 
+// Whether a product's A entries select so few products each (products per
+// entry below halves / 2, on average) that most lanes of a piece are idle, and
+// the hashed forms, which take a product per lane, are faster.  Single product,
+// numeric pass of light rows of B rows of one length, hashed and by bitmap:
+// length 1, 4096 columns, rows of 220: 0.75 and 1.03 ms a call; length 3: 0.48 and
+// 0.55; length 4: 0.43 and 0.36 (rows of 100, whose table is ranked by as few
+// words: 0.50 and 0.51; 60 entries of length 4 in 128 columns: 0.52 and 0.57).
+// The symbolic pass is ahead by bitmap from length 2 on.  In batches wider
+// than kRankColsPerSlot columns a slot the hashed form has to sort: rows of 450,
+// 131072 columns, length 1: 1.61 and 1.78, length 2: 1.27 and 1.02; rows of
+// 220, 65536 columns, whose blocks hold 64 KB by bitmap, length 2: 0.86 and 0.98,
+// length 3: 0.87 both.  Ranked segments of heavy rows take the row's entries
+// twice where they do not fit one list: rows of 3000, length 1, 200000
+// columns: 1.83 ms a call hashed in tables of 4096 slots, 3.40 ranked.
+inline bool short_ranges(int halves, long long products, long long entries) { return 2 * products < halves * entries; }
+
 __host__ __device__ __forceinline__ int rank_words(int ncols) { return ((ncols + 31) / 32 + 7) & ~7; }
 
 // LDS of one group of WPR waves (a multiple of 16): bitmap, prefix counts,

@@ -365,3 +365,23 @@ def test_batch_windows_rule(env, oracle_mod, widths):
         plan.launch(stream)
         _check_plan(plan, probs, refs, oracle_mod, f"widths {widths} replay {rep}", stream)
     plan.close()
+
+
+@pytest.mark.parametrize("n,per_row", [(4096, 1), (32768, 2), (65536, 2), (65536, 3), (131072, 1), (131072, 3)])
+def test_batch_short_b_rows(env, oracle_mod, n, per_row):
+    """B rows of one to three entries, on both sides of the lines between hash
+    tables and bitmaps, in batches of one width."""
+    torch, smash, ctx = env
+    probs = []
+    for q in range(3):
+        B = syn.uniform_k_per_row(5000, n, per_row, 30 + q, np.float32)
+        lens = np.array([2, 40, 70, 110, 230, 470, 950, 3000])[(np.arange(64) + q) % 8] // per_row
+        ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        col = np.concatenate([np.arange(m) + 31 * i for i, m in enumerate(lens)]).astype(np.int32)
+        probs.append((syn.CSR(64, 5000, ptr, col, (2.0 * syn.uniform01(q, 0, len(col)) - 1.0).astype(np.float32)), B))
+    refs = [oracle_mod.spgemm(A, B) for A, B in probs]
+    plan = _make_plan(smash, ctx, probs)
+    for rep in range(2):
+        plan.run()
+        _check_plan(plan, probs, refs, oracle_mod, f"{n} columns, {per_row} per row, run {rep}")
+    plan.close()

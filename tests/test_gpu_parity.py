@@ -612,3 +612,25 @@ def test_rank_row_edges(sm, ctx, oracle_mod, dtype, n):
     A, B = _rank_row_edges(dtype, n)
     full_check(sm, ctx, A, B, dtype, oracle_mod, False, f"rank rows n={n}")
     assert A.rows > 8192 and ctx.stats()["rows_lds"] == A.rows, ctx.stats()
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n,per_row", [(4096, 1), (4096, 3), (4097, 4), (16384, 4), (65536, 1), (131072, 2), (1 << 20, 1), (1 << 20, 3)])
+def test_short_b_rows(sm, ctx, oracle_mod, dtype, n, per_row):
+    """B rows of one to four entries, on both sides of the lines between the
+    hashed forms and the bitmaps: light rows of every table, heavy rows whose
+    segments hold up to 2048 entries in 16 chunks, lists of A entries longer
+    than a block's step, more rows than go in one launch and fewer."""
+    k = 12_000
+    B = syn.uniform_k_per_row(k, n, per_row, 77, dtype)
+    for rows in (60, 8200):
+        lens = np.array([3, 30, 60, 100, 200, 400, 900, 2500, 0, 11_000])[np.arange(rows) % 10]
+        if rows > 100:
+            lens = np.where(np.arange(rows) % 40 < 10, lens, 2)
+        lens = lens // per_row
+        ptr = np.zeros(rows + 1, np.int32)
+        ptr[1:] = np.cumsum(lens)
+        step = np.where(lens > 3000, 1, 1 + np.arange(rows) % 3)
+        col = ((np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens)) * np.repeat(step, lens)).astype(np.int32)
+        A = syn.CSR(rows, k, ptr, col, (2.0 * syn.uniform01(6, 0, len(col)) - 1.0).astype(dtype))
+        full_check(sm, ctx, A, B, dtype, oracle_mod, rows == 60, f"{rows} rows, {n} columns, {per_row} per row")
