@@ -423,11 +423,39 @@ unsigned persistent_grid(smash_ctx c, K kernel, int threads, int rpw, long long 
 }
 
 // Whether the rows of a bin are merged by a column bitmap (kRankColsPerSlot):
-// tables of 256 slots on (smaller rows mostly merge in registers).
+// tables of 256 slots on (smaller rows mostly merge in registers), and B not so
+// narrow that the marks of a wave meet in the same few words: 440 products per
+// row in 80 columns 0.56 ms a call by bitmap, 0.40 hashed; in 128 0.53 and 0.40.
 template <int LOGT>
 bool rank_bin(const Plan &p)
 {
-    return LOGT >= 8 && p.n <= ((int64_t)kRankColsPerSlot << LOGT);
+    return LOGT >= 8 && p.n > 128 && p.n <= ((int64_t)kRankColsPerSlot << LOGT);
+}
+
+// The same for the numeric pass, which knows the product's size: not with
+// short B ranges, nor where the average row, in a B too narrow for heavy rows,
+// has more products than its waves hold (64 pieces each, some 416 products), so
+// that the bitmap form loads them twice: 440 products in 256 columns 0.51 ms a
+// call by bitmap and 0.46 hashed, 400 in 200 columns 1.13 and 1.33; 900 in 512
+// columns (two waves) 0.50 and 0.44, in 1024 (four) 0.53 and 0.62.
+template <int LOGT>
+bool rank_num_bin(const Plan &p)
+{
+    const long long products = (long long)p.hdr.products;
+    return rank_bin<LOGT>(p) && !p.row_hash && !short_ranges(LOGT == 8 && p.n <= 4096 ? 9 : 7, products, p.A.nnz) &&
+           (LOGT > 8 || p.n > 256) && (p.n > 1024 || products <= 416LL * BinShape<LOGT>::WPR * p.m);
+}
+
+// Whether rows of the smallest tables are worth an attempt by small_row: with B
+// of at most 64 columns they may have any number of products, and an attempt
+// that fails has read their entries and bounds in vain (16 entries times B rows
+// of 8 in 64 columns: 0.77 ms a call, 0.71 without).  `products`: their number,
+// or an estimate of it.
+bool try_small(const Plan &p, double products) { return p.n > kWave || products <= (double)kWave * p.m; }
+
+double expected_products(const Plan &p)
+{
+    return (double)p.A.nnz * (double)p.B.nnz / (double)std::max<int64_t>(p.B.rows, 1);
 }
 
 template <int LOGT>
@@ -445,12 +473,16 @@ smash_status launch_sym_bin(smash_ctx c, hipStream_t s, const Plan &p)
                                                    &c->d_hdr->sym, LOGT - kMinLogT, (int)p.n, p.nnzc, perr(c));
             });
         }
-    auto kern = k_sym_rows<LOGT, S::WPR, S::RPW>;
-    const unsigned grid = persistent_grid(c, kern, S::THREADS, S::RPW, p.m);
-    return launch(c, K_SYM_ROWS, s, [&] {
-        kern<<<grid, S::THREADS, 0, s>>>(p.A.row_ptr, p.A.col_idx, p.B.row_ptr, p.B.col_idx, p.sym_perm,
-                                         &c->d_hdr->sym, LOGT - kMinLogT, (int)p.n, p.nnzc, perr(c));
-    });
+    auto run = [&](auto kern) {
+        const unsigned grid = persistent_grid(c, kern, S::THREADS, S::RPW, p.m);
+        return launch(c, K_SYM_ROWS, s, [&] {
+            kern<<<grid, S::THREADS, 0, s>>>(p.A.row_ptr, p.A.col_idx, p.B.row_ptr, p.B.col_idx, p.sym_perm,
+                                             &c->d_hdr->sym, LOGT - kMinLogT, (int)p.n, p.nnzc, perr(c));
+        });
+    };
+    if constexpr (LOGT <= kSmallLogT)
+        if (!try_small(p, expected_products(p))) return run(k_sym_rows<LOGT, S::WPR, S::RPW, false>);
+    return run(k_sym_rows<LOGT, S::WPR, S::RPW>);
 }
 
 template <typename V, int LOGT>
@@ -459,8 +491,7 @@ smash_status launch_num_bin(smash_ctx c, hipStream_t s, const Plan &p, int cnt, 
 {
     using S = BinShape<LOGT>;
     if constexpr (LOGT >= 8)
-        if (rank_bin<LOGT>(p) && !p.row_hash &&
-            !short_ranges(LOGT == 8 && p.n <= 4096 ? 9 : 7, (long long)p.hdr.products, p.A.nnz)) {
+        if (rank_num_bin<LOGT>(p)) {
             constexpr int cap = 1 << (LOGT - 1);
             const size_t lds = S::RPW * rank_row_lds<V, S::WPR>((int)p.n, cap);
             return launch(c, K_NUM_ROWS, s, [&] {
@@ -469,16 +500,17 @@ smash_status launch_num_bin(smash_ctx c, hipStream_t s, const Plan &p, int cnt, 
                     ccol, cval, (int)p.n, cap, c->d_numerr);
             });
         }
-    return launch(c, K_NUM_ROWS, s, [&] {
-        if (p.row_hash)
-            k_num_rows<V, LOGT, S::WPR, S::RPW, 1><<<blocks_for(cnt, S::RPW), S::THREADS, 0, s>>>(
-                p.A.row_ptr, p.A.col_idx, Aval, p.B.row_ptr, p.B.col_idx, Bval, rows, cnt, (const long long *)crp,
-                ccol, cval, (int)p.n, c->d_numerr);
-        else
-            k_num_rows<V, LOGT, S::WPR, S::RPW, 0><<<blocks_for(cnt, S::RPW), S::THREADS, 0, s>>>(
-                p.A.row_ptr, p.A.col_idx, Aval, p.B.row_ptr, p.B.col_idx, Bval, rows, cnt, (const long long *)crp,
-                ccol, cval, (int)p.n, c->d_numerr);
-    });
+    auto run = [&](auto kern) {
+        return launch(c, K_NUM_ROWS, s, [&] {
+            kern<<<blocks_for(cnt, S::RPW), S::THREADS, 0, s>>>(p.A.row_ptr, p.A.col_idx, Aval, p.B.row_ptr, p.B.col_idx,
+                                                               Bval, rows, cnt, (const long long *)crp, ccol, cval,
+                                                               (int)p.n, c->d_numerr);
+        });
+    };
+    if (p.row_hash) return run(k_num_rows<V, LOGT, S::WPR, S::RPW, 1>);
+    if constexpr (LOGT <= kSmallLogT)
+        if (!try_small(p, (double)p.hdr.products)) return run(k_num_rows<V, LOGT, S::WPR, S::RPW, 0, false>);
+    return run(k_num_rows<V, LOGT, S::WPR, S::RPW, 0>);
 }
 
 // Symbolic light rows: every bin is launched (its size is on the device).
@@ -1680,12 +1712,29 @@ void batch_analyze(const BPlan &p, hipStream_t s)
 // LDS bitmap words of the widest problem up to kWideMaxCols.
 size_t wide_words(const BPlan &p) { return std::max((p.wide_cols + 31) / 32, 1); }
 
-// Whether a bin's rows are merged by a column bitmap (kBatchRankCols).
+// Whether a bin's rows are merged by a column bitmap (kBatchRankCols), and not
+// in the few words of a narrow B (rank_bin).
 template <int LT>
 bool batch_rank_bin(const BPlan &p)
 {
-    return LT >= 8 && p.max_cols <= std::min<long long>((long long)kBatchRankCols << LT, kRankMaxCols);
+    return LT >= 8 && p.max_cols > 128 && p.max_cols <= std::min<long long>((long long)kBatchRankCols << LT, kRankMaxCols);
 }
+
+// The same for the numeric pass (rank_num_bin).  Hashed rows of 1024 slots have
+// one wave here, so those stay with the bitmap whatever they hold: 3000 products
+// in 512 columns 0.78 ms a replay, 0.82 hashed; in 256 columns 0.73 and 0.57, in
+// 1024 0.85 and 0.73.
+template <int LT>
+bool batch_rank_num_bin(const BPlan &p)
+{
+    const long long products = (long long)p.products;
+    const int halves = p.max_cols <= kRankColsPerSlot << LT ? 7 : LT == 9 ? 5 : 3;
+    return batch_rank_bin<LT>(p) && !p.cfg.row_hash && !short_ranges(halves, products, p.nnz_a) &&
+           (p.max_cols > 1024 || LT == 10 || products <= 416LL * BinShape<LT>::WPR * p.M);
+}
+
+// Whether rows of the smallest tables are worth an attempt by small_row.
+bool batch_try_small(const BPlan &p) { return p.max_cols > kWave || (long long)p.products <= kWave * p.M; }
 
 template <int LT, int WIDE>
 void bsym_bin(const BPlan &p, hipStream_t s)
@@ -1699,16 +1748,20 @@ void bsym_bin(const BPlan &p, hipStream_t s)
             return;
         }
     using S = BShape<LT, WIDE>;
-    k_bsym_rows<LT, S::WPR, S::RPW><<<bgrid(p, blocks_for(p.M, S::RPW)), S::THREADS, 0, s>>>(
-        p.d_desc, p.rd, &p.d_hdr->sym, LT - kMinLogT, p.nnzc, &p.d_hdr->error);
+    auto run = [&](auto kern) {
+        kern<<<bgrid(p, blocks_for(p.M, S::RPW)), S::THREADS, 0, s>>>(p.d_desc, p.rd, &p.d_hdr->sym, LT - kMinLogT,
+                                                                      p.nnzc, &p.d_hdr->error);
+    };
+    if constexpr (LT <= kSmallLogT)
+        if (!batch_try_small(p)) return run(k_bsym_rows<LT, S::WPR, S::RPW, false>);
+    run(k_bsym_rows<LT, S::WPR, S::RPW>);
 }
 
 template <typename V, int LT, int WIDE>
 void bnum_bin(const BPlan &p, hipStream_t s)
 {
     if constexpr (LT >= 8)
-        if (batch_rank_bin<LT>(p) && !p.cfg.row_hash &&
-            !short_ranges(p.max_cols <= kRankColsPerSlot << LT ? 7 : LT == 9 ? 5 : 3, (long long)p.products, p.nnz_a)) {
+        if (batch_rank_num_bin<LT>(p)) {
             using S = BinShape<LT>;
             constexpr int cap = 1 << (LT - 1);
             k_bnum_rank_rows<V, S::WPR, S::RPW>
@@ -1718,13 +1771,14 @@ void bnum_bin(const BPlan &p, hipStream_t s)
             return;
         }
     using S = BShape<LT, WIDE>;
-    const unsigned grid = bgrid(p, blocks_for(p.M, S::RPW));
-    if (p.cfg.row_hash)
-        k_bnum_rows<V, LT, S::WPR, S::RPW, 1><<<grid, S::THREADS, 0, s>>>(p.d_desc, p.rd, p.d_hdr, LT - kMinLogT,
-                                                                         p.ccap, p.ccol, (V *)p.cval, &p.d_hdr->error);
-    else
-        k_bnum_rows<V, LT, S::WPR, S::RPW, 0><<<grid, S::THREADS, 0, s>>>(p.d_desc, p.rd, p.d_hdr, LT - kMinLogT,
-                                                                         p.ccap, p.ccol, (V *)p.cval, &p.d_hdr->error);
+    auto run = [&](auto kern) {
+        kern<<<bgrid(p, blocks_for(p.M, S::RPW)), S::THREADS, 0, s>>>(p.d_desc, p.rd, p.d_hdr, LT - kMinLogT, p.ccap,
+                                                                      p.ccol, (V *)p.cval, &p.d_hdr->error);
+    };
+    if (p.cfg.row_hash) return run(k_bnum_rows<V, LT, S::WPR, S::RPW, 1>);
+    if constexpr (LT <= kSmallLogT)
+        if (!batch_try_small(p)) return run(k_bnum_rows<V, LT, S::WPR, S::RPW, 0, false>);
+    run(k_bnum_rows<V, LT, S::WPR, S::RPW, 0>);
 }
 
 template <int WIDE>

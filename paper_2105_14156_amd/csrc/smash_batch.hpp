@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256) void k_browdesc(const BatchDesc *__restrict__ 
 
 // Symbolic, LDS bin `bin`: RPW rows of WPR waves per work item; the next
 // item's row record is loaded while this one is processed.
-template <int LOGT, int WPR, int RPW>
+template <int LOGT, int WPR, int RPW, bool SMALL = true>
 __global__ __launch_bounds__(kWave *WPR *RPW) void k_bsym_rows(const BatchDesc *__restrict__ desc,
                                                                const RowDesc *__restrict__ rd, const BinHdr *h,
                                                                int bin, int *__restrict__ nnzc, int *err)
@@ -285,8 +285,8 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_bsym_rows(const BatchDesc *
         RowDesc nxt{};
         if (base + stride + g < cnt) nxt = rows[base + stride + g];
         const BatchDesc &d = desc[active ? cur.prob : 0];
-        sym_row<LOGT, WPR>(cur.e0, cur.e1, d.Acol, d.Brp, d.Bcol, d.cols, active, gt, s_keys[g], s_en[g], &s_cnt[g],
-                           &nnzc[active ? cur.grow : 0], err);
+        sym_row<LOGT, WPR, SMALL>(cur.e0, cur.e1, d.Acol, d.Brp, d.Bcol, d.cols, active, gt, s_keys[g], s_en[g],
+                                    &s_cnt[g], &nnzc[active ? cur.grow : 0], err);
         group_sync<WPR>();
         cur = nxt;
     }
@@ -295,7 +295,7 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_bsym_rows(const BatchDesc *
 // Numeric, LDS bin `bin` (row records with C offsets).  Does nothing when
 // the output pool is too small (the capacity check has then flagged the
 // batch).  HASH as in num_row (0 multiplicative, 1 order-preserving).
-template <typename V, int LOGT, int WPR, int RPW, int HASH>
+template <typename V, int LOGT, int WPR, int RPW, int HASH, bool SMALL = true>
 __global__ __launch_bounds__(kWave *WPR *RPW) void k_bnum_rows(const BatchDesc *__restrict__ desc,
                                                                const RowDesc *__restrict__ rd, const BatchHdr *bh,
                                                                int bin, long long ccap, int *__restrict__ Ccol,
@@ -323,9 +323,9 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_bnum_rows(const BatchDesc *
         RowDesc nxt{};
         if (base + stride + g < cnt) nxt = rows[base + stride + g];
         const BatchDesc &d = desc[active ? cur.prob : 0];
-        num_row<V, LOGT, WPR, HASH>(cur.e0, cur.e1, d.Acol, (const V *)d.Aval, d.Brp, d.Bcol, (const V *)d.Bval,
-                                    cur.rb, cur.nc, active, gt, s_keys[g], s_vals[g], s_en[g], s_scan[g], Ccol, Cval,
-                                    d.cols, err, &s_maxd[g]);
+        num_row<V, LOGT, WPR, HASH, SMALL>(cur.e0, cur.e1, d.Acol, (const V *)d.Aval, d.Brp, d.Bcol, (const V *)d.Bval,
+                                           cur.rb, cur.nc, active, gt, s_keys[g], s_vals[g], s_en[g], s_scan[g], Ccol,
+                                           Cval, d.cols, err, &s_maxd[g]);
         group_sync<WPR>();
         cur = nxt;
     }

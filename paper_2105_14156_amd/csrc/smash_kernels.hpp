@@ -1812,14 +1812,16 @@ constexpr int kSmallLogT = 7;
 // in the group; every thread of the group calls it): the distinct columns of
 // the row's A entries [e0, e1) times B, counted in an LDS key table of
 // 2^LOGT slots (step a3), are stored to *out by the group's first thread.
-template <int LOGT, int WPR>
+// SMALL: try small_row on rows of the smallest tables (a template parameter:
+// a branch on a flag takes registers from both forms, 12% of a call).
+template <int LOGT, int WPR, bool SMALL = true>
 __device__ __forceinline__ void sym_row(int e0, int e1, const int *__restrict__ Acol, const int *__restrict__ Brp,
                                         const int *__restrict__ Bcol, int ncols, bool active, int gt, int *keys,
                                         EnumScratch<float, WPR * kWave> &en, int *s_cnt, int *out, int *err)
 {
     constexpr int T = 1 << LOGT;
     constexpr int G = WPR * kWave;
-    if constexpr (WPR == 1 && LOGT <= kSmallLogT) {
+    if constexpr (WPR == 1 && LOGT <= kSmallLogT && SMALL) {
         SmallRow r;
         if (!active) return;
         if (small_row<float, false>(e0, e1, Acol, nullptr, Brp, Bcol, nullptr, ncols, en.pincl, r)) {
@@ -1853,7 +1855,7 @@ __device__ __forceinline__ void sym_row(int e0, int e1, const int *__restrict__ 
 // h->count[bin]) and the groups stride over them, so the launch needs no
 // host-side count.  With RPW > 1 each group is one wave and loops on its
 // own; with WPR > 1 the block is one group and loops as a whole.
-template <int LOGT, int WPR, int RPW>
+template <int LOGT, int WPR, int RPW, bool SMALL = true>
 __global__ __launch_bounds__(kWave *WPR *RPW) void k_sym_rows(const int *__restrict__ Arp, const int *__restrict__ Acol,
                                                               const int *__restrict__ Brp, const int *__restrict__ Bcol,
                                                               const int *__restrict__ perm, const BinHdr *h, int bin,
@@ -1874,7 +1876,8 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_sym_rows(const int *__restr
         const bool active = r < nrows;
         const int row = active ? rows[r] : 0;
         const int e0 = active ? Arp[row] : 0, e1 = active ? Arp[row + 1] : 0;
-        sym_row<LOGT, WPR>(e0, e1, Acol, Brp, Bcol, ncols, active, gt, s_keys[g], s_en[g], &s_cnt[g], &nnzc[row], err);
+        sym_row<LOGT, WPR, SMALL>(e0, e1, Acol, Brp, Bcol, ncols, active, gt, s_keys[g], s_en[g], &s_cnt[g], &nnzc[row],
+                                  err);
         group_sync<WPR>();
     }
 }
@@ -2174,7 +2177,7 @@ __device__ __forceinline__ int order_row_entries_ord(const int (&kr)[SPT], const
 // (home slot j >> shift, shift = ceil(log2 ncols) - LOGT, at least 0, with
 // the bounded insertion write-back of order_row_entries_ord; s_maxd is the
 // group's LDS word for the longest probe).
-template <typename V, int LOGT, int WPR, int HASH = 0>
+template <typename V, int LOGT, int WPR, int HASH = 0, bool SMALL = true>
 __device__ __forceinline__ void num_row(int e0, int e1, const int *__restrict__ Acol, const V *__restrict__ Aval,
                                         const int *__restrict__ Brp, const int *__restrict__ Bcol,
                                         const V *__restrict__ Bval, long long rb, int nc, bool active, int gt,
@@ -2187,7 +2190,7 @@ __device__ __forceinline__ void num_row(int e0, int e1, const int *__restrict__ 
     constexpr int SPT = T / G;          // slots per thread in the compaction
     static_assert(SPT >= 1, "table smaller than its group");
     const int lane = lane_id(), wg = gt / kWave;
-    if constexpr (WPR == 1 && LOGT <= kSmallLogT && HASH == 0) {
+    if constexpr (WPR == 1 && LOGT <= kSmallLogT && HASH == 0 && SMALL) {
         SmallRow r;
         if (!active) return;
         if (small_row<V, true>(e0, e1, Acol, Aval, Brp, Bcol, Bval, ncols, en.pincl, r)) {
@@ -2273,7 +2276,7 @@ __device__ __forceinline__ void num_row(int e0, int e1, const int *__restrict__ 
 }
 
 // Light rows: one row per group of WPR waves (RPW groups per block).
-template <typename V, int LOGT, int WPR, int RPW, int HASH = 0>
+template <typename V, int LOGT, int WPR, int RPW, int HASH = 0, bool SMALL = true>
 __global__ __launch_bounds__(kWave *WPR *RPW) void k_num_rows(
     const int *__restrict__ Arp, const int *__restrict__ Acol, const V *__restrict__ Aval,
     const int *__restrict__ Brp, const int *__restrict__ Bcol, const V *__restrict__ Bval,
@@ -2296,7 +2299,7 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_num_rows(
     const int e0 = active ? Arp[row] : 0, e1 = active ? Arp[row + 1] : 0;
     const long long rb = active ? Crp[row] : 0;
     const int nc = active ? (int)(Crp[row + 1] - rb) : 0;
-    num_row<V, LOGT, WPR, HASH>(e0, e1, Acol, Aval, Brp, Bcol, Bval, rb, nc, active, gt, s_keys[g], s_vals[g],
+    num_row<V, LOGT, WPR, HASH, SMALL>(e0, e1, Acol, Aval, Brp, Bcol, Bval, rb, nc, active, gt, s_keys[g], s_vals[g],
                                 s_en[g], s_scan[g], Ccol, Cval, ncols, err, &s_maxd[g]);
 }
 
@@ -2330,7 +2333,8 @@ __global__ __launch_bounds__(256) void k_num_few(const int *__restrict__ Arp, co
         const int row = active ? rows[r] : 0;
         const long long rb = active ? Crp[row] : 0;
         num_row<V, LOGT, WPR, HASH>(active ? Arp[row] : 0, active ? Arp[row + 1] : 0, Acol, Aval, Brp, Bcol, Bval, rb,
-                                    active ? (int)(Crp[row + 1] - rb) : 0, active, threadIdx.x - g * WPR * kWave,
+                                    active ? (int)(Crp[row + 1] - rb) : 0, active,
+                                    threadIdx.x - g * WPR * kWave,
                                     L.keys[g], L.vals[g], L.en[g], L.scan[g], Ccol, Cval, ncols, err, &L.maxd[g]);
     });
 }

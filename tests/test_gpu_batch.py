@@ -385,3 +385,23 @@ def test_batch_short_b_rows(env, oracle_mod, n, per_row):
         plan.run()
         _check_plan(plan, probs, refs, oracle_mod, f"{n} columns, {per_row} per row, run {rep}")
     plan.close()
+
+
+@pytest.mark.parametrize("n", [5, 64, 65, 128, 129, 256, 512, 1024, 1025])
+def test_batch_narrow_b(env, oracle_mod, n):
+    """B of few columns in batches, on both sides of the same lines."""
+    torch, smash, ctx = env
+    for mean in (7, 9, 51, 53, 103, 210):
+        probs = []
+        for q in range(3):
+            B = syn.uniform_k_per_row(3000, n, min(8, n), 40 + q, np.float32)
+            lens = np.arange(400) * 7 % (2 * mean + 1)
+            ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+            col = ((np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens)) * 7 + np.repeat(np.arange(400) % 17, lens)).astype(np.int32)
+            probs.append((syn.CSR(400, 3000, ptr, col, (2.0 * syn.uniform01(q, 0, len(col)) - 1.0).astype(np.float32)), B))
+        refs = [oracle_mod.spgemm(A, B) for A, B in probs]
+        plan = _make_plan(smash, ctx, probs)
+        for rep in range(2):
+            plan.run()
+            _check_plan(plan, probs, refs, oracle_mod, f"{n} columns, {mean} entries per A row, run {rep}")
+        plan.close()

@@ -634,3 +634,21 @@ def test_short_b_rows(sm, ctx, oracle_mod, dtype, n, per_row):
         col = ((np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens)) * np.repeat(step, lens)).astype(np.int32)
         A = syn.CSR(rows, k, ptr, col, (2.0 * syn.uniform01(6, 0, len(col)) - 1.0).astype(dtype))
         full_check(sm, ctx, A, B, dtype, oracle_mod, rows == 60, f"{rows} rows, {n} columns, {per_row} per row")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [5, 63, 64, 65, 128, 129, 256, 257, 512, 1024, 1025])
+def test_narrow_b(sm, ctx, oracle_mod, dtype, n):
+    """B of few columns, so that rows hold far fewer entries than products: on
+    both sides of the widths and of the products per row at which rows are
+    merged in registers, hashed or merged by a bitmap."""
+    k = 3000
+    per = min(8, n)
+    B = syn.uniform_k_per_row(k, n, per, 91, dtype)
+    for mean in (7, 9, 51, 53, 103, 210):     # products per row: per times this, on average
+        lens = (np.arange(8300) * 7 % (2 * mean + 1)).astype(np.int64)
+        lens[::1000] = 400
+        ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        col = ((np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens)) * 7 + np.repeat(np.arange(8300) % 17, lens)).astype(np.int32)
+        A = syn.CSR(8300, k, ptr, col, (2.0 * syn.uniform01(9, 0, len(col)) - 1.0).astype(dtype))
+        full_check(sm, ctx, A, B, dtype, oracle_mod, False, f"{n} columns, {mean} entries per A row")
