@@ -108,6 +108,8 @@ __device__ __forceinline__ int problem_of(const long long *__restrict__ row0s, i
     return lo;
 }
 
+constexpr int kBatchShortRow = 128;   // entries of a row that eight lanes sum (k_banalyze)
+
 // Blocks of k_banalyze that look for long rows, and all of them.
 __host__ __device__ __forceinline__ int banalyze_long_blocks(long long M) { return (int)((M + 255) / 256) + 1; }
 inline int banalyze_blocks(long long M) { return banalyze_long_blocks(M) + (int)((M + 255) / 256); }
@@ -117,9 +119,11 @@ inline int banalyze_blocks(long long M) { return banalyze_long_blocks(M) + (int)
 // rows of problems wider than kWideMaxCols, its global table size.
 //
 // Bound by the latency of two dependent gathers per entry; the split is that
-// of for_rows.  Rows of at most kShortRow entries: a wave takes 64 consecutive
+// of for_rows.  Rows of at most kBatchShortRow entries: a wave takes 64 consecutive
 // rows, reads their bounds one per lane and sums them eight at a time, eight
-// lanes each.  Longer rows: by a whole wave, eight entries per lane in flight,
+// lanes each: in turn, hence a lower limit than there (four products of RMAT
+// scale 16, edge factor 8, with a B of 8 entries per row: 41 us, with 256
+// entries 65).  Longer rows: by a whole wave, eight entries per lane in flight,
 // the rows a wave looks at an odd stride apart.  Batch of 512 RMAT pairs:
 // 0.40 ms; with 64 consecutive rows per wave, the long ones (they come in
 // clusters) in turn and one entry per lane in flight, 0.71.
@@ -156,7 +160,7 @@ __global__ __launch_bounds__(256) void k_banalyze(long long M, int count, const 
             e0 = d.Arp[g - d.row0];
             e1 = d.Arp[g - d.row0 + 1];
         }
-        for (unsigned long long todo = __ballot(e1 - e0 > kShortRow); todo; todo &= todo - 1) {
+        for (unsigned long long todo = __ballot(e1 - e0 > kBatchShortRow); todo; todo &= todo - 1) {
             const int src = __ffsll((long long)todo) - 1;
             const int f0 = __builtin_amdgcn_readlane(e0, src), f1 = __builtin_amdgcn_readlane(e1, src);
             const int lp = __builtin_amdgcn_readlane(pr, src);
@@ -177,14 +181,14 @@ __global__ __launch_bounds__(256) void k_banalyze(long long M, int count, const 
         e0 = d.Arp[g - d.row0];
         e1 = d.Arp[g - d.row0 + 1];
     }
-    const bool here = g < M && e1 - e0 <= kShortRow;
+    const bool here = g < M && e1 - e0 <= kBatchShortRow;
     const int sl = lane & (kRowLanes - 1);
     long long ub = 0;
     for (int t = 0; t < kWave / kRowLanes; ++t) {
         const int src = t * kRowLanes + lane / kRowLanes;       // this group's row
         const int f0 = __shfl(e0, src, kWave), f1 = __shfl(e1, src, kWave), lp = __shfl(pr, src, kWave);
         RowPart r;
-        if (f1 - f0 <= kShortRow) row_part<false>(desc[lp].Acol, desc[lp].Brp, f0 + sl, f1, kRowLanes, r);
+        if (f1 - f0 <= kBatchShortRow) row_part<false>(desc[lp].Acol, desc[lp].Brp, f0 + sl, f1, kRowLanes, r);
         row_reduce<false>(r, kRowLanes);
         const long long mine = __shfl(r.ub, sl * kRowLanes, kWave);
         if (lane / kRowLanes == t) ub = mine;
@@ -286,7 +290,7 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_bsym_rows(const BatchDesc *
         if (base + stride + g < cnt) nxt = rows[base + stride + g];
         const BatchDesc &d = desc[active ? cur.prob : 0];
         sym_row<LOGT, WPR, SMALL>(cur.e0, cur.e1, d.Acol, d.Brp, d.Bcol, d.cols, active, gt, s_keys[g], s_en[g],
-                                    &s_cnt[g], &nnzc[active ? cur.grow : 0], err);
+                                  &s_cnt[g], &nnzc[active ? cur.grow : 0], err);
         group_sync<WPR>();
         cur = nxt;
     }
