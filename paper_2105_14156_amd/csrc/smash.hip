@@ -464,7 +464,8 @@ smash_status launch_sym_bin(smash_ctx c, hipStream_t s, const Plan &p)
     using S = BinShape<LOGT>;
     if constexpr (LOGT >= 8)
         if (rank_bin<LOGT>(p) && !short_ranges(3, p.B.nnz, p.B.rows)) {
-            auto kern = k_sym_rank_rows<S::WPR, S::RPW>;
+            const bool read = read_marks(expected_products(p), p.m, p.n);
+            auto kern = read ? k_sym_rank_rows<S::WPR, S::RPW, true> : k_sym_rank_rows<S::WPR, S::RPW, false>;
             const size_t lds = S::RPW * rank_sym_lds<S::WPR>((int)p.n);
             const int res = resident_blocks(c, (const void *)kern, S::THREADS, lds);
             const unsigned grid = (unsigned)std::max<long long>(1, std::min<long long>(res, blocks_for(p.m, S::RPW)));
@@ -1733,6 +1734,9 @@ bool batch_rank_num_bin(const BPlan &p)
            (p.max_cols > 1024 || LT == 10 || products <= 416LL * BinShape<LT>::WPR * p.M);
 }
 
+// Whether bitmap marks are read before they are set.
+bool batch_read_marks(const BPlan &p) { return read_marks((double)p.products, p.M, p.max_cols); }
+
 // Whether rows of the smallest tables are worth an attempt by small_row.
 bool batch_try_small(const BPlan &p) { return p.max_cols > kWave || (long long)p.products <= kWave * p.M; }
 
@@ -1742,8 +1746,9 @@ void bsym_bin(const BPlan &p, hipStream_t s)
     if constexpr (LT >= 8)
         if (batch_rank_bin<LT>(p)) {
             using S = BinShape<LT>;
-            k_bsym_rank_rows<S::WPR, S::RPW>
-                <<<bgrid(p, blocks_for(p.M, S::RPW), 256 / S::THREADS), S::THREADS, S::RPW * rank_sym_lds<S::WPR>(p.max_cols), s>>>(
+            auto kern = batch_read_marks(p) ? k_bsym_rank_rows<S::WPR, S::RPW, true>
+                                            : k_bsym_rank_rows<S::WPR, S::RPW, false>;
+            kern<<<bgrid(p, blocks_for(p.M, S::RPW), 256 / S::THREADS), S::THREADS, S::RPW * rank_sym_lds<S::WPR>(p.max_cols), s>>>(
                     p.d_desc, p.rd, &p.d_hdr->sym, LT - kMinLogT, p.max_cols, p.nnzc);
             return;
         }
@@ -1764,8 +1769,9 @@ void bnum_bin(const BPlan &p, hipStream_t s)
         if (batch_rank_num_bin<LT>(p)) {
             using S = BinShape<LT>;
             constexpr int cap = 1 << (LT - 1);
-            k_bnum_rank_rows<V, S::WPR, S::RPW>
-                <<<bgrid(p, blocks_for(p.M, S::RPW), 256 / S::THREADS), S::THREADS, S::RPW * rank_row_lds<V, S::WPR>(p.max_cols, cap), s>>>(
+            auto kern = batch_read_marks(p) ? k_bnum_rank_rows<V, S::WPR, S::RPW, true>
+                                            : k_bnum_rank_rows<V, S::WPR, S::RPW, false>;
+            kern<<<bgrid(p, blocks_for(p.M, S::RPW), 256 / S::THREADS), S::THREADS, S::RPW * rank_row_lds<V, S::WPR>(p.max_cols, cap), s>>>(
                     p.d_desc, p.rd, p.d_hdr, LT - kMinLogT, p.max_cols, cap, p.ccap, p.ccol, (V *)p.cval,
                     &p.d_hdr->error);
             return;
@@ -1834,7 +1840,8 @@ void batch_enqueue(const BPlan &p, hipStream_t s)
                                                                p.rd);
     if (p.cfg.wide_groups) bsym_bins<1>(p, s);
     else bsym_bins<0>(p, s);
-    k_bsym_wide<<<bgrid(p, p.M), kWideThreads, wide_words(p) * sizeof(unsigned), s>>>(
+    auto wide = batch_read_marks(p) ? k_bsym_wide<true> : k_bsym_wide<false>;
+    wide<<<bgrid(p, p.M), kWideThreads, wide_words(p) * sizeof(unsigned), s>>>(
         p.d_desc, p.prob, &p.d_hdr->sym, p.sym_perm, p.nnzc);
     if (p.any_global)
         k_bsym_global<<<bgrid(p, p.M), kGlobalThreads, 0, s>>>(p.d_desc, p.prob, &p.d_hdr->sym, p.sym_perm, p.cap,
@@ -1975,8 +1982,10 @@ smash_status smash_batch_plan_create(smash_ctx c, smash_dtype dtype, int32_t cou
                             (int)rank_row_lds<float, kWideWaves>(kRankMaxCols, kWideCap)) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bnum_wide_rank<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)rank_row_lds<double, kWideWaves>(kRankMaxCols, kWideCap)) != hipSuccess ||
-        hipFuncSetAttribute((const void *)k_bsym_wide, hipFuncAttributeMaxDynamicSharedMemorySize,
-                            (int)(wide_words(*p) * sizeof(unsigned))) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_bsym_wide<false>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            kWideMaxCols / 8) != hipSuccess ||
+        hipFuncSetAttribute((const void *)k_bsym_wide<true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            kWideMaxCols / 8) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bnum_global<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)global_rank_lds(kGlobalRankBits)) != hipSuccess ||
         hipFuncSetAttribute((const void *)k_bnum_global<double>, hipFuncAttributeMaxDynamicSharedMemorySize,

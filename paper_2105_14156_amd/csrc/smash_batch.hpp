@@ -345,7 +345,7 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_bnum_rows(const BatchDesc *
 // 0.94.
 constexpr int kBatchRankCols = 128;
 
-template <int WPR, int RPW>
+template <int WPR, int RPW, bool READ>
 __global__ __launch_bounds__(kWave *WPR *RPW) void k_bsym_rank_rows(const BatchDesc *__restrict__ desc,
                                                                     const RowDesc *__restrict__ rd, const BinHdr *h,
                                                                     int bin, int lds_cols, int *__restrict__ nnzc)
@@ -363,12 +363,12 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_bsym_rank_rows(const BatchD
         const RowDesc cur = nxt;
         if (r + stride < cnt) nxt = rows[r + stride];
         const BatchDesc &d = desc[cur.prob];
-        rank_sym_row<WPR>(cur.e0, cur.e1, d.Acol, d.Brp, d.Bcol, d.cols, gt, raw, &nnzc[cur.grow]);
+        rank_sym_row<WPR, READ>(cur.e0, cur.e1, d.Acol, d.Brp, d.Bcol, d.cols, gt, raw, &nnzc[cur.grow]);
         group_sync<WPR>();
     }
 }
 
-template <typename V, int WPR, int RPW>
+template <typename V, int WPR, int RPW, bool READ>
 __global__ __launch_bounds__(kWave *WPR *RPW) void k_bnum_rank_rows(const BatchDesc *__restrict__ desc,
                                                                     const RowDesc *__restrict__ rd,
                                                                     const BatchHdr *bh, int bin, int lds_cols, int cap,
@@ -389,8 +389,8 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_bnum_rank_rows(const BatchD
         const RowDesc cur = nxt;
         if (r + stride < cnt) nxt = rows[r + stride];
         const BatchDesc &d = desc[cur.prob];
-        rank_num_row<V, WPR>(cur.e0, cur.e1, d.Acol, (const V *)d.Aval, d.Brp, d.Bcol, (const V *)d.Bval, cur.rb,
-                             cur.nc, d.cols, lds_cols, cap, gt, raw, Ccol, Cval, err);
+        rank_num_row<V, WPR, READ>(cur.e0, cur.e1, d.Acol, (const V *)d.Aval, d.Brp, d.Bcol, (const V *)d.Bval, cur.rb,
+                                   cur.nc, d.cols, lds_cols, cap, gt, raw, Ccol, Cval, err);
         group_sync<WPR>();
     }
 }
@@ -462,6 +462,8 @@ __global__ __launch_bounds__(kGlobalThreads) void k_bnum_global(const BatchDesc 
 // Symbolic, heavy rows of problems with at most kWideMaxCols columns: one
 // block per row sets one bit per column of the row in an LDS bitmap over all
 // of B's columns (dynamic LDS, ceil(cols / 32) words) and counts the bits.
+// READ as in rank_sym_row.
+template <bool READ>
 __global__ __launch_bounds__(kWideThreads) void k_bsym_wide(const BatchDesc *__restrict__ desc,
                                                             const int *__restrict__ prob, const BinHdr *h,
                                                             const int *__restrict__ perm, int *__restrict__ nnzc)
@@ -481,10 +483,7 @@ __global__ __launch_bounds__(kWideThreads) void k_bsym_wide(const BatchDesc *__r
         for (int t = gt; t < nw; t += kWideThreads) s_bmw[t] = 0u;
         if (gt == 0) s_cnt = 0;                            // the products' first barrier follows
         auto mark = [&](const auto &j, const auto &ok) {
-            constexpr int N = sizeof(j) / sizeof(j[0]);
-#pragma unroll
-            for (int u = 0; u < N; ++u)
-                if (ok[u]) atomicOr(&s_bmw[j[u] >> 5], 1u << (j[u] & 31));
+            mark_columns<READ>(s_bmw, j, ok);
         };
         piece_products<float, false, kWideThreads, kWideThreads, 4, true, kRankPiece>(
             d.Arp[arow], d.Arp[arow + 1], gt, S, d.Acol, (const float *)nullptr, d.Brp, 1, 1, d.Bcol,

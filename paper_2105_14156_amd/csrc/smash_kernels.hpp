@@ -1595,9 +1595,47 @@ __host__ __device__ __forceinline__ size_t rank_sym_lds(int ncols)
     return (((size_t)rank_words(ncols) * 4 + sizeof(PieceScratch<float, WPR * kWave>) + sizeof(int)) + 15) & ~(size_t)15;
 }
 
+// Marks the columns j (where ok) in a bitmap over B's columns.  READ: those
+// marked already skip the atomic, whose lanes wait for each other where they
+// meet in one word; the reads overlap, and an OR after a stale read is merely
+// redundant.
+template <bool READ, typename J, typename K>
+__device__ __forceinline__ void mark_columns(unsigned *bm, const J &j, const K &ok)
+{
+    constexpr int N = sizeof(j) / sizeof(j[0]);
+    if constexpr (READ) {
+        unsigned w[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) w[u] = ok[u] ? bm[j[u] >> 5] : ~0u;
+#pragma unroll
+        for (int u = 0; u < N; ++u) {
+            const unsigned bit = 1u << (j[u] & 31);
+            if (!(w[u] & bit)) atomicOr(&bm[j[u] >> 5], bit);
+        }
+    } else {
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+            if (ok[u]) atomicOr(&bm[j[u] >> 5], 1u << (j[u] & 31));
+    }
+}
+
+// Marks are read first where the average row has more than kRepeatRead products
+// per column (most marks are set already) of at most 4096 columns (many lanes
+// meet in a word): 8000 rows of 300 x 300 products 2.55 ms a replay without and
+// 2.34 with in 1500 columns (60 per column), 2.97 and 2.12 in 600, 5.37 and 2.96
+// in 300.  Elsewhere the reads cost: rows of 600 x 300 products in 6000 columns
+// (30 per column) 4.34 and 4.44, the batch of 512 RMAT pairs 5.93 and 5.97.
+constexpr int kRepeatRead = 24;
+
+inline bool read_marks(double products, long long rows, long long cols)
+{
+    return cols <= 4096 && products > (double)kRepeatRead * rows * cols;
+}
+
 // Symbolic count of one light row by a group of WPR waves, stored to *out.
-// raw: rank_sym_lds bytes.  B is at most ncols wide.
-template <int WPR>
+// raw: rank_sym_lds bytes.  B is at most ncols wide.  READ: marks are read
+// before they are set (kRepeatRead).
+template <int WPR, bool READ>
 __device__ __forceinline__ void rank_sym_row(int e0, int e1, const int *__restrict__ Acol,
                                              const int *__restrict__ Brp, const int *__restrict__ Bcol, int ncols,
                                              int gt, unsigned char *raw, int *out)
@@ -1610,10 +1648,7 @@ __device__ __forceinline__ void rank_sym_row(int e0, int e1, const int *__restri
     for (int t = gt * 4; t < W; t += 4 * G) *(uint4 *)&bm[t] = make_uint4(0, 0, 0, 0);
     if (gt == 0) *cnt = 0;                                  // the products' first barrier follows
     auto mark = [&](const auto &j, const auto &ok) {
-        constexpr int N = sizeof(j) / sizeof(j[0]);
-#pragma unroll
-        for (int u = 0; u < N; ++u)
-            if (ok[u]) atomicOr(&bm[j[u] >> 5], 1u << (j[u] & 31));
+        mark_columns<READ>(bm, j, ok);
     };
     piece_products<float, false, G, G, 4, true, kRankPiece>(e0, e1, gt, S, Acol, (const float *)nullptr, Brp, 1, 1,
                                                             Bcol, (const float *)nullptr, mark);
@@ -1638,7 +1673,8 @@ __device__ __forceinline__ void rank_sym_row(int e0, int e1, const int *__restri
 // at a time (rows of more entries repeat the second pass).  raw: rank_row_lds
 // bytes for lds_cols >= ncols columns.  Products stay in registers between the
 // passes where the row's A entries fit one list and its pieces one locating.
-template <typename V, int WPR>
+// READ as in rank_sym_row.
+template <typename V, int WPR, bool READ = false>
 __device__ __forceinline__ void rank_num_row(int e0, int e1, const int *__restrict__ Acol, const V *__restrict__ Aval,
                                              const int *__restrict__ Brp, const int *__restrict__ Bcol,
                                              const V *__restrict__ Bval, long long rb, int nc, int ncols, int lds_cols,
@@ -1697,7 +1733,12 @@ __device__ __forceinline__ void rank_num_row(int e0, int e1, const int *__restri
     };
     auto mark = [&](auto t) {
         constexpr int T = decltype(t)::value;
-        if (hok[T]) atomicOr(&bm[hc[T] >> 5], 1u << (hc[T] & 31));
+        if constexpr (READ) {
+            const unsigned bit = 1u << (hc[T] & 31);
+            if (hok[T] && !(bm[hc[T] >> 5] & bit)) atomicOr(&bm[hc[T] >> 5], bit);
+        } else {
+            if (hok[T]) atomicOr(&bm[hc[T] >> 5], 1u << (hc[T] & 31));
+        }
     };
     pass(mark);
     // prefix counts: every thread the same number of consecutive 4-word groups
@@ -1764,7 +1805,7 @@ __device__ __forceinline__ void rank_num_row(int e0, int e1, const int *__restri
 
 // Light rows of one bin (see k_sym_rows and k_num_rows) by a column bitmap;
 // dynamic LDS: RPW times the group's.
-template <int WPR, int RPW>
+template <int WPR, int RPW, bool READ>
 __global__ __launch_bounds__(kWave *WPR *RPW) void k_sym_rank_rows(
     const int *__restrict__ Arp, const int *__restrict__ Acol, const int *__restrict__ Brp,
     const int *__restrict__ Bcol, const int *__restrict__ perm, const BinHdr *h, int bin, int ncols,
@@ -1779,7 +1820,7 @@ __global__ __launch_bounds__(kWave *WPR *RPW) void k_sym_rank_rows(
     const int *rows = perm + h->offset[bin];
     for (int r = blockIdx.x * RPW + g; r < nrows; r += gridDim.x * RPW) {
         const int row = rows[r];
-        rank_sym_row<WPR>(Arp[row], Arp[row + 1], Acol, Brp, Bcol, ncols, gt, raw, &nnzc[row]);
+        rank_sym_row<WPR, READ>(Arp[row], Arp[row + 1], Acol, Brp, Bcol, ncols, gt, raw, &nnzc[row]);
         group_sync<WPR>();
     }
 }

@@ -405,3 +405,24 @@ def test_batch_narrow_b(env, oracle_mod, n):
             plan.run()
             _check_plan(plan, probs, refs, oracle_mod, f"{n} columns, {mean} entries per A row, run {rep}")
         plan.close()
+
+
+@pytest.mark.parametrize("n", [129, 300, 600, 1500, 3000])
+def test_batch_repeated_columns(env, oracle_mod, n):
+    """Rows with many products per column of B in batches, light and heavy, on
+    both sides of the line from which marks are read before they are set."""
+    torch, smash, ctx = env
+    for mean in (18 * n // 128, 32 * n // 128):
+        probs = []
+        for q in range(2):
+            B = syn.uniform_k_per_row(2000, n, 128, 50 + q, np.float32)
+            lens = np.arange(100) * 7 % (2 * mean + 1)
+            ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+            col = ((np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens)) + np.repeat(np.arange(100) % 17, lens)).astype(np.int32)
+            probs.append((syn.CSR(100, 2000, ptr, col, (2.0 * syn.uniform01(q, 0, len(col)) - 1.0).astype(np.float32)), B))
+        refs = [oracle_mod.spgemm(A, B) for A, B in probs]
+        plan = _make_plan(smash, ctx, probs)
+        for rep in range(2):
+            plan.run()
+            _check_plan(plan, probs, refs, oracle_mod, f"{n} columns, {mean} entries per A row, run {rep}")
+        plan.close()

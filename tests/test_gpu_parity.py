@@ -652,3 +652,20 @@ def test_narrow_b(sm, ctx, oracle_mod, dtype, n):
         col = ((np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens)) * 7 + np.repeat(np.arange(8300) % 17, lens)).astype(np.int32)
         A = syn.CSR(8300, k, ptr, col, (2.0 * syn.uniform01(9, 0, len(col)) - 1.0).astype(dtype))
         full_check(sm, ctx, A, B, dtype, oracle_mod, False, f"{n} columns, {mean} entries per A row")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n", [129, 250, 600, 1025, 1700])
+def test_repeated_columns(sm, ctx, oracle_mod, dtype, n):
+    """Light rows with many products per column of B, on both sides of the line
+    from which marks in a bitmap are read before they are set."""
+    k, per = 4000, 128
+    B = syn.uniform_k_per_row(k, n, per, 93, dtype)
+    for mean in (20 * n // per, 30 * n // per):
+        lens = np.where(np.arange(8200) % 20 == 0, 20 * mean - 19, 1).astype(np.int64)
+        ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+        col = ((np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens)) * k // np.repeat(lens, lens)).astype(np.int32)
+        if lens.max() > k:
+            continue
+        A = syn.CSR(8200, k, ptr, col, (2.0 * syn.uniform01(9, 0, len(col)) - 1.0).astype(dtype))
+        full_check(sm, ctx, A, B, dtype, oracle_mod, False, f"{n} columns, {mean} entries per A row")
