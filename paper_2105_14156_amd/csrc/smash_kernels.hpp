@@ -3208,9 +3208,9 @@ __device__ __forceinline__ int gclaim(int *p, int key)
 }
 
 // A slot of a numeric table: key and value side by side, so that a probe and
-// the add that follows it touch one cache line.  `list` is an entry of the
-// row's list of claimed slots (entry i of the list is the i-th slot's), not of
-// this slot.
+// the add that follows it touch one cache line.  `list` is not of this slot: in
+// slot i < nc (the row's entries) it is the number of the i-th slot that was
+// claimed, in slot nc + i that slot's key (a table has at least 2 nc slots).
 struct alignas(16) GSlot {
     double val;
     int key;
@@ -3220,8 +3220,8 @@ struct alignas(16) GSlot {
 // Slots of the U columns j in a table of 2^logT keys, key_at(h) the address of
 // slot h's (claimed where new; -1 for an absent product or a full table, which
 // sets kErrProbe): the first reads of all U are in flight together, and a
-// column that is there already costs no compare-and-swap.  claimed(slot) is
-// called for every new key.
+// column that is there already costs no compare-and-swap.  claimed(slot, key)
+// is called for every new key.
 template <int U, typename K, typename F>
 __device__ __forceinline__ void gfind(int logT, const int (&j)[U], const bool (&ok)[U], int (&slot)[U], int *err,
                                       K key_at, F claimed)
@@ -3242,7 +3242,7 @@ __device__ __forceinline__ void gfind(int logT, const int (&j)[U], const bool (&
             if ((open >> u & 1) && cur[u] == kEmpty) {
                 cur[u] = gclaim(key_at(slot[u]), j[u]);
                 if (cur[u] == kEmpty) {
-                    claimed(slot[u]);
+                    claimed(slot[u], j[u]);
                     open &= ~(1u << u);
                 }
             }
@@ -3320,7 +3320,7 @@ __device__ __forceinline__ void sym_global_row(const int *__restrict__ Arp, cons
             far[u] = ok[u] && front_find(front, j[u], fresh) < 0;
             mine += fresh;
         }
-        gfind<N>(logT, j, far, slot, err, [&](int h) { return &keys[h]; }, [&](int) { ++mine; });
+        gfind<N>(logT, j, far, slot, err, [&](int h) { return &keys[h]; }, [&](int, int) { ++mine; });
     };
     piece_products<float, false, kGlobalThreads, kGlobalThreads, 4>(Arp[arow], Arp[arow + 1], threadIdx.x, S, Acol,
                                                                     (const float *)nullptr, Brp, 1, 1, Bcol,
@@ -3347,25 +3347,27 @@ __global__ __launch_bounds__(kGlobalThreads) void k_sym_global(
 }
 
 // Numeric pass of one heavy row in global mode by a whole block: clears the
-// row's global tag/value table, merges the row's products into it with
-// compare-and-swap and atomic add (FP64 values: the sum is rounded to the
-// output type once, at write-out), then writes the entries in column order
-// at C's row `crow`.  Every slot the row claims is appended to the row's
-// touched-slot list (nc entries: the paper's third version keeps
-// its tags in dense arrays with an offset array for the same purpose), so
-// the write-out reads the row's nc entries instead of scanning all T >= 2 nc
-// slots of its table: per window of kGlobalRankBits columns, the listed
-// entries of the window are marked in an LDS bitmap and ranked by its
-// prefix counts (a count per owner thread, and 16-bit counts of the words
-// inside the owner's range).  The bitmap and those counts are the block's
-// dynamic LDS (global_rank_lds bytes, no more than B's columns need, so that
-// several rows share a CU where B is narrow).
+// row's global table, merges the row's products into it with compare-and-swap
+// on the key and atomic add on the FP64 value (the sum is rounded to the output
+// type once, at write-out), then writes the entries in column order at C's row
+// `crow`.  Every slot the row claims is appended, with its column, to the row's
+// touched-slot list (nc entries: the paper's third version keeps its tags in
+// dense arrays with an offset array for the same purpose), so the write-out
+// reads the row's nc entries instead of scanning all T >= 2 nc slots of its
+// table: per window of kGlobalRankBits columns, the listed columns of the window
+// are marked in an LDS bitmap and ranked by its prefix counts (a count per owner
+// thread, and 16-bit counts of the words inside the owner's range).  The bitmap
+// and those counts are the block's dynamic LDS (global_rank_lds bytes, no more
+// than B's columns need, so that several rows share a CU where B is narrow).
 //
 // Bound by memory traffic: the tables' lines and their clearing.  RMAT 12289
 // A * A (edge factor 12, 20M products in heavy rows), FP32: 0.77 ms; without the
 // front table 1.53, with keys and values in separate arrays and a
 // compare-and-swap per product 1.80, with agent scope and a 2^19-column
-// bitmap per row 5.64 (symbolic pass 0.17, 0.57, 0.81 and 0.47 ms).
+// bitmap per row 5.64 (symbolic pass 0.17, 0.57, 0.81 and 0.47 ms).  Every
+// window looks at the whole list twice, hence the columns in it: 500 rows of
+// 2000 x 100 products in eight windows 32 ms, 59 where each look reads the
+// listed slot's key; 50 rows of 300 x 300 in 191 windows 33 and 61.
 constexpr int kGlobalRankBits = 1 << 19;
 
 __host__ __device__ __forceinline__ size_t global_rank_lds(long long ncols)
@@ -3389,7 +3391,8 @@ __device__ __forceinline__ void num_global_row(const int *__restrict__ Arp, cons
                                                const V *__restrict__ Aval, const int *__restrict__ Brp,
                                                const int *__restrict__ Bcol, const V *__restrict__ Bval, int arow,
                                                long long crow, int ncols, GSlot *tab, GlobalNumLds<V> &L,
-                                               unsigned *s_bm, const long long *__restrict__ Crp, int *__restrict__ Ccol, V *__restrict__ Cval, int *err)
+                                               unsigned *s_bm, const long long *__restrict__ Crp,
+                                               int *__restrict__ Ccol, V *__restrict__ Cval, int *err)
 {
     constexpr int G = kGlobalThreads;
     const long long rb = Crp[crow];
@@ -3416,9 +3419,12 @@ __device__ __forceinline__ void num_global_row(const int *__restrict__ Arp, cons
             mine += fresh;
             if (ok[u] && f >= 0) atomicAdd(&L.fval[f], p[u]);
         }
-        gfind<N>(logT, j, far, slot, err, [&](int h) { return &tab[h].key; }, [&](int h) {
+        gfind<N>(logT, j, far, slot, err, [&](int h) { return &tab[h].key; }, [&](int h, int key) {
             const int at = atomicAdd(&L.ntouched, 1);
-            if (at < nc) tab[at].list = h;
+            if (at < nc) {
+                tab[at].list = h;
+                tab[nc + at].list = key;
+            }
         });
 #pragma unroll
         for (int u = 0; u < N; ++u)
@@ -3433,7 +3439,7 @@ __device__ __forceinline__ void num_global_row(const int *__restrict__ Arp, cons
     // the row's entries: the front table's slots, then the list
     const int nt = L.ntouched < nc ? L.ntouched : nc, listed = L.nfront + nt;
     const int nf = 1 << kFrontLog;
-    auto key_of = [&](int t) { return t < nf ? L.fkey[t] : gload(&tab[tab[t - nf].list].key); };
+    auto key_of = [&](int t) { return t < nf ? L.fkey[t] : tab[nc + t - nf].list; };
     const int top = ncols < kGlobalRankBits ? ncols : kGlobalRankBits;
     const int words = (top + 31) >> 5;
     unsigned short *s_pref = reinterpret_cast<unsigned short *>(s_bm + ((words + 1) & ~1));
@@ -3480,8 +3486,7 @@ __global__ __launch_bounds__(kGlobalThreads) void k_num_global(
     const int *__restrict__ Arp, const int *__restrict__ Acol, const V *__restrict__ Aval,
     const int *__restrict__ Brp, const int *__restrict__ Bcol, const V *__restrict__ Bval,
     const int *__restrict__ rows, int ncols, const long long *__restrict__ goff, long long gbase, GSlot *pool,
-    const long long *__restrict__ Crp, int *__restrict__ Ccol, V *__restrict__ Cval,
-    int *err)
+    const long long *__restrict__ Crp, int *__restrict__ Ccol, V *__restrict__ Cval, int *err)
 {
     extern __shared__ unsigned s_bm[];                     // global_rank_lds(ncols) bytes
     __shared__ GlobalNumLds<V> L;

@@ -669,3 +669,21 @@ def test_repeated_columns(sm, ctx, oracle_mod, dtype, n):
             continue
         A = syn.CSR(8200, k, ptr, col, (2.0 * syn.uniform01(9, 0, len(col)) - 1.0).astype(dtype))
         full_check(sm, ctx, A, B, dtype, oracle_mod, False, f"{n} columns, {mean} entries per A row")
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("count", [8191, 8192, 8193, 16384])
+def test_global_list_fills_table(sm, ctx, oracle_mod, dtype, count):
+    """Global-mode rows whose list of slots and of their columns takes up to all
+    of a table of twice their entries, over three rank windows."""
+    n = 3 << 19
+    cols = np.unique(syn.splitmix64(7, 0, 2 * count) % np.uint64(n))[:2 * count]
+    cols = np.sort(cols[(np.arange(count) * len(cols)) // count]).astype(np.int32)
+    assert len(np.unique(cols)) == count
+    B = syn.CSR(2, n, np.array([0, count, 2 * count], np.int32), np.concatenate([cols, cols]),
+                (2.0 * syn.uniform01(83, 0, 2 * count) - 1.0).astype(dtype))
+    A = syn.CSR(3, 2, np.array([0, 2, 2, 4], np.int32), np.array([0, 1, 0, 1], np.int32),
+                (2.0 * syn.uniform01(84, 0, 4) - 1.0).astype(dtype))
+    ctx.set_option(sm.OPT_HEAVY_MODE, 1)
+    full_check(sm, ctx, A, B, dtype, oracle_mod, False, f"global list of {count}")
+    assert ctx.stats()["rows_heavy"] == 2
