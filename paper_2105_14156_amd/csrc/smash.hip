@@ -661,7 +661,10 @@ smash_status numeric_impl(smash_ctx c, hipStream_t s, const Plan &p, const V *Av
     // by the symbolic phase (each row clears its own table, so the pool is
     // reused as it is)
     const size_t lds = global_rank_lds(p.n);
-    (void)hipFuncSetAttribute((const void *)k_num_global<V>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    // the most that any call needs: the attribute is the process's, and another
+    // thread's call with a wider B may come between this line and the launch
+    (void)hipFuncSetAttribute((const void *)k_num_global<V>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                              (int)global_rank_lds(kGlobalRankBits));
     const int *rows = p.num_perm + p.hdr.num.offset[kBinHeavy];
     for (size_t w = 0; w + 1 < p.num_waves.size(); ++w) {
         const int h0 = p.num_waves[w].first, nh = p.num_waves[w + 1].first - h0;
