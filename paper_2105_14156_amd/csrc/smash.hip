@@ -605,16 +605,14 @@ smash_status scan_counts(smash_ctx c, hipStream_t s, long long n, const TIn *cnt
 
 template <typename V, int LOGT, int THREADS>
 smash_status launch_seg_bin(smash_ctx c, hipStream_t s, const Plan &p, int bin, const V *Aval, const V *Bval,
-                            const int64_t *crp, int32_t *ccol, V *cval)
+                            int32_t *ccol, V *cval)
 {
     const int cnt = p.hdr.seg.count[bin];
     if (!cnt) return SMASH_OK;
-    const int *hrows = p.sym_perm + p.hdr.sym.offset[kBinHeavy];
     const Seg *segs = p.segs + p.hdr.seg.offset[bin];
     return launch(c, K_NUM_SEG, s, [&] {
-        k_num_seg<V, LOGT, THREADS><<<cnt, THREADS, 0, s>>>(p.A.row_ptr, p.A.col_idx, Aval, p.B.col_idx, Bval, p.bsplit, (long long)(p.nchunks + 1),
-                                                     hrows, segs, p.nchunks, p.woff, (const long long *)crp, ccol,
-                                                     cval, c->d_numerr);
+        k_num_seg<V, LOGT, THREADS><<<cnt, THREADS, 0, s>>>(p.A.col_idx, Aval, p.B.col_idx, Bval, p.bsplit,
+                                                            (long long)(p.nchunks + 1), segs, ccol, cval, c->d_numerr);
     });
 }
 
@@ -628,10 +626,10 @@ smash_status numeric_impl(smash_ctx c, hipStream_t s, const Plan &p, const V *Av
     if (p.heavy_mode == 0) {
         // segments of up to 128 entries are hashed by one wave (table of 256
         // slots), larger ones ranked
-        TRY(launch_seg_bin<V, 8, 64>(c, s, p, 0, Aval, Bval, crp, ccol, cval));
+        TRY(launch_seg_bin<V, 8, 64>(c, s, p, 0, Aval, Bval, ccol, cval));
         const int nr = p.hdr.seg.count[1];
         if (nr && short_ranges(7, (long long)p.hdr.products, p.A.nnz)) {
-            TRY(launch_seg_bin<V, 12, 512>(c, s, p, 1, Aval, Bval, crp, ccol, cval));
+            TRY(launch_seg_bin<V, 12, 512>(c, s, p, 1, Aval, Bval, ccol, cval));
         } else if (nr) {
             const int grid = std::min(nr, resident_blocks(c, (const void *)k_num_rank<V>, kRankThreads, 0));
             TRY(launch(c, K_NUM_SEG, s, [&] {

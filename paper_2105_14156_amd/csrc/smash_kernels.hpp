@@ -2746,11 +2746,9 @@ __global__ __launch_bounds__(kWave) void k_seg_scan(int nchunks, int *__restrict
 // coalesced stores.
 template <typename V, int LOGT, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_num_seg(
-    const int *__restrict__ Arp, const int *__restrict__ Acol, const V *__restrict__ Aval,
-    const int *__restrict__ Bcol, const V *__restrict__ Bval, const int *__restrict__ Bsplit, long long per,
-    const int *__restrict__ heavy_rows, const Seg *__restrict__ segs, int nchunks,
-    const int *__restrict__ woff, const long long *__restrict__ Crp, int *__restrict__ Ccol,
-    V *__restrict__ Cval, int *err)
+    const int *__restrict__ Acol, const V *__restrict__ Aval, const int *__restrict__ Bcol,
+    const V *__restrict__ Bval, const int *__restrict__ Bsplit, long long per, const Seg *__restrict__ segs,
+    int *__restrict__ Ccol, V *__restrict__ Cval, int *err)
 {
     constexpr int T = 1 << LOGT;
     constexpr int SPT = T / THREADS;
