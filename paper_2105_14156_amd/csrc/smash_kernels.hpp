@@ -63,8 +63,9 @@ constexpr int kDenseMin = 1024;         // chunks with more entries are accumula
 constexpr int kSegCap = 2048;           // entries of one segment
 constexpr int kSegMaxSpan = 16;         // chunks spanned by one segment
 constexpr int kSegHash = 128;           // segments of at most this many entries are hashed
-constexpr int kSegBins = 3;             // hashed segments, ranked segments, dense chunks
-constexpr int kSegDense = 2;
+constexpr int kSegBins = 4;             // segments hashed by a wave, ranked, hashed by a block; dense chunks
+constexpr int kSegDense = 3;
+constexpr int kRankEntries = 256;       // A entries up to which a row's segments are ranked (k_num_rank)
 constexpr int kBinBlockRows = 1024;     // rows per block of the binning kernels
 
 enum : int {
@@ -1573,9 +1574,7 @@ constexpr int kRankMaxCols = kRankColsPerSlot << kMaxLogT;      // 2^17: 16-bit 
 // than kRankColsPerSlot columns a slot the hashed form has to sort: rows of 450,
 // 131072 columns, length 1: 1.61 and 1.78, length 2: 1.27 and 1.02; rows of
 // 220, 65536 columns, whose blocks hold 64 KB by bitmap, length 2: 0.86 and 0.98,
-// length 3: 0.87 both.  Ranked segments of heavy rows take the row's entries
-// twice where they do not fit one list: rows of 3000, length 1, 200000
-// columns: 1.83 ms a call hashed in tables of 4096 slots, 3.40 ranked.
+// length 3: 0.87 both.
 inline bool short_ranges(int halves, long long products, long long entries) { return 2 * products < halves * entries; }
 
 __host__ __device__ __forceinline__ int rank_words(int ncols) { return ((ncols + 31) / 32 + 7) & ~7; }
@@ -2615,9 +2614,20 @@ __global__ __launch_bounds__(256) void k_chunk_prefix(const BinHdr *sh, int nchu
 // consecutive chunks are merged while the count stays <= kSegCap and the
 // span <= kSegMaxSpan chunks.  Pass 0 counts segments per block and bin;
 // pass 1 writes them at offset[bin] + block base + rank in block.
-__device__ __forceinline__ int seg_bin(int count, bool dense)
+//
+// Segments of more than kSegHash entries are ranked where the row's A entries
+// fit one list, and hashed by a block where they do not: a ranked segment then
+// lists them and loads its products twice, and as it has at most 2048 entries,
+// most of their ranges hold few products or none, which leaves most lanes of a
+// piece idle.  Rows of 300 entries times B rows of 20, 60 and 150 in 1M columns:
+// hashed 2.40, 3.66 and 7.23 ms a call, ranked 3.51, 4.64 and 9.65 (400 entries
+// the same; 3000 times 32: 20.9 and 35.8).  Rows of 100 entries times 100 in
+// 300000 columns: hashed 1.77, ranked 0.99; of 200 times 200 in 1M: 2.29 and
+// 1.67.  RMAT scale 16, edge factor 16, times B rows of 16 in 200000 columns,
+// rows of all lengths: 0.83, all hashed 0.87, all ranked 0.88.
+__device__ __forceinline__ int seg_bin(int count, int entries, bool dense)
 {
-    return dense ? kSegDense : (count <= kSegHash ? 0 : 1);
+    return dense ? kSegDense : count <= kSegHash ? 0 : entries <= kRankEntries ? 1 : 2;
 }
 
 template <typename F>
@@ -2649,7 +2659,7 @@ __device__ __forceinline__ void plan_row_segments(const int *__restrict__ wc, in
 // every segment at its (bin, chunk) cursor.  Blocks aggregate their counts
 // in LDS (one global atomic per block and group) when the kSegBins x nchunks
 // histogram fits kSegPlanLds entries.
-constexpr int kSegPlanLds = 4096;
+constexpr int kSegPlanLds = 5464;       // 1366 chunks
 
 __global__ __launch_bounds__(256) void k_seg_plan(int pass, const BinHdr *bh, const int *__restrict__ perm,
                                                   int nchunks, const int *__restrict__ wcnt,
@@ -2670,11 +2680,17 @@ __global__ __launch_bounds__(256) void k_seg_plan(int pass, const BinHdr *bh, co
     __syncthreads();
     const int h = blockIdx.x * blockDim.x + threadIdx.x;
     const int *wc = wcnt + (long long)h * nchunks;
+    int row = 0, e0 = 0, e1 = 0;
+    if (h < nheavy) {
+        row = heavy_rows[h];
+        e0 = Arp[row];
+        e1 = Arp[row + 1];
+    }
     // count this block's segments per (bin, chunk)
     if (h < nheavy) {
         long long lnnz[kSegBins] = {};
         plan_row_segments(wc, nchunks, [&](int a, int, int n, bool dense) {
-            const int b = seg_bin(n, dense);
+            const int b = seg_bin(n, e1 - e0, dense);
             if (pass == 0) {
                 if (local) atomicAdd(&s_cnt[b * nchunks + a], 1);
                 else atomicAdd(&hist[(long long)b * nchunks + a], 1);
@@ -2702,12 +2718,10 @@ __global__ __launch_bounds__(256) void k_seg_plan(int pass, const BinHdr *bh, co
             s_cnt[t] = s_cnt[t] ? atomicAdd(&hist[t], s_cnt[t]) : 0;
     __syncthreads();
     if (h < nheavy) {
-        const int row = heavy_rows[h];
-        const int e0 = Arp[row], e1 = Arp[row + 1];
         const long long rb = Crp[row];
         const int *wo = woff + (long long)h * nchunks;
         plan_row_segments(wc, nchunks, [&](int a, int b, int n, bool dense) {
-            const int bin = seg_bin(n, dense);
+            const int bin = seg_bin(n, e1 - e0, dense);
             const int cell = bin * nchunks + a;
             const int pos = local ? atomicAdd(&s_cnt[cell], 1) : atomicAdd(&hist[cell], 1);
             segs[pos] = Seg{row, e0, e1, a, b, n, rb + wo[a]};
@@ -2822,8 +2836,8 @@ __global__ __launch_bounds__(THREADS) void k_num_seg(
 // rank is two LDS reads, so a second pass adds each product straight into its
 // entry's sum and notes its column: no table, no probing, and the entries are
 // in column order when the pass ends.  Products are loaded once, into
-// registers (HOLD steps per wave; more than that, or more A entries than one
-// list holds, takes them from memory twice).
+// registers (HOLD steps per wave; more than that takes them from memory
+// twice).
 //
 // A segment has some 1900 products, four per thread, so a block that starts
 // from nothing spends its time in a chain of six memory latencies.  The grid
@@ -2835,7 +2849,6 @@ __global__ __launch_bounds__(THREADS) void k_num_seg(
 // persistent grid, 13.9 loading the products twice, 12.9 with four waves;
 // hashed segments of up to 1024 entries in 8 chunks (3.4M of them) took 21.3.
 constexpr int kRankThreads = 512;
-constexpr int kRankEntries = 256;       // A entries listed per step
 constexpr int kRankWords = kSegMaxSpan * kChunkWords;
 
 template <typename V>

@@ -687,3 +687,28 @@ def test_global_list_fills_table(sm, ctx, oracle_mod, dtype, count):
     ctx.set_option(sm.OPT_HEAVY_MODE, 1)
     full_check(sm, ctx, A, B, dtype, oracle_mod, False, f"global list of {count}")
     assert ctx.stats()["rows_heavy"] == 2
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("per_row,short", [(5, 0), (9, 0), (70, 0), (9, 60), (70, 60)])
+def test_segments_by_row_length(sm, ctx, oracle_mod, dtype, per_row, short):
+    """Heavy rows around 256 A entries (ranked and hashed segments) whose
+    segments hold 129 to 2048 entries in up to 16 chunks, alone and among so many
+    shorter rows that all of them are ranked."""
+    k, n = 2000, 400_000
+    B = syn.uniform_k_per_row(k, n, per_row, 95, dtype)
+    B.col_idx[1::4] //= 16                      # a quarter of the columns in the first chunks
+    B = syn.CSR(k, n, B.row_ptr, np.concatenate([np.sort(B.col_idx[a:b]) for a, b in zip(B.row_ptr[:-1], B.row_ptr[1:])]),
+                B.val)
+    for a, b in zip(B.row_ptr[:-1], B.row_ptr[1:]):
+        c = B.col_idx[a:b]
+        for i in range(1, len(c)):              # strictly increasing again
+            c[i] = max(c[i], c[i - 1] + 1)
+    assert B.col_idx.max() < n
+    lens = np.array([255, 256, 257, 300, 511, 512, 513, 1024, 1025, 1900] if not short else [250] * short + [257, 1100])
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col = (np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens) + np.repeat(np.arange(len(lens)) % 10 * 7, lens)).astype(np.int32)
+    A = syn.CSR(len(lens), k, ptr, col, (2.0 * syn.uniform01(9, 0, len(col)) - 1.0).astype(dtype))
+    full_check(sm, ctx, A, B, dtype, oracle_mod, True, f"rows of {per_row}")
+    st = ctx.stats()
+    assert st["rows_heavy"] > 0 and st["heavy_segments"] > 0, st
