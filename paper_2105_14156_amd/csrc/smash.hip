@@ -625,14 +625,9 @@ smash_status numeric_impl(smash_ctx c, hipStream_t s, const Plan &p, const V *Av
     if (H == 0) return SMASH_OK;
     if (p.heavy_mode == 0) {
         // segments of up to 128 entries are hashed by one wave (table of 256
-        // slots), larger ones ranked, or hashed by a block (seg_bin): few of the
-        // latter are ranked with the others, as a launch of their own with a
-        // long tail costs more (RMAT 40009, edge factor 16, FP64: 696 us a call,
-        // 712 with it)
+        // slots), larger ones ranked, or hashed by a block (seg_bin)
         TRY(launch_seg_bin<V, 8, 64>(c, s, p, 0, Aval, Bval, ccol, cval));
-        const int nh = p.hdr.seg.count[2];
-        const bool hash = 4 * (long long)nh > p.hdr.seg.count[1];
-        const int nr = p.hdr.seg.count[1] + (hash ? 0 : nh);            // the bins lie side by side
+        const int nr = p.hdr.seg.count[1];
         if (nr) {
             const int grid = std::min(nr, resident_blocks(c, (const void *)k_num_rank<V>, kRankThreads, 0));
             TRY(launch(c, K_NUM_SEG, s, [&] {
@@ -641,7 +636,7 @@ smash_status numeric_impl(smash_ctx c, hipStream_t s, const Plan &p, const V *Av
                                                            nr, ccol, cval, c->d_numerr);
             }));
         }
-        if (hash) TRY(launch_seg_bin<V, 12, 512>(c, s, p, 2, Aval, Bval, ccol, cval));
+        TRY(launch_seg_bin<V, 12, 512>(c, s, p, 2, Aval, Bval, ccol, cval));
         const int nd = p.hdr.seg.count[kSegDense];
         if (nd) {
             const size_t lds = (size_t)kChunkCols * sizeof(double);

@@ -2624,7 +2624,8 @@ __global__ __launch_bounds__(256) void k_chunk_prefix(const BinHdr *sh, int nchu
 // the same; 3000 times 32: 20.9 and 35.8).  Rows of 100 entries times 100 in
 // 300000 columns: hashed 1.77, ranked 0.99; of 200 times 200 in 1M: 2.29 and
 // 1.67.  RMAT scale 16, edge factor 16, times B rows of 16 in 200000 columns,
-// rows of all lengths: 0.83, all hashed 0.87, all ranked 0.88.
+// rows of all lengths: 0.83, all hashed 0.87, all ranked 0.88.  See k_seg_scan
+// for products that have few of them.
 __device__ __forceinline__ int seg_bin(int count, int entries, bool dense)
 {
     return dense ? kSegDense : count <= kSegHash ? 0 : entries <= kRankEntries ? 1 : 2;
@@ -2730,23 +2731,38 @@ __global__ __launch_bounds__(256) void k_seg_plan(int pass, const BinHdr *bh, co
 }
 
 // Offsets of the segment bins and of every (bin, chunk) group; hist becomes
-// the write cursor of each group (one wave).
+// the write cursor of each group (one wave).  Block-hashed segments that are few
+// beside the ranked ones are ranked, chunk by chunk with these: a launch of their
+// own has a long tail (RMAT 40009, edge factor 16, FP64: 696 us a call, 712 with
+// it), and ranked after the others they read the columns' slices of B again
+// (RMAT scale 21, edge factor 4: 22.2 ms in k_num_rank, 23.5 so).
 __global__ __launch_bounds__(kWave) void k_seg_scan(int nchunks, int *__restrict__ hist, SegHdr *sh, const int *err)
 {
     if (stopped(err)) return;
     const int lane = lane_id();
+    int ranked = 0, hashed = 0;
+    for (int c = lane; c < nchunks; c += kWave) {
+        ranked += hist[nchunks + c];
+        hashed += hist[2LL * nchunks + c];
+    }
+    const bool join = 4LL * wave_sum(hashed) <= wave_sum(ranked);
     int run = 0;
     for (int b = 0; b < kSegBins; ++b) {
         if (lane == 0) sh->offset[b] = run;
         const int start = run;
-        for (int c0 = 0; c0 < nchunks; c0 += kWave) {
-            const int c = c0 + lane;
-            const long long at = (long long)b * nchunks + c;
-            const int v = c < nchunks ? hist[at] : 0;
-            const int incl = wave_incl_scan(v);
-            if (c < nchunks) hist[at] = run + incl - v;
-            run += __shfl(incl, kWave - 1, kWave);
-        }
+        if (!(join && b == 2))
+            for (int c0 = 0; c0 < nchunks; c0 += kWave) {
+                const int c = c0 + lane;
+                const long long at = (long long)b * nchunks + c;
+                const int own = c < nchunks ? hist[at] : 0;
+                const int v = own + (join && b == 1 && c < nchunks ? hist[at + nchunks] : 0);
+                const int incl = wave_incl_scan(v);
+                if (c < nchunks) {
+                    hist[at] = run + incl - v;
+                    if (join && b == 1) hist[at + nchunks] = run + incl - v + own;
+                }
+                run += __shfl(incl, kWave - 1, kWave);
+            }
         if (lane == 0) sh->count[b] = run - start;
     }
     if (lane == 0) sh->offset[kSegBins] = run;
