@@ -640,16 +640,19 @@ smash_status numeric_impl(smash_ctx c, hipStream_t s, const Plan &p, const V *Av
         const int nd = p.hdr.seg.count[kSegDense];
         if (nd) {
             const size_t lds = (size_t)kChunkCols * sizeof(double);
-            (void)hipFuncSetAttribute((const void *)k_num_dense<V>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            const bool shrt = p.nchunks <= kDenseShortChunks &&
+                              short_ranges(4, (long long)p.hdr.products, (long long)p.A.nnz * p.nchunks);
+            auto kern = shrt ? k_num_dense<V, true> : k_num_dense<V, false>;
+            (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             // persistent: as many blocks as are resident at once, fed by a queue
-            const int grid = std::min(nd, resident_blocks(c, (const void *)k_num_dense<V>, kDenseThreads, lds));
+            const int grid = std::min(nd, resident_blocks(c, (const void *)kern, kDenseThreads, lds));
             TRY(launch(c, K_FILL, s, [&] { k_fill_i32<<<1, kWave, 0, s>>>(1, p.queue, 0); }));
             TRY(launch(c, K_NUM_DENSE, s, [&] {
-                k_num_dense<V><<<grid, kDenseThreads, lds, s>>>(p.A.col_idx, Aval, p.B.col_idx, Bval, p.bsplit,
-                                                               (long long)(p.nchunks + 1),
-                                                               p.segs + p.hdr.seg.offset[kSegDense], nd,
-                                                               nd >= kDenseClaimMinPerBlock * grid ? kDenseClaim : 1,
-                                                               ccol, cval, c->d_numerr, p.queue);
+                kern<<<grid, kDenseThreads, lds, s>>>(p.A.col_idx, Aval, p.B.col_idx, Bval, p.bsplit,
+                                                      (long long)(p.nchunks + 1),
+                                                      p.segs + p.hdr.seg.offset[kSegDense], nd,
+                                                      nd >= kDenseClaimMinPerBlock * grid ? kDenseClaim : 1, ccol, cval,
+                                                      c->d_numerr, p.queue);
             }));
         }
         return SMASH_OK;

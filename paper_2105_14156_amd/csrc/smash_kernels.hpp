@@ -3138,14 +3138,25 @@ __device__ __forceinline__ void wave_store_ranked(const double (&vr)[ROUNDS], co
 // four instead of up to eight products per thread in flight 16.9.  Chunks
 // dealt ahead, their A entries and split points fetched while the one before
 // is ranked, were no faster (15.1).
+//
+// SHORT: a product per lane instead of a piece, for chunks in which the average
+// A entry selects fewer than two products, so that most lanes of a piece have
+// none.  8192 rows of 5000 entries, B rows of one, 4096 columns: 1.81 ms a call,
+// by pieces 2.09; 20000 entries, B rows of 4, 20000 columns: 0.85 and 1.10,
+// 200000 columns 3.63 and 5.02 (4.56 and 5.02 with two and four products per
+// thread in flight); 3000 entries, B rows of 16, 4096 columns: 0.77 and 0.75.  In wide products, whose dense
+// chunks are few and not average, the other way round (RMAT scale 20, edge
+// factor 4, 256 chunks, three products: 18.8 and 18.1; scale 21, 3: 40.8 and
+// 40.1), hence not beyond kDenseShortChunks.
 constexpr int kDenseThreads = 512;
+constexpr int kDenseShortChunks = 64;
 // dense chunks a block claims with one atomic on the queue when every block
 // has many to do (one atomic per chunk from every resident block serialises
 // on the counter); one at a time otherwise, for the balance of the tail
 constexpr int kDenseClaim = 4;
 constexpr int kDenseClaimMinPerBlock = 256;
 
-template <typename V>
+template <typename V, bool SHORT>
 __global__ __launch_bounds__(kDenseThreads) void k_num_dense(
     const int *__restrict__ Acol, const V *__restrict__ Aval, const int *__restrict__ Bcol,
     const V *__restrict__ Bval, const int *__restrict__ Bsplit, long long per, const Seg *__restrict__ segs, int nseg,
@@ -3156,7 +3167,7 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_dense(
     constexpr int ROUNDS = CPW / kWave;
     extern __shared__ __align__(16) unsigned char s_raw[];
     double *acc = (double *)s_raw;                      // [kChunkCols]
-    __shared__ PieceScratch<V, G> S;
+    __shared__ std::conditional_t<SHORT, EnumScratch<V, G>, PieceScratch<V, G>> S;
     __shared__ int s_wt[NW];
     __shared__ int s_next;
     const int gt = threadIdx.x, lane = lane_id(), wg = gt / kWave;
@@ -3179,7 +3190,19 @@ __global__ __launch_bounds__(kDenseThreads) void k_num_dense(
                 if (ok[u]) atomicAdd(&acc[j[u] - lo], p[u] + 0.0);
         };
         // its first barrier also says that the previous chunk is fully written
-        piece_products<V, true, G, G, 4>(sg.e0, sg.e1, gt, S, Acol, Aval, split0, per, 1, Bcol, Bval, sink);
+        if constexpr (SHORT) {
+            auto get = [&](int e, int &bs, int &bl, V &a) {
+                const int k = Acol[e];
+                bs = split0[k * per];
+                bl = split0[k * per + 1] - bs;
+                a = Aval[e];
+            };
+            group_products<V, true, G, 1, decltype(get), decltype(sink), true>(sg.e0, sg.e1, gt, S, Bcol, Bval, get,
+                                                                               sink);
+            __syncthreads();
+        } else {
+            piece_products<V, true, G, G, 4>(sg.e0, sg.e1, gt, S, Acol, Aval, split0, per, 1, Bcol, Bval, sink);
+        }
         double vr[ROUNDS];
         unsigned long long msk[ROUNDS];
         int wcount = 0;

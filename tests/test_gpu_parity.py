@@ -690,6 +690,22 @@ def test_global_list_fills_table(sm, ctx, oracle_mod, dtype, count):
 
 
 @pytest.mark.parametrize("dtype", [np.float32, np.float64])
+@pytest.mark.parametrize("n,per_row", [(8192, 1), (8192, 2), (8193, 1), (64 * 8192, 1), (64 * 8192 + 1, 1)])
+def test_dense_chunks_of_short_rows(sm, ctx, oracle_mod, dtype, n, per_row):
+    """Dense chunks whose A entries select few products each, on both sides of
+    the lines between a product per lane and pieces; entry lists of one, of 512
+    and of 513 entries among them."""
+    k = 200_000
+    B = syn.uniform_k_per_row(k, n, per_row, 97, dtype)
+    lens = np.array([1, 512, 513, 3000, 5000, 0, 150_000 if n > 100_000 else 20_000])
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col = (np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens) + np.repeat(np.arange(7) * 11, lens)).astype(np.int32)
+    A = syn.CSR(7, k, ptr, col, (2.0 * syn.uniform01(9, 0, len(col)) - 1.0).astype(dtype))
+    full_check(sm, ctx, A, B, dtype, oracle_mod, True, f"{n} columns, rows of {per_row}")
+    assert ctx.stats()["heavy_dense_chunks"] > 0
+
+
+@pytest.mark.parametrize("dtype", [np.float32, np.float64])
 @pytest.mark.parametrize("per_row,short", [(5, 0), (9, 0), (70, 0), (9, 60), (70, 60)])
 def test_segments_by_row_length(sm, ctx, oracle_mod, dtype, per_row, short):
     """Heavy rows around 256 A entries (ranked and hashed segments) whose
