@@ -1108,7 +1108,7 @@ __device__ __forceinline__ float row_feature(int t, int na, long long ub, double
 // the only rows the predictor is asked about.
 //
 // Bound by the latency of two dependent gathers per entry, so the work is
-// spread for it (for_rows): rows of at most kShortRow entries are summed by
+// spread for it (for_rows): rows of at most short_row entries are summed by
 // groups of eight lanes, consecutive rows in consecutive groups; longer rows by
 // a whole wave, eight entries per lane in flight, and the rows a wave looks
 // at lie an odd stride apart, since hub rows come in clusters (consecutive
@@ -1116,11 +1116,12 @@ __device__ __forceinline__ float row_feature(int t, int na, long long ub, double
 // entries): 0.23 ms; with eight consecutive rows per wave, long ones summed by
 // the wave in turn, 0.58.  The limit: a wave has at most a few entries per lane
 // of rows just above it and waits for each row's gathers in turn (features of a
-// million rows of 150 entries with a limit of 128: 0.93 ms, 256: 0.67), eight
+// million rows of 150 entries with a limit of 128: 0.77 ms, 256: 0.66), eight
 // lanes take longer with longer rows (RMAT scale 20, edge factor 8: 0.150 ms,
-// 512: 0.176).
+// 512: 0.176).  From a million and a half rows on, whose clusters of such rows
+// are longer, the lower limit (RMAT scale 21, edge factor 8: 0.246 and 0.277 ms).
 constexpr int kRowLanes = 8;
-constexpr int kShortRow = 256;
+constexpr int kShortRow = 256;          // 128 in tall matrices: short_row
 constexpr int kRowThreads = 256;
 constexpr int kBlockRows = kRowThreads / kRowLanes;
 
@@ -1205,6 +1206,8 @@ __host__ __device__ __forceinline__ int long_row_blocks(int m)
     const int per = k >= 20 ? 6 : k >= 16 ? k - 14 : k >= 14 ? 2 : k >= 12 ? k - 12 : 0;      // log2 rows per wave
     return (int)((((long long)m + (1 << per) - 1) >> per) / (kRowThreads / kWave)) + 1;
 }
+// Entries up to which for_rows sums a row of m by eight lanes.
+__device__ __forceinline__ int short_row(int m) { return m > 3 << 19 ? kShortRow / 2 : kShortRow; }
 __host__ __device__ __forceinline__ int row_blocks(int m)
 {
     return long_row_blocks(m) + (m + kBlockRows - 1) / kBlockRows;
@@ -1222,7 +1225,7 @@ __device__ __forceinline__ void for_rows(int m, const int *__restrict__ Arp, con
         if (w == waves) return;
         const long long row = (long long)lane * waves + w;
         const int e0 = row < m ? Arp[row] : 0, e1 = row < m ? Arp[row + 1] : 0;
-        for (unsigned long long todo = __ballot(e1 - e0 > kShortRow); todo; todo &= todo - 1) {
+        for (unsigned long long todo = __ballot(e1 - e0 > short_row(m)); todo; todo &= todo - 1) {
             const int src = __ffsll((long long)todo) - 1;
             const int f0 = __builtin_amdgcn_readlane(e0, src), f1 = __builtin_amdgcn_readlane(e1, src);
             RowPart r;
@@ -1234,7 +1237,7 @@ __device__ __forceinline__ void for_rows(int m, const int *__restrict__ Arp, con
     }
     const int row = ((int)blockIdx.x - nl) * kBlockRows + (int)threadIdx.x / kRowLanes, sl = lane & (kRowLanes - 1);
     const int e0 = row < m ? Arp[row] : 0, e1 = row < m ? Arp[row + 1] : 0;
-    const bool here = row < m && e1 - e0 <= kShortRow;
+    const bool here = row < m && e1 - e0 <= short_row(m);
     RowPart r;
     if (here) row_part<FEATS>(Acol, Brp, e0 + sl, e1, kRowLanes, r);
     row_reduce<FEATS>(r, kRowLanes);

@@ -73,6 +73,29 @@ def test_features_long_row_split(env, m):
     np.testing.assert_allclose(F, mlp.features(X, Y), rtol=2e-6, atol=1e-6)
 
 
+@pytest.mark.parametrize("m", [3 << 19, (3 << 19) + 1])
+def test_features_tall(env, m):
+    """Rows around both limits between eight lanes and a wave (128 and 256
+    entries) where the lower one begins to apply."""
+    torch, smash, ctx = env
+    lens = np.arange(m) % 2
+    at = np.array([0, 1, 2, 63, 64, 1000, m // 2, m - 70, m - 2, m - 1])
+    lens[at] = [127, 128, 129, 255, 256, 257, 1500, 200, 128, 129]
+    cols = 2500
+    ptr = np.zeros(m + 1, np.int32)
+    ptr[1:] = np.cumsum(lens)
+    col = (np.arange(ptr[-1]) - np.repeat(ptr[:-1], lens) + np.repeat(np.arange(m) % 900, lens)).astype(np.int32)
+    X = syn.CSR(m, cols, ptr, col, np.ones(len(col), np.float32))
+    Y = syn.rmat_rect(cols, 4, 9, np.float32)
+    got = ctx.features(smash.to_device(X), smash.to_device(Y)).cpu().numpy()
+    some = np.unique(np.concatenate([at, np.arange(0, m, 997)]))
+    n = lens[some]
+    sptr = np.concatenate([[0], np.cumsum(n)]).astype(np.int32)
+    scol = np.concatenate([col[ptr[i]:ptr[i + 1]] for i in some])
+    part = syn.CSR(len(some), cols, sptr, scol, np.ones(len(scol), np.float32))
+    np.testing.assert_allclose(got[some], mlp.features(part, Y), rtol=2e-6, atol=1e-6)
+
+
 def _setup(torch, n=3000, seed=3):
     F = np.abs(syn.normal01(seed, 0, n * 6).reshape(n, 6)) * 4
     y = F[:, 1] * 0.7 + np.sin(F[:, 0]) + 0.1 * syn.normal01(seed + 1, 0, n)
