@@ -96,8 +96,9 @@ typedef enum {
      * entries leave the LDS row tables for the heavy-row path.  Range
      * 32..1024, default 1024. */
     SMASH_OPT_LDS_ROW_MAX = 1,
-    /* Heavy-row path: 0 = column segments merged in LDS, hashed or, for
-     * chunks with more than 1024 of their 8192 columns, accumulated by column (default);
+    /* Heavy-row path: 0 = column segments merged in LDS, by the ranks of a
+     * column bitmap or hashed or, for chunks with more than 1024 of their 8192
+     * columns, accumulated by column (default);
      * 1 = one hash table per row in global memory (the paper's third
      * version, "Fragmenting Memory", moves the table to DRAM), behind a
      * small LDS table for the columns that come first. */

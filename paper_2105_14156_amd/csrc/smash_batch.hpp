@@ -9,9 +9,10 @@
 // host synchronisation: analysis, binning, symbolic per bin, one row-pointer
 // scan over the batch (each C_p lands at a device-computed offset of one
 // output pool), numeric per bin.  Rows whose bound exceeds the LDS hash
-// limit are counted in an LDS bitmap over B's columns and accumulated in LDS
-// windows of columns (per-row global tables only for problems wider than
-// kWideMaxCols columns).
+// limit are counted in an LDS bitmap over B's columns and merged at the ranks
+// of such a bitmap (up to kRankMaxCols columns) or accumulated in LDS windows
+// of columns (wide_rank_row); per-row global tables only for problems wider
+// than kWideMaxCols columns.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -41,8 +42,10 @@ struct BatchHdr {
 };
 
 // Heavy rows of problems with at most kWideMaxCols columns are counted with
-// an LDS bitmap over all columns and accumulated in LDS windows of
-// kWideWin columns; wider problems use per-row global tables.
+// an LDS bitmap over all columns and merged by bitmap ranks or, where that
+// would take too many passes over their products and beyond kRankMaxCols
+// columns, in LDS windows of kWideWin columns; wider problems use per-row
+// global tables.
 constexpr int kWideMaxCols = 1 << 20;
 constexpr int kWideWin = 8192;
 constexpr int kWideThreads = 512;

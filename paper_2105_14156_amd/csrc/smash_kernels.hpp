@@ -13,21 +13,24 @@
 //     segment of a heavy row) and its LDS table; rows are binned by table
 //     size so each bin launches a workgroup shape that fits its rows (the
 //     paper's windows sized to the scratchpad);
-//   * the products of a row are enumerated "flat": the group loads a chunk of
-//     A's row, prefix-sums the lengths of the B rows it selects, and every
-//     thread takes products q = t, t + G, ... of the concatenation, so a long
-//     B row and many short ones keep every lane busy (the paper gives each
-//     row two threads for the same reason, "SMASH Version 2: Tokenization");
-//     several products per thread are loaded before any is merged, to keep
-//     loads in flight;
+//   * the group loads a chunk of A's row and prefix-sums the lengths of the B
+//     rows it selects; their products are enumerated in pieces of 8 or 16
+//     consecutive entries, each piece located once for its lanes, or, where
+//     the ranges are too short to fill pieces (short_ranges), "flat", every
+//     thread taking products q = t, t + G, ... of the concatenation (the paper
+//     gives each row two threads for the same reason, "SMASH Version 2:
+//     Tokenization"); several products per thread are loaded before any is
+//     merged, to keep loads in flight;
 //   * slots come from a multiplicative (Fibonacci) hash of the column, which
 //     spreads clustered columns like the paper's low-order-bit hash of
 //     version 2, with +1 linear probing;
 //   * heavy rows (output bound above the LDS row limit) are cut into column
 //     segments of at most kSegCap entries using per-8192-column counts from
-//     the symbolic phase.  Sparse segments are hashed in LDS; chunks denser
-//     than kSegCap are accumulated directly by column (the paper's per-row
-//     dense/sparse decision of the Window Distribution Phase).  Optionally a
+//     the symbolic phase.  Small segments, and those of rows with many A
+//     entries, are hashed in LDS, the others merged at the ranks of a column
+//     bitmap (seg_bin); chunks with more than kDenseMin entries are
+//     accumulated directly by column (the paper's per-row dense/sparse
+//     decision of the Window Distribution Phase).  Optionally a
 //     heavy row instead uses one hash table in global memory (version 3,
 //     "Fragmenting Memory").
 //   * output is written in column order: ranks from an occupancy bitmap of
@@ -59,10 +62,14 @@ constexpr int kBatchBins = kNumBins + 2;
 constexpr int kChunkCols = 8192;        // column granularity of heavy-row counts
 constexpr int kChunkWords = kChunkCols / 32;
 constexpr int kSymWinChunks = 16;       // symbolic heavy window: 16 chunks, 16 KiB bitmap
-constexpr int kDenseMin = 1024;         // chunks with more entries are accumulated by column
+// Chunks with more entries are accumulated by column.  RMAT A * A in ms a call
+// with 512, 1024 and 2048: scale 16, edge factor 16: 2.10, 1.82, 1.76; 17, 4: 1.18,
+// 1.05, 1.08; 18, 8: 6.04, 5.25, 5.32; scale 16 times 16 per row of 200000 columns
+// 0.82, 0.82, 0.86.
+constexpr int kDenseMin = 1024;
 constexpr int kSegCap = 2048;           // entries of one segment
 constexpr int kSegMaxSpan = 16;         // chunks spanned by one segment
-constexpr int kSegHash = 128;           // segments of at most this many entries are hashed
+constexpr int kSegHash = 128;           // segments of at most this many entries are hashed by a wave
 constexpr int kSegBins = 4;             // segments hashed by a wave, ranked, hashed by a block; dense chunks
 constexpr int kSegDense = 3;
 constexpr int kRankEntries = 256;       // A entries up to which a row's segments are ranked (k_num_rank)
@@ -1043,6 +1050,12 @@ __global__ __launch_bounds__(256) void k_validate_cols(int cols, long long nnz, 
 // bitmap: an entry not above its predecessor looks for itself among the row
 // pointers (a search of 13 steps, made about once per row).  Without `strict`
 // only what memory safety needs is checked.
+//
+// Up to kFewRows rows every step of a product is one launch.  The line lies
+// where that stops to pay: products of 8192 rows in us a call, so and with a
+// launch per bin: 16 products a row 126 and 143, 100 in 1M columns 208 and 218,
+// 400 there 354 and 329, 900 in 4096 columns 240 and 185; RMAT scale 13, edge
+// factor 4 175 and 203, 16 270 and 290.
 constexpr int kFewRows = 8192;
 
 __global__ __launch_bounds__(256) void k_validate_few(int rows, int cols, long long nnz, const int *__restrict__ rp,
@@ -3147,10 +3160,10 @@ __device__ __forceinline__ void wave_store_ranked(const double (&vr)[ROUNDS], co
 // none.  8192 rows of 5000 entries, B rows of one, 4096 columns: 1.81 ms a call,
 // by pieces 2.09; 20000 entries, B rows of 4, 20000 columns: 0.85 and 1.10,
 // 200000 columns 3.63 and 5.02 (4.56 and 5.02 with two and four products per
-// thread in flight); 3000 entries, B rows of 16, 4096 columns: 0.77 and 0.75.  In wide products, whose dense
-// chunks are few and not average, the other way round (RMAT scale 20, edge
-// factor 4, 256 chunks, three products: 18.8 and 18.1; scale 21, 3: 40.8 and
-// 40.1), hence not beyond kDenseShortChunks.
+// thread in flight); 3000 entries, B rows of 16, 4096 columns: 0.77 and 0.75.
+// In wide products, whose dense chunks are few and not average, the other way
+// round (RMAT scale 20, edge factor 4, 256 chunks, three products: 18.8 and
+// 18.1; scale 21, 3: 40.8 and 40.1), hence not beyond kDenseShortChunks.
 constexpr int kDenseThreads = 512;
 constexpr int kDenseShortChunks = 64;
 // dense chunks a block claims with one atomic on the queue when every block

@@ -8,8 +8,11 @@
 // Training minimises the mean squared error with Adam (Kingma and Ba 2015)
 // on batches of rows whose exact counts come from the symbolic phase.
 // Reductions over a batch use fixed orders (no atomics), so training is
-// deterministic.  The network is far too small for matrix cores to matter
-// (about 4.5K multiply-adds per row); every layer is plain FMA.
+// deterministic.  Predictions for many rows run on the FP32 matrix
+// instructions (k_mlp_rows), and training's FP64 gradient sums on the FP64 ones
+// (k_mlp_step).  The capacities of the fused pass are plain FMA (k_mlp_predict):
+// only rows above the LDS limit are asked about, often one among the rows of a
+// wave, too few for a matrix tile.
 #pragma once
 
 #include <hip/hip_runtime.h>
